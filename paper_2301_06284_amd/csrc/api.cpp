@@ -369,7 +369,7 @@ extern "C" rgnn_status rgcn_forward(const rgnn_graph_t *g, const float *h, const
         ga.split_bf16 = 1;
         ga.X = h; ga.ldx = d_in; ga.gather = g->dev.uniq_src;
         ga.W[0] = W; ga.K = d_in; ga.Nc = d_out;
-        ga.tiles = g->dev.tiles_pairs; ga.ntiles = g->n_tiles_pairs;
+        ga.tiles = g->gemm_tiles(kRowsPairs);
         ga.Y = w.M; ga.ldy = d_out;
         if ((st = launch_typed_gemm(ga, s)) != RGNN_OK) return st;
         TravArgs ta;
@@ -393,7 +393,7 @@ extern "C" rgnn_status rgcn_forward(const rgnn_graph_t *g, const float *h, const
         GemmArgs ga;
         ga.split_bf16 = 1;
         ga.X = h; ga.ldx = d_in; ga.W[0] = W0; ga.K = d_in; ga.Nc = d_out;
-        ga.tiles = g->dev.tiles_all; ga.ntiles = g->n_tiles_all;
+        ga.tiles = g->gemm_tiles(kRowsAll);
         ga.Y = out; ga.ldy = d_out;
         ga.ep.accumulate = 1; ga.ep.relu = relu;
         if ((st = launch_typed_gemm(ga, s)) != RGNN_OK) return st;
@@ -488,7 +488,7 @@ rgnn_status rgat_forward_impl(const rgnn_graph *g, const float *h, const float *
         gd.split_bf16 = 1;
         gd.X = h; gd.ldx = d_in; gd.gather = g->dev.vsegdst_byrel;
         gd.W[0] = W; gd.K = d_in; gd.Nc = d_out;
-        gd.tiles = g->dev.tiles_vsegs; gd.ntiles = g->n_tiles_vsegs;
+        gd.tiles = g->gemm_tiles(kRowsVsegs);
         gd.Y = w.T; gd.ldy = d_out; gd.scatter = g->dev.vseg_byrel;
         gd.ep.dot_vec = w_dst; gd.ep.dot_out = w.vatt; gd.ep.dot_heads = heads;
         if ((st = launch_typed_gemm(gd, s)) != RGNN_OK) return st;
@@ -506,7 +506,7 @@ rgnn_status rgat_forward_impl(const rgnn_graph *g, const float *h, const float *
         ga.split_bf16 = 1;
         ga.X = h; ga.ldx = d_in; ga.gather = g->dev.uniq_src;
         ga.W[0] = W; ga.K = d_in; ga.Nc = d_out;
-        ga.tiles = g->dev.tiles_pairs; ga.ntiles = g->n_tiles_pairs;
+        ga.tiles = g->gemm_tiles(kRowsPairs);
         ga.Y = w.M; ga.ldy = attmsg ? att_row_ld(d_out, heads) : d_out;
         if (attmsg) {   // the source terms m . w_src[r] per head, written after each row's message
             ga.ep.dot_vec = w_src; ga.ep.dot_out = w.M + d_out; ga.ep.dot_heads = heads; ga.ep.dot_ld = ga.ldy;
@@ -584,7 +584,7 @@ extern "C" rgnn_status hgt_forward(const rgnn_graph_t *g, const float *h, const 
     ga.split_bf16 = 1;
     ga.X = h; ga.ldx = d; ga.gather = g->dev.ntype_perm; ga.scatter = g->dev.ntype_perm;
     ga.K = d;
-    ga.tiles = g->dev.tiles_nodes; ga.ntiles = g->n_tiles_nodes;
+    ga.tiles = g->gemm_tiles(kRowsNodes);
     if (d == 64 && fold_q) {
         ga.W[0] = Wk; ga.W[1] = Wv; ga.nparts = 2;
         ga.Nc = 2 * d;
@@ -632,7 +632,7 @@ extern "C" rgnn_status hgt_forward(const rgnn_graph_t *g, const float *h, const 
         gq.W[0] = w.Wqp; gq.K = d; gq.Nc = d;
         // tiles by destination range: each destination row is gathered by its
         // relations' tiles on one XCD, from L2 after the first
-        gq.tiles = g->dev.tiles_vsegs_dst; gq.ntiles = g->n_tiles_vsegs_dst;
+        gq.tiles = g->gemm_tiles(kRowsVsegsDst);
         gq.Y = w.QP; gq.ldy = d; gq.ep.diag_blocks = fold_q ? 1 : heads;
         if ((st = launch_typed_gemm(gq, s)) != RGNN_OK) return st;
         ha.QP = w.QP;
@@ -646,7 +646,7 @@ extern "C" rgnn_status hgt_forward(const rgnn_graph_t *g, const float *h, const 
         gb.split_bf16 = 1;
         gb.X = w.agg; gb.ldx = d; gb.gather = g->dev.ntype_perm; gb.scatter = g->dev.ntype_perm;
         gb.W[0] = Wa; gb.K = d; gb.Nc = d;
-        gb.tiles = g->dev.tiles_nodes; gb.ntiles = g->n_tiles_nodes;
+        gb.tiles = g->gemm_tiles(kRowsNodes);
         gb.Y = out; gb.ldy = d;
         if (flags & RGNN_FLAG_RESIDUAL) { gb.ep.residual = h; gb.ep.ld_res = d; }
         return launch_typed_gemm(gb, s);
@@ -777,7 +777,7 @@ extern "C" rgnn_status rgnn_segment_gemm(const float *X, int64_t ldx, const int3
     GemmArgs ga;
     ga.split_bf16 = 1;
     ga.X = X; ga.ldx = ldx; ga.gather = gather; ga.W[0] = W; ga.K = K; ga.Nc = Nc;
-    ga.tiles = dt; ga.ntiles = (int64_t)tiles.size();
+    ga.tiles = TileTable{dt, (int64_t)tiles.size(), dt, (int64_t)tiles.size()};
     ga.Y = Y; ga.ldy = ldy; ga.scatter = scatter;
     return launch_typed_gemm(ga, s);
 }

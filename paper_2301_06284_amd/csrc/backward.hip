@@ -940,7 +940,7 @@ size_t bwd_layout(const rgnn_graph *g, int D, void *base, BwdWs *w)
     x.ay = take((size_t)g->E * 2);
     x.ysum = take((size_t)std::max<int64_t>(g->V, 1));
     x.ypair = take((size_t)std::max<int64_t>(g->U_src, 1));
-    x.pvec = take((size_t)std::max<int64_t>(g->n_tiles_pairs, 1) * D);
+    x.pvec = take((size_t)std::max<int64_t>(g->n_gemm_tiles[kRowsPairs][0], 1) * D);
     x.pws = take((size_t)g->R * D);
     x.pwt = take((size_t)g->R * D);
     x.partial = take(nchunks * D * D);
@@ -1207,7 +1207,7 @@ rgnn_status rgat_backward_d(const rgnn_graph *g, const float *h, const float *W,
     GemmArgs ga;
     ga.X = Gm; ga.ldx = D; ga.gather = g->dev.vsegdst_byrel;
     ga.W[0] = W; ga.trans_b = 1; ga.K = D; ga.Nc = D;
-    ga.tiles = g->dev.tiles_vsegs; ga.ntiles = g->n_tiles_vsegs;
+    ga.tiles = g->gemm_tiles(kRowsVsegs);
     ga.Y = w.dS; ga.ldy = D; ga.scatter = nullptr;   // dS rows in by-relation order
     if ((st = launch_typed_gemm(ga, s)) != RGNN_OK) return st;
 
@@ -1288,10 +1288,10 @@ rgnn_status rgat_backward_d(const rgnn_graph *g, const float *h, const float *W,
     }
     if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "bwd_src launch");
     if ((st = launch_src_merge(g, w.part, dh, D, s)) != RGNN_OK) return st;
-    if (g->n_tiles_pairs) {   // dws' per pair tile
+    if (g->n_gemm_tiles[kRowsPairs][0]) {   // dws' per pair tile
         LaunchScope ls("rgat_bwd_pair_gemv", s);
-        hipLaunchKernelGGL(pair_gemv_kernel<D>, dim3((unsigned)g->n_tiles_pairs), dim3(256), 0, s,
-                           g->dev.tiles_pairs, g->dev.uniq_src, w.ypair, h, w.pvec);
+        hipLaunchKernelGGL(pair_gemv_kernel<D>, dim3((unsigned)g->n_gemm_tiles[kRowsPairs][0]), dim3(256), 0, s,
+                           g->dev.gemm_tiles[kRowsPairs][0], g->dev.uniq_src, w.ypair, h, w.pvec);
     }
     if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "pair_gemv launch");
     if (g->n_tiles_outer) {

@@ -899,7 +899,7 @@ rgnn_status mh_backward_dh(const rgnn_graph *g, const float *h, const float *W, 
         GemmArgs ga;
         ga.X = h; ga.ldx = D; ga.gather = x.uniq_src;
         ga.W[0] = W; ga.K = D; ga.Nc = D;
-        ga.tiles = x.tiles_pairs; ga.ntiles = g->n_tiles_pairs;
+        ga.tiles = g->gemm_tiles(kRowsPairs);
         ga.Y = w.M; ga.ldy = D;
         if ((st = launch_typed_gemm(ga, s)) != RGNN_OK) return st;
     }
@@ -1007,7 +1007,7 @@ rgnn_status mh_backward_dh(const rgnn_graph *g, const float *h, const float *W, 
             GemmArgs ga;
             ga.X = dM; ga.ldx = D; ga.gather = nullptr;
             ga.W[0] = W; ga.trans_b = 1; ga.K = D; ga.Nc = D;
-            ga.tiles = x.tiles_pairs; ga.ntiles = g->n_tiles_pairs;
+            ga.tiles = g->gemm_tiles(kRowsPairs);
             ga.Y = w.dHp; ga.ldy = D; ga.scatter = x.pair_smpos;
             if ((st = launch_typed_gemm(ga, s)) != RGNN_OK) return st;
         }

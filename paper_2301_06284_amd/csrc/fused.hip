@@ -420,10 +420,13 @@ bool dispatch(int di, int dout, const FK &k, int64_t n, hipStream_t s)
 rgnn_status launch_af_fused(const FusedArgs &a, hipStream_t s)
 {
     const rgnn_graph *g = a.g;
-    if (g->n_tiles_fused == 0) return RGNN_OK;
+    const TileTable tt = g->fused_tiles();
+    const bool wide = wide_shape(a.d_in, a.d_out);
+    const int64_t ntiles = wide ? tt.n_wide : tt.n_narrow;
+    if (ntiles == 0) return RGNN_OK;
     FK k{};
-    k.rows = g->dev.fused_rows; k.tiles = g->dev.tiles_fused;
-    k.ntiles = g->n_tiles_fused; k.nedges = g->E; k.src = g->dev.fused_src;
+    k.rows = g->dev.fused_rows; k.tiles = wide ? tt.wide : tt.narrow;
+    k.ntiles = ntiles; k.nedges = g->E; k.src = g->dev.fused_src;
     k.h = a.h; k.W = a.W; k.wsp = a.wsp; k.vatt = a.vatt; k.slope = a.slope;
     k.T = a.T; k.vstat = a.vstat; k.S = a.S; k.pos = g->dev.vseg_pos;
     k.out = a.out; k.saved = a.saved; k.relu = a.relu;
@@ -433,9 +436,9 @@ rgnn_status launch_af_fused(const FusedArgs &a, hipStream_t s)
     bool ok;
     {
         LaunchScope ls(a.softmax ? "rgat_af_fused" : (a.S ? "segment_means" : "rgcn_af_fused"), s);
-        ok = a.softmax ? dispatch<kModeSoftmax>(a.d_in, a.d_out, k, g->n_tiles_fused, s)
-             : a.S     ? dispatch<kModeSum>(a.d_in, a.d_out, k, g->n_tiles_fused, s)
-                       : dispatch<kModeMean>(a.d_in, a.d_out, k, g->n_tiles_fused, s);
+        ok = a.softmax ? dispatch<kModeSoftmax>(a.d_in, a.d_out, k, ntiles, s)
+             : a.S     ? dispatch<kModeSum>(a.d_in, a.d_out, k, ntiles, s)
+                       : dispatch<kModeMean>(a.d_in, a.d_out, k, ntiles, s);
     }
     if (!ok) return fail(RGNN_EUNSUPPORTED, "fused aggregation: unsupported (d_in, d_out)");
     hipError_t e = hipGetLastError();

@@ -513,12 +513,14 @@ bool dispatch_rect(int ep, const GemmK &k, int64_t n, hipStream_t s)
 
 rgnn_status launch_typed_gemm(const GemmArgs &a, hipStream_t s)
 {
-    if (a.ntiles == 0) return RGNN_OK;
+    const bool wide = wide_shape(a.K, a.Nc);
+    const int64_t ntiles = wide ? a.tiles.n_wide : a.tiles.n_narrow;
+    if (ntiles == 0) return RGNN_OK;
     GemmK k{};
     k.X = a.X; k.ldx = a.ldx; k.gather = a.gather;
     k.W0 = a.W[0]; k.W1 = a.W[1]; k.W2 = a.W[2];
     k.nparts = a.nparts; k.trans_b = a.trans_b;
-    k.tiles = a.tiles; k.Y = a.Y; k.ldy = a.ldy; k.scatter = a.scatter;
+    k.tiles = wide ? a.tiles.wide : a.tiles.narrow; k.Y = a.Y; k.ldy = a.ldy; k.scatter = a.scatter;
     k.row_scale = a.ep.row_scale;
     k.dot_vec = a.ep.dot_vec; k.dot_out = a.ep.dot_out;
     k.dot_ld = a.ep.dot_ld ? a.ep.dot_ld : a.ep.dot_heads;
@@ -539,27 +541,27 @@ rgnn_status launch_typed_gemm(const GemmArgs &a, hipStream_t s)
     {
         LaunchScope ls("typed_gemm", s);
         const bool sp = a.split_bf16;
-        if (a.K == 32 && a.Nc == 32) ok = dispatch_square<32, 32>(ep, heads, k, a.ntiles, s);
+        if (a.K == 32 && a.Nc == 32) ok = dispatch_square<32, 32>(ep, heads, k, ntiles, s);
         else if (a.K == 64 && a.Nc == 64)
-            ok = sp ? dispatch_square<64, 64, true>(ep, heads, k, a.ntiles, s)
-                    : dispatch_square<64, 64>(ep, heads, k, a.ntiles, s);
+            ok = sp ? dispatch_square<64, 64, true>(ep, heads, k, ntiles, s)
+                    : dispatch_square<64, 64>(ep, heads, k, ntiles, s);
         else if (a.K == 128 && a.Nc == 128)
-            ok = sp ? dispatch_square<128, 128, true>(ep, heads, k, a.ntiles, s)
-                    : dispatch_square<128, 128>(ep, heads, k, a.ntiles, s);
+            ok = sp ? dispatch_square<128, 128, true>(ep, heads, k, ntiles, s)
+                    : dispatch_square<128, 128>(ep, heads, k, ntiles, s);
         else if (a.K == 64 && a.Nc == 128)
-            ok = sp ? dispatch_rect<64, 128, true>(ep, k, a.ntiles, s) : dispatch_rect<64, 128>(ep, k, a.ntiles, s);
+            ok = sp ? dispatch_rect<64, 128, true>(ep, k, ntiles, s) : dispatch_rect<64, 128>(ep, k, ntiles, s);
         else if (a.K == 128 && a.Nc == 64)
-            ok = sp ? dispatch_rect<128, 64, true>(ep, k, a.ntiles, s) : dispatch_rect<128, 64>(ep, k, a.ntiles, s);
+            ok = sp ? dispatch_rect<128, 64, true>(ep, k, ntiles, s) : dispatch_rect<128, 64>(ep, k, ntiles, s);
         else if (a.K == 64 && a.Nc == 192 && ep == EP_SPLIT) {
-            launch_k<64, 192, EP_SPLIT>(k, a.ntiles, s);
+            launch_k<64, 192, EP_SPLIT>(k, ntiles, s);
             ok = true;
         } else if (a.K == 192 && a.Nc == 64 && (ep == 0 || ep == EP_RESID)) {   // three weights stacked in K
-            if (ep) launch_k<192, 64, EP_RESID>(k, a.ntiles, s);
-            else launch_k<192, 64, 0>(k, a.ntiles, s);
+            if (ep) launch_k<192, 64, EP_RESID>(k, ntiles, s);
+            else launch_k<192, 64, 0>(k, ntiles, s);
             ok = true;
         } else if (a.K == 96 && a.Nc == 32 && (ep == 0 || ep == EP_RESID)) {
-            if (ep) launch_k<96, 32, EP_RESID>(k, a.ntiles, s);
-            else launch_k<96, 32, 0>(k, a.ntiles, s);
+            if (ep) launch_k<96, 32, EP_RESID>(k, ntiles, s);
+            else launch_k<96, 32, 0>(k, ntiles, s);
             ok = true;
         }
     }

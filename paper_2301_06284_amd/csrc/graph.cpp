@@ -43,6 +43,14 @@ void build_tiles(const std::vector<int32_t> &type_ptr, int tile_rows, std::vecto
             out.push_back(Tile{t, r0, std::min<int32_t>(tile_rows, type_ptr[t + 1] - r0), 0});
 }
 
+// Rows per tile of a table over `total` rows: a multiple of 64 that gives about
+// `want` tiles, between 64 and `most`.
+int tile_rows_for(int64_t total, int64_t want, int most)
+{
+    const int64_t rows = (total + 64 * want - 1) / (64 * want) * 64;
+    return (int)std::min<int64_t>(most, std::max<int64_t>(64, rows));
+}
+
 // The rows of each relation (sorted by destination) cut where the destination
 // crosses a multiple of `span` node ids, at most tile_rows rows per tile; the
 // tiles of eight consecutive destination ranges are interleaved (range i of a
@@ -247,24 +255,31 @@ rgnn_status build_host_index(int64_t N, int32_t T, int32_t R, int64_t E, const i
                 for (int32_t j = 0; j < n; ++j) x.fused_src[(size_t)fpos + j] = x.in_src[(size_t)b + j];
                 fpos += n;
             }
-            x.tiles_fused.clear();
-            for (int32_t r = 0; r < R; ++r) {
-                const int32_t end = x.rel_vsegptr[r + 1];
-                int32_t r0 = x.rel_vsegptr[r];
-                while (r0 < end) {
-                    int32_t rows = 0, edges = 0;
-                    while (rows < kFusedTileRows && r0 + rows < end) {
-                        const int32_t nb = std::min<int32_t>(16, end - (r0 + rows));
-                        int32_t be = 0;
-                        for (int32_t j = 0; j < nb; ++j) be += x.fused_rows[r0 + rows + j].ne;
-                        if (rows > 0 && edges + be > kFusedTileEdges) break;
-                        rows += nb;
-                        edges += be;
+            auto cut = [&](int max_rows, std::vector<Tile> &out) {
+                out.clear();
+                for (int32_t r = 0; r < R; ++r) {
+                    const int32_t end = x.rel_vsegptr[r + 1];
+                    int32_t r0 = x.rel_vsegptr[r];
+                    while (r0 < end) {
+                        int32_t rows = 0, edges = 0;
+                        while (rows < max_rows && r0 + rows < end) {
+                            const int32_t nb = std::min<int32_t>(16, end - (r0 + rows));
+                            int32_t be = 0;
+                            for (int32_t j = 0; j < nb; ++j) be += x.fused_rows[r0 + rows + j].ne;
+                            if (rows > 0 && edges + be > kFusedTileEdges) break;
+                            rows += nb;
+                            edges += be;
+                        }
+                        out.push_back(Tile{r, r0, rows, x.fused_rows[r0].e0});
+                        r0 += rows;
                     }
-                    x.tiles_fused.push_back(Tile{r, r0, rows, x.fused_rows[r0].e0});
-                    r0 += rows;
                 }
-            }
+            };
+            const int fr = tile_rows_for(g->V, kFusedTilesWanted, kFusedTileRows);
+            const int frw = tile_rows_for(g->V, kFusedTilesWantedWide, kFusedTileRows);
+            cut(fr, x.tiles_fused);
+            if (frw != fr) cut(frw, x.tiles_fused_wide);
+            g->n_tiles_fused_wide = (int64_t)x.tiles_fused_wide.size();
             g->n_tiles_fused = (int64_t)x.tiles_fused.size();
         }
 
@@ -274,6 +289,10 @@ rgnn_status build_host_index(int64_t N, int32_t T, int32_t R, int64_t E, const i
         int32_t slots = 0;
         int64_t v = 0;
         auto deg = [&](int64_t u) { return x.rowptr[u + 1] - x.rowptr[u]; };
+        // edges and destinations (sources) of a bundle: fewer on small graphs,
+        // so that the items still fill the chip
+        const int64_t be = std::min<int64_t>(C, std::max<int64_t>(kMinBundleEdges, (E / kItemsWanted + 7) / 8 * 8));
+        const int64_t bd = be * kMaxDstPerItem / C;
         while (v < N) {
             if (deg(v) > C) {
                 int32_t s = x.dst_vsegptr[v];
@@ -294,7 +313,7 @@ rgnn_status build_host_index(int64_t N, int32_t T, int32_t R, int64_t E, const i
             } else {
                 const int64_t v0 = v;
                 int64_t tot = 0;
-                while (v < N && deg(v) <= C && tot + deg(v) <= C && v - v0 < kMaxDstPerItem) {
+                while (v < N && deg(v) <= C && (v == v0 || tot + deg(v) <= be) && v - v0 < bd) {
                     tot += deg(v);
                     ++v;
                 }
@@ -402,7 +421,7 @@ rgnn_status build_host_index(int64_t N, int32_t T, int32_t R, int64_t E, const i
                 } else {
                     const int64_t u0 = u;
                     int64_t tot = 0;
-                    while (u < N && odeg(u) <= C && tot + odeg(u) <= C && u - u0 < kMaxDstPerItem) {
+                    while (u < N && odeg(u) <= C && (u == u0 || tot + odeg(u) <= be) && u - u0 < bd) {
                         tot += odeg(u);
                         ++u;
                     }
@@ -417,24 +436,29 @@ rgnn_status build_host_index(int64_t N, int32_t T, int32_t R, int64_t E, const i
         }
 
         // ---- GEMM tile tables ----
-        build_tiles(x.uniq_rel_ptr, kGemmTileRows, x.tiles_pairs);
-        build_tiles(x.rel_vsegptr, kGemmTileRows, x.tiles_vsegs);
-        build_tiles_dst_ranges(x.rel_vsegptr, x.vsegdst_byrel, kGemmTileRows, kGemmTileRows, x.tiles_vsegs_dst);
-        g->n_tiles_vsegs_dst = (int64_t)x.tiles_vsegs_dst.size();
-        build_tiles(x.ntype_ptr, kGemmTileRows, x.tiles_nodes);
         std::vector<int32_t> all{0, (int32_t)N};
-        build_tiles(all, kGemmTileRows, x.tiles_all);
-        g->n_tiles_pairs = (int64_t)x.tiles_pairs.size();
-        g->n_tiles_vsegs = (int64_t)x.tiles_vsegs.size();
-        g->n_tiles_nodes = (int64_t)x.tiles_nodes.size();
-        g->n_tiles_all = (int64_t)x.tiles_all.size();
-        build_tiles(x.rel_vsegptr, kOuterRows, x.tiles_outer);
+        const std::vector<int32_t> *type_ptr[kNumGemmRows] = {&x.uniq_rel_ptr, &x.rel_vsegptr, &x.rel_vsegptr,
+                                                              &x.ntype_ptr, &all};
+        for (int t = 0; t < kNumGemmRows; ++t) {
+            const int64_t total = type_ptr[t]->back();
+            const int rows[2] = {tile_rows_for(total, kGemmTilesWanted, kGemmTileRows),
+                                 tile_rows_for(total, kGemmTilesWantedWide, kGemmTileRows)};
+            for (int w = 0; w < (rows[1] != rows[0] ? 2 : 1); ++w) {
+                if (t == kRowsVsegsDst)
+                    build_tiles_dst_ranges(x.rel_vsegptr, x.vsegdst_byrel, rows[w], rows[w], x.gemm_tiles[t][w]);
+                else
+                    build_tiles(*type_ptr[t], rows[w], x.gemm_tiles[t][w]);
+                g->n_gemm_tiles[t][w] = (int64_t)x.gemm_tiles[t][w].size();
+            }
+        }
+        auto outer_rows = [](int64_t rows) { return tile_rows_for(rows, kOuterChunksWanted, kOuterRows); };
+        build_tiles(x.rel_vsegptr, outer_rows(g->V), x.tiles_outer);
         g->n_tiles_outer = (int64_t)x.tiles_outer.size();
-        build_tiles(all, kOuterRows, x.tiles_nodes_outer);   // node chunks (self-loop dW0)
+        build_tiles(all, outer_rows(N), x.tiles_nodes_outer);   // node chunks (self-loop dW0)
         g->n_tiles_nodes_outer = (int64_t)x.tiles_nodes_outer.size();
         x.nodes_chunkptr = {0, (int32_t)g->n_tiles_nodes_outer};
         // chunks over the nodes grouped by type (per-type weight gradients)
-        build_tiles(x.ntype_ptr, kOuterRows, x.tiles_types_outer);
+        build_tiles(x.ntype_ptr, outer_rows(N), x.tiles_types_outer);
         g->n_tiles_types_outer = (int64_t)x.tiles_types_outer.size();
         x.types_chunkptr.assign((size_t)T + 1, 0);
         for (const Tile &t : x.tiles_types_outer) x.types_chunkptr[(size_t)t.type + 1]++;
@@ -443,10 +467,10 @@ rgnn_status build_host_index(int64_t N, int32_t T, int32_t R, int64_t E, const i
         for (const Tile &t : x.tiles_outer) x.rel_chunkptr[(size_t)t.type + 1]++;
         for (int32_t r = 0; r < R; ++r) x.rel_chunkptr[r + 1] += x.rel_chunkptr[r];
         x.rel_pairtileptr.assign((size_t)R + 1, 0);
-        for (const Tile &t : x.tiles_pairs) x.rel_pairtileptr[(size_t)t.type + 1]++;
+        for (const Tile &t : x.gemm_tiles[kRowsPairs][0]) x.rel_pairtileptr[(size_t)t.type + 1]++;
         for (int32_t r = 0; r < R; ++r) x.rel_pairtileptr[r + 1] += x.rel_pairtileptr[r];
         // outer-product chunks over the pairs of each relation
-        build_tiles(x.uniq_rel_ptr, kOuterRows, x.tiles_outer_pairs);
+        build_tiles(x.uniq_rel_ptr, outer_rows(g->U_src), x.tiles_outer_pairs);
         g->n_tiles_outer_pairs = (int64_t)x.tiles_outer_pairs.size();
         x.rel_pairchunkptr.assign((size_t)R + 1, 0);
         for (const Tile &t : x.tiles_outer_pairs) x.rel_pairchunkptr[(size_t)t.type + 1]++;
@@ -507,7 +531,7 @@ rgnn_status build_host_index(int64_t N, int32_t T, int32_t R, int64_t E, const i
             x.src_vpairptr.assign((size_t)N + 1, 0);
             for (int64_t i = 0; i < g->n_vpairs; ++i) x.src_vpairptr[(size_t)x.vpair_src[i] + 1]++;
             for (int64_t u = 0; u < N; ++u) x.src_vpairptr[u + 1] += x.src_vpairptr[u];
-            build_tiles(rel_vpairptr, kPairChunkRows, x.tiles_vpairs);
+            build_tiles(rel_vpairptr, tile_rows_for(g->n_vpairs, kPairChunksWanted, kPairChunkRows), x.tiles_vpairs);
             g->n_tiles_vpairs = (int64_t)x.tiles_vpairs.size();
             x.rel_vpairchunkptr.assign((size_t)R + 1, 0);
             for (const Tile &t : x.tiles_vpairs) x.rel_vpairchunkptr[(size_t)t.type + 1]++;
@@ -551,12 +575,12 @@ rgnn_status upload(rgnn_graph *g, hipStream_t s)
     add32(&d.oitem_slot, x.oitem_slot); add32(&d.osplit_slotptr, x.osplit_slotptr);
     add32(&d.split_order, x.split_order); add32(&d.osplit_order, x.osplit_order);
     parts.push_back(Part{(void **)&d.items, x.items.data(), x.items.size() * sizeof(Item)});
-    parts.push_back(Part{(void **)&d.tiles_pairs, x.tiles_pairs.data(), x.tiles_pairs.size() * sizeof(Tile)});
-    parts.push_back(Part{(void **)&d.tiles_vsegs, x.tiles_vsegs.data(), x.tiles_vsegs.size() * sizeof(Tile)});
-    parts.push_back(Part{(void **)&d.tiles_vsegs_dst, x.tiles_vsegs_dst.data(),
-                         x.tiles_vsegs_dst.size() * sizeof(Tile)});
-    parts.push_back(Part{(void **)&d.tiles_nodes, x.tiles_nodes.data(), x.tiles_nodes.size() * sizeof(Tile)});
-    parts.push_back(Part{(void **)&d.tiles_all, x.tiles_all.data(), x.tiles_all.size() * sizeof(Tile)});
+    for (int t = 0; t < kNumGemmRows; ++t)
+        for (int w = 0; w < 2; ++w)
+            parts.push_back(Part{(void **)&d.gemm_tiles[t][w], x.gemm_tiles[t][w].data(),
+                                 x.gemm_tiles[t][w].size() * sizeof(Tile)});
+    parts.push_back(Part{(void **)&d.tiles_fused_wide, x.tiles_fused_wide.data(),
+                         x.tiles_fused_wide.size() * sizeof(Tile)});
     parts.push_back(Part{(void **)&d.tiles_outer, x.tiles_outer.data(), x.tiles_outer.size() * sizeof(Tile)});
     parts.push_back(Part{(void **)&d.tiles_nodes_outer, x.tiles_nodes_outer.data(),
                          x.tiles_nodes_outer.size() * sizeof(Tile)});
@@ -592,15 +616,40 @@ rgnn_status upload(rgnn_graph *g, hipStream_t s)
                                         : hip_fail(e, "hipMalloc");
     }
     d.bytes = total;
-    size_t off = 0;
-    for (auto &p : parts) {
-        *p.dst = (char *)d.base + off;
-        if (p.bytes) {
-            e = hipMemcpyAsync(*p.dst, p.src, p.bytes, hipMemcpyHostToDevice, s);
-            if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync (graph upload)");
-        }
-        off += (p.bytes + 255) & ~size_t(255);
+    // The small parts lie together at the front of the allocation and go up in
+    // one copy from a packed host buffer: a copy from pageable memory costs about
+    // 10 us however short, and a graph has some 90 parts.
+    constexpr size_t kPackedPart = 64 * 1024;
+    std::vector<char> packed;
+    try {
+        size_t small = 0;
+        for (auto &p : parts)
+            if (p.bytes <= kPackedPart) small += (p.bytes + 255) & ~size_t(255);
+        packed.resize(small);
+    } catch (const std::bad_alloc &) {
+        return fail(RGNN_ENOMEM, "host allocation failed while uploading the graph index");
     }
+    size_t off = 0;
+    for (auto &p : parts)
+        if (p.bytes <= kPackedPart) {
+            *p.dst = (char *)d.base + off;
+            if (p.bytes) std::memcpy(packed.data() + off, p.src, p.bytes);
+            off += (p.bytes + 255) & ~size_t(255);
+        }
+    if (!packed.empty()) {
+        e = hipMemcpyAsync(d.base, packed.data(), packed.size(), hipMemcpyHostToDevice, s);
+        if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync (graph upload)");
+    }
+    for (auto &p : parts)
+        if (p.bytes > kPackedPart) {
+            *p.dst = (char *)d.base + off;
+            e = hipMemcpyAsync(*p.dst, p.src, p.bytes, hipMemcpyHostToDevice, s);
+            if (e != hipSuccess) {
+                (void)hipStreamSynchronize(s);   // the packed buffer may still be in flight
+                return hip_fail(e, "hipMemcpyAsync (graph upload)");
+            }
+            off += (p.bytes + 255) & ~size_t(255);
+        }
     e = hipStreamSynchronize(s);
     if (e != hipSuccess) return hip_fail(e, "hipStreamSynchronize (graph upload)");
     return RGNN_OK;

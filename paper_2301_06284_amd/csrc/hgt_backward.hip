@@ -449,7 +449,7 @@ rgnn_status node_gemm_t(const rgnn_graph *g, int D, const float *X, int64_t ldx,
     ga.split_bf16 = 1;
     ga.X = X; ga.ldx = ldx; ga.gather = g->dev.ntype_perm; ga.scatter = g->dev.ntype_perm;
     ga.W[0] = W; ga.trans_b = 1; ga.K = D; ga.Nc = D;
-    ga.tiles = g->dev.tiles_nodes; ga.ntiles = g->n_tiles_nodes;
+    ga.tiles = g->gemm_tiles(kRowsNodes);
     ga.Y = Y; ga.ldy = D;
     if (residual) { ga.ep.residual = residual; ga.ep.ld_res = D; }
     ga.ep.accumulate = accumulate;
@@ -487,7 +487,7 @@ rgnn_status hgt_backward_d(const rgnn_graph *g, const float *h, const float *Wk,
         ga.split_bf16 = 1;
         ga.X = h; ga.ldx = D; ga.gather = g->dev.ntype_perm; ga.scatter = g->dev.ntype_perm;
         ga.K = D;
-        ga.tiles = g->dev.tiles_nodes; ga.ntiles = g->n_tiles_nodes;
+        ga.tiles = g->gemm_tiles(kRowsNodes);
         if (D == 64) {   // K | V | Q in one GEMM
             ga.W[0] = Wk; ga.W[1] = Wv; ga.W[2] = Wq; ga.nparts = 3;
             ga.Nc = 3 * D;
@@ -518,7 +518,7 @@ rgnn_status hgt_backward_d(const rgnn_graph *g, const float *h, const float *Wk,
         gq.split_bf16 = 1;
         gq.X = fold_q ? h : w.Q; gq.ldx = D; gq.gather = g->dev.vsegdst_byrel; gq.scatter = g->dev.vseg_byrel;
         gq.W[0] = fold_q ? w.Wf : w.Wqp; gq.K = D; gq.Nc = D;
-        gq.tiles = g->dev.tiles_vsegs; gq.ntiles = g->n_tiles_vsegs;
+        gq.tiles = g->gemm_tiles(kRowsVsegs);
         gq.Y = w.QP; gq.ldy = D; gq.ep.diag_blocks = fold_q ? 1 : H;
         if ((st = launch_typed_gemm(gq, s)) != RGNN_OK) return st;
     }
@@ -550,7 +550,7 @@ rgnn_status hgt_backward_d(const rgnn_graph *g, const float *h, const float *Wk,
         gp.split_bf16 = 1;
         gp.X = dagg; gp.ldx = D; gp.gather = g->dev.vsegdst_byrel; gp.scatter = g->dev.vseg_byrel;
         gp.W[0] = w.Wmt; gp.K = D; gp.Nc = D;
-        gp.tiles = g->dev.tiles_vsegs; gp.ntiles = g->n_tiles_vsegs;
+        gp.tiles = g->gemm_tiles(kRowsVsegs);
         gp.Y = w.dP; gp.ldy = D; gp.ep.diag_blocks = H;
         if ((st = launch_typed_gemm(gp, s)) != RGNN_OK) return st;
     }
@@ -590,7 +590,7 @@ rgnn_status hgt_backward_d(const rgnn_graph *g, const float *h, const float *Wk,
             GemmArgs gm;
             gm.split_bf16 = 1;
             gm.X = w.Sal; gm.ldx = D; gm.W[0] = w.Wmt; gm.trans_b = 1; gm.K = D; gm.Nc = D;
-            gm.tiles = g->dev.tiles_vsegs; gm.ntiles = g->n_tiles_vsegs;
+            gm.tiles = g->gemm_tiles(kRowsVsegs);
             gm.Y = w.Tq; gm.ldy = D; gm.scatter = g->dev.vseg_byrel; gm.ep.diag_blocks = H;
             if ((st = launch_typed_gemm(gm, s)) != RGNN_OK) return st;
         }
@@ -608,7 +608,7 @@ rgnn_status hgt_backward_d(const rgnn_graph *g, const float *h, const float *Wk,
         GemmArgs gt;
         gt.split_bf16 = 1;
         gt.X = w.dQP; gt.ldx = D; gt.W[0] = w.Wqp; gt.trans_b = 1; gt.K = D; gt.Nc = D;
-        gt.tiles = g->dev.tiles_vsegs; gt.ntiles = g->n_tiles_vsegs;
+        gt.tiles = g->gemm_tiles(kRowsVsegs);
         gt.Y = w.Tq; gt.ldy = D; gt.scatter = g->dev.vseg_byrel; gt.ep.diag_blocks = H;
         if ((st = launch_typed_gemm(gt, s)) != RGNN_OK) return st;
     }
@@ -682,7 +682,7 @@ rgnn_status hgt_backward_d(const rgnn_graph *g, const float *h, const float *Wk,
         ga.split_bf16 = 1;
         ga.X = w.dKV; ga.ldx = 3 * D; ga.gather = g->dev.ntype_perm; ga.scatter = g->dev.ntype_perm;
         ga.W[0] = w.Wc; ga.trans_b = 1; ga.K = 3 * D; ga.Nc = D;
-        ga.tiles = g->dev.tiles_nodes; ga.ntiles = g->n_tiles_nodes;
+        ga.tiles = g->gemm_tiles(kRowsNodes);
         ga.Y = dh; ga.ldy = D;
         if (res) { ga.ep.residual = res; ga.ep.ld_res = D; }
         if ((st = launch_typed_gemm(ga, s)) != RGNN_OK) return st;

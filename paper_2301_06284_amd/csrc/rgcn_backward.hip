@@ -183,7 +183,7 @@ rgnn_status rgcn_backward_d(const rgnn_graph *g, const float *h, const float *W,
         ga.split_bf16 = 1;
         ga.X = Gp; ga.ldx = D; ga.gather = g->dev.vsegdst_byrel;
         ga.W[0] = W; ga.trans_b = 1; ga.K = D; ga.Nc = D;
-        ga.tiles = g->dev.tiles_vsegs; ga.ntiles = g->n_tiles_vsegs;
+        ga.tiles = g->gemm_tiles(kRowsVsegs);
         ga.Y = w.dS; ga.ldy = D;
         ga.ep.row_scale = g->dev.invcnt_byrel;
         if ((st = launch_typed_gemm(ga, s)) != RGNN_OK) return st;
@@ -193,7 +193,7 @@ rgnn_status rgcn_backward_d(const rgnn_graph *g, const float *h, const float *W,
         GemmArgs ga;
         ga.split_bf16 = 1;
         ga.X = Gp; ga.ldx = D; ga.W[0] = W0; ga.trans_b = 1; ga.K = D; ga.Nc = D;
-        ga.tiles = g->dev.tiles_all; ga.ntiles = g->n_tiles_all;
+        ga.tiles = g->gemm_tiles(kRowsAll);
         ga.Y = dh; ga.ldy = D;
         if ((st = launch_typed_gemm(ga, s)) != RGNN_OK) return st;
     } else if (g->N > 0) {

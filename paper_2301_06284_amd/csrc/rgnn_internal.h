@@ -16,7 +16,7 @@ namespace rgnn {
 constexpr int kChunkEdges = 64;
 // Maximum destinations bundled into one work item.
 constexpr int kMaxDstPerItem = 32;
-// Rows of one typed-GEMM tile (a tile never mixes weight types).
+// Rows of one typed-GEMM tile, at most (a tile never mixes weight types).
 constexpr int kGemmTileRows = 512;
 // fused aggregate-first tiles: at most this many segments of one relation and,
 // beyond the first 16-row block, at most this many in-edges
@@ -31,16 +31,57 @@ constexpr int kWaveSlots = 64;
 // the partials of a destination split over more than kBigRange items are
 // merged in two levels: chunks of kMergeChunk partials, then the chunks
 constexpr int kMergeChunk = 128;
-// rows (segments or nodes) per K-chunk of the backward outer-product GEMMs
+// rows (segments or nodes) per K-chunk of the backward outer-product GEMMs, at most
 constexpr int kOuterRows = 2048;
 // several-head backward, pair pass: out-edges per virtual pair (longer pairs
-// are cut into pieces) and virtual pairs per workgroup chunk
+// are cut into pieces) and virtual pairs per workgroup chunk, at most
 constexpr int kPairPiece = 64;
 constexpr int kPairChunkRows = 1024;
+
+// How finely a graph's work is cut.  The sizes above are the largest pieces,
+// which amortise what a workgroup stages once (the weight tile) or writes once
+// (an outer product's partial); on a small graph they leave most of the 256 CUs
+// idle and each workgroup with a long serial chain (a 64-row step of an outer
+// product takes about 2.9 us, so one 2048-row chunk 92 us at any graph size).
+// A table is therefore cut into about this many pieces (multiples of 64 rows,
+// at least 64; bundles of at least kMinBundleEdges edges) until the pieces reach
+// those sizes.  Measured (us per call, largest pieces -> this rule): HGT
+// training step on 12 000 nodes 824 -> 217, RGCN forward on 2 000 nodes 38.6 ->
+// 17.7, RGCN backward at d = 32 on 131 000 nodes 266 -> 174; half or twice the
+// counts below are within 4 % on these and slower on larger graphs (twice the
+// outer chunks: HGT backward on 950 000 nodes 5.11 -> 5.21 ms; twice the GEMM
+// tiles: HGT forward at d = 128 on 172 000 nodes 1.21 -> 1.24 ms).
+// The 128-wide shapes of the typed GEMM and of the fused kernel stage 104 KB
+// and 68 KB of weights per workgroup and so run one workgroup per CU: they
+// take tables of their own ("wide") with about one tile per CU.  On
+// the tables of the narrow shapes they were slower than with the largest tiles
+// (RGCN forward at d = 128 on 48 000 nodes 103 -> 117 us, HGT on 254 000 nodes
+// 841 -> 870).
+constexpr int64_t kGemmTilesWanted = 768, kGemmTilesWantedWide = 256;
+constexpr int64_t kFusedTilesWanted = 1024, kFusedTilesWantedWide = 256;
+constexpr int64_t kOuterChunksWanted = 1024;
+constexpr int64_t kPairChunksWanted = 2048;
+constexpr int64_t kItemsWanted = 16384;
+constexpr int64_t kMinBundleEdges = 16;
 
 struct Tile {          // one typed-GEMM tile: rows [row0, row0 + rows) of type `type`
     int32_t type, row0, rows, pad;
 };
+
+// The two tables over one set of rows: for the narrow weight shapes, and for
+// the wide ones (the same table when both come out with the same tiles).
+struct TileTable {
+    const Tile *narrow = nullptr;
+    int64_t n_narrow = 0;
+    const Tile *wide = nullptr;
+    int64_t n_wide = 0;
+};
+// weights beyond 64 x 128 leave room for one workgroup per CU
+constexpr bool wide_shape(int K, int Nc) { return K * Nc > 64 * 128; }
+
+// typed-GEMM row sets: compact pairs, virtual segments (by relation; by
+// destination range), nodes grouped by type, all nodes as one type
+enum GemmRows : int { kRowsPairs, kRowsVsegs, kRowsVsegsDst, kRowsNodes, kRowsAll, kNumGemmRows };
 
 struct FusedRow {      // one virtual segment in the fused aggregate-first order
     int32_t vs;           // virtual segment id
@@ -83,19 +124,20 @@ struct HostIndex {
     std::vector<int32_t> osplit_slotptr;   // slots of each of those sources [n_osplit+1]
     std::vector<int32_t> osplit_order;     // indices into osplit, most slots first [n_osplit]
     std::vector<FusedRow> fused_rows;  // vsegs by (rel, edge count desc, id) [V]
-    std::vector<Tile> tiles_fused;     // tiles over fused_rows (pad: first fused_src position)
+    std::vector<Tile> tiles_fused;     // tiles over fused_rows (pad: first fused_src position), narrow
     std::vector<int32_t> fused_src;    // in-edge sources, segment by segment in fused order [E]
     std::vector<int32_t> vseg_fpos;    // position of each vseg in fused_rows [V]
     std::vector<int32_t> vseg_seg;     // (dst, rel) segment of each vseg [V]
-    std::vector<Tile> tiles_pairs, tiles_vsegs, tiles_nodes, tiles_all, tiles_outer;
-    std::vector<Tile> tiles_vsegs_dst;   // tiles_vsegs' rows by destination range, XCD-interleaved
+    std::vector<Tile> gemm_tiles[kNumGemmRows][2];   // narrow, wide (empty: the narrow one)
+    std::vector<Tile> tiles_fused_wide;              // empty: tiles_fused
+    std::vector<Tile> tiles_outer;
     std::vector<int32_t> rel_chunkptr;   // outer-product chunks per relation [R+1]
     std::vector<float> invcnt_byrel;      // 1 / c_{v,r} of each virtual segment, by-relation order
     std::vector<Tile> tiles_nodes_outer;  // outer-product chunks over all nodes
     std::vector<int32_t> nodes_chunkptr;  // {0, number of node chunks}
     std::vector<Tile> tiles_types_outer;  // outer-product chunks over the nodes of each type
     std::vector<int32_t> types_chunkptr;  // chunks per node type [T+1]
-    std::vector<int32_t> rel_pairtileptr;   // compact-pair GEMM tiles per relation [R+1]
+    std::vector<int32_t> rel_pairtileptr;   // narrow compact-pair GEMM tiles per relation [R+1]
     // out-edges (source-major view of the sorted in-edges), for the backward pass
     std::vector<int32_t> out_ptr, out_pos, out_vseg, out_rel, out_pair;
     std::vector<int32_t> out_vs, out_dst;   // per out-edge: its in-edge's vseg id and destination
@@ -143,10 +185,9 @@ struct DeviceIndex {
     int32_t *fused_src = nullptr;
     int32_t *vseg_fpos = nullptr;
     int32_t *vseg_seg = nullptr;
-    Tile *tiles_fused = nullptr;
-    Tile *tiles_vsegs_dst = nullptr;
-    Tile *tiles_pairs = nullptr, *tiles_vsegs = nullptr, *tiles_nodes = nullptr,
-         *tiles_all = nullptr, *tiles_outer = nullptr;
+    Tile *tiles_fused = nullptr, *tiles_fused_wide = nullptr;
+    Tile *gemm_tiles[kNumGemmRows][2] = {};
+    Tile *tiles_outer = nullptr;
     int32_t *out_ptr = nullptr, *out_pos = nullptr, *out_vseg = nullptr, *out_rel = nullptr;
     int32_t *out_pair = nullptr, *out_vs = nullptr, *out_dst = nullptr;
     int32_t *vseg_pos = nullptr;
@@ -168,9 +209,8 @@ struct rgnn_graph {
     int64_t max_in_deg = 0, n_empty = 0;
     int32_t chunk = rgnn::kChunkEdges;
     int32_t device = -1;
-    int64_t n_tiles_pairs = 0, n_tiles_vsegs = 0, n_tiles_nodes = 0, n_tiles_all = 0;
-    int64_t n_tiles_vsegs_dst = 0;
-    int64_t n_tiles_outer = 0, n_tiles_fused = 0, n_tiles_nodes_outer = 0, n_tiles_types_outer = 0;
+    int64_t n_gemm_tiles[rgnn::kNumGemmRows][2] = {};   // narrow, wide (0: the narrow one)
+    int64_t n_tiles_outer = 0, n_tiles_fused = 0, n_tiles_fused_wide = 0, n_tiles_nodes_outer = 0, n_tiles_types_outer = 0;
     int64_t n_big_split = 0, n_big_vdst = 0, n_big_seg = 0, n_big_chunks = 0, n_reduce_dst = 0;
     int64_t n_oitems = 0, n_osplit = 0, n_oslots = 0, n_split_items = 0, n_tiles_outer_pairs = 0;
     int64_t n_vpairs = 0, n_tiles_vpairs = 0;
@@ -178,6 +218,18 @@ struct rgnn_graph {
     bool rel_dst_typed = false;   // every relation's destinations share one node type
     rgnn::HostIndex host;
     rgnn::DeviceIndex dev;
+
+    rgnn::TileTable gemm_tiles(rgnn::GemmRows r) const
+    {
+        const int w = n_gemm_tiles[r][1] ? 1 : 0;
+        return {dev.gemm_tiles[r][0], n_gemm_tiles[r][0], dev.gemm_tiles[r][w], n_gemm_tiles[r][w]};
+    }
+    rgnn::TileTable fused_tiles() const
+    {
+        const bool w = n_tiles_fused_wide != 0;
+        return {dev.tiles_fused, n_tiles_fused, w ? dev.tiles_fused_wide : dev.tiles_fused,
+                w ? n_tiles_fused_wide : n_tiles_fused};
+    }
 };
 
 namespace rgnn {
@@ -240,7 +292,7 @@ struct GemmArgs {
     int nparts = 1;
     int trans_b = 0;                     // B = W[type]^T (W stored [types, Nc, K])
     int K = 0, Nc = 0;
-    const Tile *tiles = nullptr;   int64_t ntiles = 0;
+    TileTable tiles;
     float *Y = nullptr;   int64_t ldy = 0;
     const int32_t *scatter = nullptr;    // row -> Y row (NULL: identity)
     GemmEpilogue ep;

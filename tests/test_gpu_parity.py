@@ -834,3 +834,49 @@ def test_plans_agree():
         a, b = fn(plan=1), fn(plan=2)
         assert row_err(a, b.astype(np.float64)) <= 1e-5
     run.close()
+
+
+def degree_graph(seed, degrees, R, T):
+    """In-degrees and out-degrees both run through `degrees` (in different
+    node orders), repeated over the nodes; relation r has its own edge count."""
+    rng = np.random.default_rng(seed)
+    deg = np.repeat(np.asarray(degrees), 3)
+    N = len(deg)
+    dst = np.repeat(rng.permutation(N), deg).astype(np.int32)
+    src = np.repeat(rng.permutation(N), deg).astype(np.int32)
+    src = src[rng.permutation(len(src))]
+    rel = np.minimum(rng.geometric(0.4, len(src)) - 1, R - 1).astype(np.int32)
+    return dict(N=N, E=len(src), R=R, T=T, src=src, dst=dst, rel=rel,
+                ntype=rng.integers(0, T, N, dtype=np.int32))
+
+
+@pytest.mark.parametrize("d", [32, 64, 128])
+def test_piece_sizes_of_small_graphs(d):
+    """Degrees at the edges of the work items of a small graph (bundles of 16
+    edges and 8 nodes, whole destinations up to 64 edges, pieces beyond) and
+    relations of 1 to several 64-row tiles: forward and backward of every layer."""
+    g = degree_graph(61, [0, 1, 7, 8, 9, 15, 16, 17, 31, 33, 63, 64, 65, 128, 129], R=9, T=3)
+    heads = d // 16
+    t = workloads.tiny_tensors(61, g, d, d, heads=heads)
+    print(f"piece sizes d={d}", flush=True)
+    run = Runner(g, t)
+    assert row_err(run.rgcn(plan=1), oracle.rgcn_forward(g, t["h"], t["W"], t["W0"])) <= TOL
+    assert row_err(run.rgcn(plan=2), oracle.rgcn_forward(g, t["h"], t["W"], t["W0"])) <= TOL
+    for plan, H in ((1, heads), (2, 1)):
+        ref = oracle.rgat_forward(g, t["h"], t["W"], t["w_src"], t["w_dst"], heads=H)
+        assert row_err(run.rgat(heads=H, plan=plan), ref) <= TOL
+    hgt = [t[k] for k in ("h", "Wk", "Wq", "Wv", "Wa", "Watt", "Wmsg", "mu")]
+    assert row_err(run.hgt(heads, 0.25), oracle.hgt_forward(g, *hgt, heads=heads, att_scale=0.25)) <= TOL
+    isolated = (np.bincount(g["src"], minlength=g["N"]) + np.bincount(g["dst"], minlength=g["N"])) == 0
+    for H in {1, heads}:
+        got = run.rgat_backward(heads=H)
+        ref = rgat_backward_ref(g, t, heads=H)
+        assert row_err(got[0], ref[0], structural_zero=isolated, cancel_floor=1e-6) <= TOL
+        for a, b in zip(got[1:], ref[1:]):
+            assert row_err(a.reshape(-1, d), b.reshape(-1, d)) <= TOL
+    for a, b in zip(run.rgcn_backward(), oracle.rgcn_backward(g, t["h"], t["W"], t["W0"], t["grad_out"])):
+        assert row_err(a.reshape(-1, d), b.reshape(-1, d)) <= TOL
+    ref = oracle.hgt_backward(g, *hgt, t["grad_out"], heads=heads, att_scale=0.25)
+    for use_saved in (False, True):
+        check_hgt_grads(run.hgt_backward(heads, 0.25, use_saved=use_saved), ref, heads, d)
+    run.close()
