@@ -505,6 +505,9 @@ bool dispatch_rect(int ep, const GemmK &k, int64_t n, hipStream_t s)
     case 0: launch_k<K, NC, 0, 1, S3>(k, n, s); return true;
     case EP_ACC: launch_k<K, NC, EP_ACC, 1, S3>(k, n, s); return true;
     case EP_ACC | EP_RELU: launch_k<K, NC, EP_ACC | EP_RELU, 1, S3>(k, n, s); return true;
+    case EP_RESID:   // two weights stacked in K
+        if constexpr (K == 128) { launch_k<K, NC, EP_RESID, 1, S3>(k, n, s); return true; }
+        return false;
     default: return false;
     }
 }
@@ -558,6 +561,10 @@ rgnn_status launch_typed_gemm(const GemmArgs &a, hipStream_t s)
         } else if (a.K == 192 && a.Nc == 64 && (ep == 0 || ep == EP_RESID)) {   // three weights stacked in K
             if (ep) launch_k<192, 64, EP_RESID>(k, ntiles, s);
             else launch_k<192, 64, 0>(k, ntiles, s);
+            ok = true;
+        } else if (a.K == 64 && a.Nc == 32 && (ep == 0 || ep == EP_RESID)) {   // two weights stacked in K
+            if (ep) launch_k<64, 32, EP_RESID>(k, ntiles, s);
+            else launch_k<64, 32, 0>(k, ntiles, s);
             ok = true;
         } else if (a.K == 96 && a.Nc == 32 && (ep == 0 || ep == EP_RESID)) {
             if (ep) launch_k<96, 32, EP_RESID>(k, ntiles, s);

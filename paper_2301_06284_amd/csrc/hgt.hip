@@ -66,7 +66,7 @@ struct HK {
     const float *KV, *QP, *Wmsg;
     const float *Q, *Watt, *mu;   // queries formed in the kernel: Q [N, d], Watt, mu, scale
     float scale;
-    int R;
+    int R, ldq;            // ldq: row stride of QP
     float *agg, *partial;
     float *saved;          // [N, H, 2] per destination and head (max, sum), or NULL
 };
@@ -185,7 +185,7 @@ __global__ __launch_bounds__(HS<D>::NTH) void hgt_kernel(HK k)
     // qcur: FQ, the Q row of segment jv's destination; otherwise segment jv's
     // reordered query row, loaded one segment ahead.  qp: segment jv's query.
     float4 qcur = zero4(), qp = zero4();
-    if (ne > 0) qcur = FQ ? ld4(k.Q + (size_t)st.vdst[0] * D + gl * 4) : ld4(k.QP + (size_t)vs0 * D + gl * 4);
+    if (ne > 0) qcur = FQ ? ld4(k.Q + (size_t)st.vdst[0] * D + gl * 4) : ld4(k.QP + (size_t)vs0 * k.ldq + gl * 4);
     if (ne > 0) {
         // Ping-pong batches: batch A is consumed while batch B is in flight.
         // Each edge brings its K|V row; each segment's query row is read once,
@@ -212,7 +212,7 @@ __global__ __launch_bounds__(HS<D>::NTH) void hgt_kernel(HK k)
                                 qcur = ld4(k.Q + (size_t)st.vdst[jv + 1] * D + gl * 4);
                         } else {
                             qp = qcur;
-                            if (jv + 1 < nv) qcur = ld4(k.QP + (size_t)(vs0 + jv + 1) * D + gl * 4);
+                            if (jv + 1 < nv) qcur = ld4(k.QP + (size_t)(vs0 + jv + 1) * k.ldq + gl * 4);
                         }
                     }
                     const float a = gsum<LH>(dot4(Xk[u], qp));
@@ -287,6 +287,7 @@ __global__ void hgt_qp_fold_kernel(const float *Wq, const float *Watt, const flo
     const float *wq = Wq + ((size_t)rel_dsttype[r] * D + j) * D + i * dk;
     const float *wa = Watt + (((size_t)r * heads + i) * dk + (n - i * dk)) * dk;
     float acc = 0.f;
+#pragma unroll 16
     for (int k = 0; k < dk; ++k) acc = fmaf(wq[k], wa[k], acc);
     Wc[idx] = mu[r] * scale * acc;
 }
@@ -336,7 +337,7 @@ rgnn_status launch_hgt_traverse(const HgtArgs &a, hipStream_t s)
     k.Q = a.Q; k.Watt = a.Watt; k.mu = a.mu; k.scale = a.scale;
     if (!a.QP && !(a.Q && a.Watt && a.mu && hgt_fused_query_fits(g->R, a.d, a.heads)))
         return fail(RGNN_EINVAL, "HGT traversal without segment queries needs Q, Watt, mu and LDS room");
-    k.R = g->R; k.agg = a.agg; k.partial = a.partial; k.saved = a.saved;
+    k.R = g->R; k.ldq = a.ldq ? a.ldq : a.d; k.agg = a.agg; k.partial = a.partial; k.saved = a.saved;
     LaunchScope ls("hgt_traverse", s);
     hipError_t e;
     const int64_t n = g->n_items;

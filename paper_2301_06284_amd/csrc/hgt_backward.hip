@@ -19,7 +19,9 @@
 //
 // Kernel sequence: the forward (K|V|Q GEMM, segment queries, traversal with
 // its softmax statistics) is recomputed; dagg and dWa; the block-diagonal
-// W_msg^T and the segment rows dP (typed GEMM); a destination-major pass over
+// W_msg^T and the segment rows dP (typed GEMM), kept beside the segment queries
+// (one 2d-float row QP | dP per segment, so that the source-major pass gathers
+// 512 contiguous bytes per out-edge at d = 64); a destination-major pass over
 // the forward's work items (per edge alpha and dalpha from the K|V row and the
 // segment's QP and dP rows; per segment Salpha, A, B; per destination s); the
 // split destinations' s merged in slot order; dQP; dQ by the typed GEMM and
@@ -28,6 +30,12 @@
 // out-edge and writes dK|dV once per source (float atomics only for pieces of
 // sources with more than kChunkEdges out-edges); dh and the per-type weight
 // gradients by typed GEMMs and outer-product chunks.
+//
+// With typed relations (every relation's destinations of one node type, the
+// case of heterogeneous graphs) the node-type weights Wq and Wa are folded into
+// the per-relation ones instead (see "typed relations" below): no Q, dagg,
+// rebuilt aggregate or dQ, and two outer products over all nodes fewer.
+// 950 000 nodes, 10.5M edges, d = 64, 4 heads: 5.11 -> 4.28 ms.
 #include "rgnn_internal.h"
 #include "wave_ops.h"
 
@@ -78,7 +86,7 @@ struct DKArgs {
     int64_t n_items;
     const Item *items;
     const int32_t *item_slot, *dst_vsegptr, *vseg_ptr, *in_src, *vseg_pos;
-    const float *KV, *QP, *dP, *saved;
+    const float *KV, *QD, *saved;   // QD [V, 2D]: QP | dP of each virtual segment
     float *Sal, *Aac, *Bac, *sfin, *spart;
 };
 
@@ -135,7 +143,8 @@ __global__ __launch_bounds__(256) void hgt_bwd_dst_kernel(DKArgs k)
     if (ne > 0) {
         // ping-pong batches of (K row, V row); each segment's QP and dP rows
         // are read once, while the segment before it runs
-        float4 qn = ld4(k.QP + (size_t)vs0 * D + gl * 4), pn = ld4(k.dP + (size_t)vs0 * D + gl * 4);
+        const float *qd = k.QD + (size_t)vs0 * (2 * D) + gl * 4;
+        float4 qn = ld4(qd), pn = ld4(qd + D);
         float4 qs = zero4(), ps = zero4();
         float4 Ak[kU], Av[kU], Bk[kU], Bv[kU];
         auto load = [&](float4 (&Xk)[kU], float4 (&Xv)[kU], int base) {
@@ -155,9 +164,8 @@ __global__ __launch_bounds__(256) void hgt_bwd_dst_kernel(DKArgs k)
                     if (e == st.vptr[jv]) {   // first edge of segment jv
                         qs = qn; ps = pn;
                         if (jv + 1 < nv) {
-                            const size_t vrow = (size_t)(vs0 + jv + 1) * D + gl * 4;
-                            qn = ld4(k.QP + vrow);
-                            pn = ld4(k.dP + vrow);
+                            qn = ld4(qd + (size_t)(jv + 1) * (2 * D));
+                            pn = ld4(qd + (size_t)(jv + 1) * (2 * D) + D);
                         }
                     }
                     const float a = gsum<LH>(dot4(Xk[u], qs));
@@ -238,7 +246,7 @@ __global__ __launch_bounds__(256) void hgt_bwd_dqp_kernel(int64_t V, int D, int 
 
 // ---------------------------------------------------------------- source-major pass
 struct SStageH {
-    int ev[kE];          // virtual segment (QP / dP row) of each out-edge
+    int ev[kE];          // virtual segment (QP | dP row) of each out-edge
     int et[kE];          // its destination
     int enode[kE];       // item-local source of each out-edge
     int optr[kDst + 1];  // item-local first out-edge of each source
@@ -248,11 +256,12 @@ struct SKArgs {
     int64_t n_items;
     const Item *items;
     const int32_t *out_ptr;
-    const int32_t *out_vs, *out_dst;   // per out-edge: vseg (QP / dP row) and destination, read in order
-    const float *KV, *QP, *dP;
+    const int32_t *out_vs, *out_dst;   // per out-edge: vseg (QP | dP row) and destination, read in order
+    const float *KV, *QD;
     const float4 *rec;   // [N, H] (max, 1 / sum, s, 0) per destination and head
-    float *dKV;          // [N, 3D] dK | dV | dQ rows: dK | dV of split sources zero on entry,
+    float *dKV;          // [N, ldk] dK | dV first in each row: of split sources zero on entry,
                          // of every other source written here
+    int ldk;
 };
 
 template <int D, int H>
@@ -291,7 +300,7 @@ __global__ __launch_bounds__(256) void hgt_bwd_src_kernel(SKArgs k)
     // sources of a bundle without out-edges get zero rows
     for (int jj = 0; jj < nn; ++jj)
         if (st.optr[jj + 1] == st.optr[jj]) {
-            float *p = k.dKV + (size_t)(n0 + jj) * (3 * D) + gl * 4;
+            float *p = k.dKV + (size_t)(n0 + jj) * k.ldk + gl * 4;
             st4(p, zero4());
             st4(p + D, zero4());
         }
@@ -310,12 +319,12 @@ __global__ __launch_bounds__(256) void hgt_bwd_src_kernel(SKArgs k)
         for (int u = 0; u < kU; ++u) {
             const int e = b0 + u < nq ? b0 + u : nq - 1;
             const size_t row = (size_t)(n0 + st.enode[e]) * (2 * D);
-            const size_t vrow = (size_t)st.ev[e] * D;
+            const size_t vrow = (size_t)st.ev[e] * (2 * D);
             const size_t th = (size_t)st.et[e] * H + head;
             Xk[u] = ld4(k.KV + row + gl * 4);
             Xv[u] = ld4(k.KV + row + D + gl * 4);
-            Xq[u] = ld4(k.QP + vrow + gl * 4);
-            Xp[u] = ld4(k.dP + vrow + gl * 4);
+            Xq[u] = ld4(k.QD + vrow + gl * 4);
+            Xp[u] = ld4(k.QD + vrow + D + gl * 4);
             Xm[u] = k.rec[th];
         }
     };
@@ -331,7 +340,7 @@ __global__ __launch_bounds__(256) void hgt_bwd_src_kernel(SKArgs k)
                 dk = axpy4(dk, al * (dal - Xm[u].z), Xq[u]);
                 dv = axpy4(dv, al, Xp[u]);
                 if (e + 1 == st.optr[j + 1]) {   // the source's last out-edge in this item
-                    float *p = k.dKV + (size_t)(n0 + j) * (3 * D) + gl * 4;
+                    float *p = k.dKV + (size_t)(n0 + j) * k.ldk + gl * 4;
                     if (split) {
                         atomic_add4(p, dk);
                         atomic_add4(p + D, dv);
@@ -385,6 +394,132 @@ __global__ __launch_bounds__(256) void hgt_bwd_rel_kernel(const float *OT, const
     }
 }
 
+// ---------------------------------------------------------------- typed relations
+// When all destinations of a relation share one node type t(r), Q = h Wq[t] and
+// dagg = G Wa[t]^T enter the per-segment terms only through products with
+// per-relation weights, so neither is formed:
+//   QP_vs = h_t Wf[r],   Wf[r] = Wq[t(r)] Wqp[r]       (as in the forward)
+//   dP_vs = G_t Wg[r],   Wg[r] = Wa[t(r)]^T Wmsg[r]^T  (without the output linear: Wmsg[r]^T)
+// and every weight gradient on the destination side follows from two outer
+// products per relation, P1[r] = sum_vs dQP_vs^T h_t and P2[r] = sum_vs
+// Salpha_vs^T G_t, by products of d x d matrices:
+//   sum_vs dQP^T Q = P1 Wq[t],      sum_vs Salpha^T dagg = P2 Wa[t]^T
+//   dWq[t] = sum_{r of t} P1[r]^T Wqp[r]^T,   dWa[t] = sum_{r of t} Wmsg[r]^T P2[r]
+// and dh's query part is sum_vs dQP_vs Wf[r]^T.  Against the general path this
+// drops the Q and dagg projections, the rebuilt aggregate (a GEMM over the
+// segments and a reduction), dQ and two outer products over all nodes.
+
+// Wg[r][g][i dk + a] = sum_b Wa[t(r)][i dk + b][g] Wmsg[r, i][a][b].
+__global__ __launch_bounds__(256) void hgt_msg_fold_kernel(const float *Wa, const float *Wmsg,
+                                                           const int32_t *rel_dsttype, int R, int D, int heads,
+                                                           float *Wg)
+{
+    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (idx >= (int64_t)R * D * D) return;
+    const int r = (int)(idx / (D * D)), g = (int)(idx / D % D), n = (int)(idx % D);
+    const int dk = D / heads, i = n / dk;
+    const float *wa = Wa + ((size_t)rel_dsttype[r] * D + i * dk) * D + g;
+    const float *wm = Wmsg + (((size_t)r * heads + i) * dk + (n - i * dk)) * dk;
+    float acc = 0.f;
+#pragma unroll 16
+    for (int b = 0; b < dk; ++b) acc = fmaf(wa[(size_t)b * D], wm[b], acc);
+    Wg[idx] = acc;
+}
+
+// Per relation (blockIdx.x) and 256 entries of its head blocks (blockIdx.y):
+// dWatt = c_r (P1 Wq[t])[blocks], dWmsg = (P2 Wa[t]^T)[blocks] (Wa NULL: P2's
+// blocks), and the block's share of <P1 Wq[t], Watt> for dmu.
+__global__ __launch_bounds__(256) void hgt_bwd_rel_typed_kernel(const float *P1, const float *P2, const float *Wq,
+                                                                const float *Wa, const float *Watt, const float *mu,
+                                                                const int32_t *rel_dsttype, float scale, int D,
+                                                                int heads, float *dWatt, float *dWmsg, float *mupart)
+{
+    __shared__ float red[4];
+    const int r = blockIdx.x, tid = threadIdx.x;
+    const int dk = D / heads, n = heads * dk * dk;
+    const int idx = blockIdx.y * 256 + tid;
+    float part = 0.f;
+    if (idx < n) {
+        const int i = idx / (dk * dk), p = idx / dk % dk, q = idx % dk;
+        const size_t t = (size_t)rel_dsttype[r] * D;
+        const float *p1 = P1 + ((size_t)r * D + i * dk + p) * D;
+        const float *p2 = P2 + ((size_t)r * D + i * dk + p) * D;
+        const float *wq = Wq + t * D + i * dk + q;
+        float ot = 0.f, m2 = 0.f;
+#pragma unroll 16
+        for (int k = 0; k < D; ++k) ot = fmaf(p1[k], wq[(size_t)k * D], ot);
+        if (Wa) {
+            const float *wa = Wa + (t + i * dk + q) * D;
+#pragma unroll 16
+            for (int k = 0; k < D; ++k) m2 = fmaf(p2[k], wa[k], m2);
+        } else {
+            m2 = p2[i * dk + q];
+        }
+        dWatt[(size_t)r * n + idx] = mu[r] * scale * ot;
+        dWmsg[(size_t)r * n + idx] = m2;
+        part = ot * Watt[(size_t)r * n + idx];
+    }
+    part = gsum<32>(part);
+    part += __shfl_xor(part, 32);
+    if ((tid & 63) == 0) red[tid >> 6] = part;
+    __syncthreads();
+    if (tid == 0) mupart[(size_t)r * gridDim.y + blockIdx.y] = red[0] + red[1] + red[2] + red[3];
+}
+
+// Blocks [0, nb): 64 entries of dWq[t], nb = T D^2 / 64; then, with Wmsg, nb
+// blocks for dWa[t]; the last ones dmu.  Sixteen slices of threads take every
+// sixteenth relation, their sums are added in slice order.
+__global__ __launch_bounds__(1024) void hgt_bwd_type_kernel(const float *P1, const float *P2, const float *Watt,
+                                                            const float *Wmsg, const float *mu,
+                                                            const int32_t *rel_dsttype, float scale, int R, int D,
+                                                            int heads, int nb, int want_wa, const float *mupart,
+                                                            int nmu, float *dWq, float *dWa, float *dmu)
+{
+    __shared__ float red[16][64];
+    const int tid = threadIdx.x, li = tid & 63, sl = tid >> 6;
+    int b = (int)blockIdx.x;
+    const int which = b < nb ? 0 : (want_wa && b < 2 * nb ? 1 : 2);
+    if (which == 2) {   // dmu[r] = scale * the ordered sum of its shares
+        const int r = (b - (want_wa ? 2 : 1) * nb) * 1024 + tid;
+        if (r < R) {
+            float s = 0.f;
+            for (int j = 0; j < nmu; ++j) s += mupart[(size_t)r * nmu + j];
+            dmu[r] = scale * s;
+        }
+        return;
+    }
+    if (which == 1) b -= nb;
+    const int dk = D / heads;
+    const int64_t idx = (int64_t)b * 64 + li;   // (t, row, col)
+    const int t = (int)(idx / (D * D)), row = (int)(idx / D % D), col = (int)(idx % D);
+    float acc = 0.f;
+    for (int r = sl; r < R; r += 16) {
+        if (rel_dsttype[r] != t) continue;
+        if (which == 0) {   // dWq[j][i dk + q] += c_r sum_p P1[i dk + p][j] Watt[i][p][q]
+            const int i = col / dk;
+            const float *p1 = P1 + ((size_t)r * D + i * dk) * D + row;
+            const float *wa = Watt + ((size_t)r * heads + i) * dk * dk + (col - i * dk);
+            float x = 0.f;
+#pragma unroll 8
+            for (int p = 0; p < dk; ++p) x = fmaf(p1[(size_t)p * D], wa[(size_t)p * dk], x);
+            acc = fmaf(mu[r] * scale, x, acc);
+        } else {            // dWa[i dk + b][g] += sum_a Wmsg[i][a][b] P2[i dk + a][g]
+            const int i = row / dk;
+            const float *p2 = P2 + ((size_t)r * D + i * dk) * D + col;
+            const float *wm = Wmsg + ((size_t)r * heads + i) * dk * dk + (row - i * dk);
+#pragma unroll 8
+            for (int a = 0; a < dk; ++a) acc = fmaf(p2[(size_t)a * D], wm[(size_t)a * dk], acc);
+        }
+    }
+    red[sl][li] = acc;
+    __syncthreads();
+    if (sl == 0) {
+        float s = red[0][li];
+        for (int j = 1; j < 16; ++j) s += red[j][li];
+        (which == 0 ? dWq : dWa)[idx] = s;
+    }
+}
+
 // zero the first w floats (w a multiple of 4) of the rows (stride ld) listed in rows
 __global__ __launch_bounds__(256) void zero_rows_kernel(const int32_t *rows, int64_t n, int w, int ld, float *p)
 {
@@ -392,15 +527,15 @@ __global__ __launch_bounds__(256) void zero_rows_kernel(const int32_t *rows, int
     if (i < n * q) st4(p + (size_t)rows[i / q] * ld + (i % q) * 4, zero4());
 }
 
-// Wc[t][n][j D + k] = W_j[t][n][k] for (W_0, W_1, W_2) = (Wk, Wv, Wq): the three
-// transposed weights side by side, so that dh = [dK | dV | dQ] Wc^T is one GEMM.
+// Wc[t][n][j D + k] = W_j[t][n][k], j < np, for (W_0, W_1, W_2) = (Wk, Wv, Wq): the
+// transposed weights side by side, so that dh = [dK | dV (| dQ)] Wc^T is one GEMM.
 __global__ __launch_bounds__(256) void hgt_cat_weights_kernel(const float *Wk, const float *Wv, const float *Wq,
-                                                              int T, int D, float *Wc)
+                                                              int np, int T, int D, float *Wc)
 {
     const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= (int64_t)T * D * 3 * D) return;
-    const int64_t row = idx / (3 * D);
-    const int c = (int)(idx % (3 * D)), j = c / D, k = c % D;
+    if (idx >= (int64_t)T * D * np * D) return;
+    const int64_t row = idx / (np * D);
+    const int c = (int)(idx % (np * D)), j = c / D, k = c % D;
     const float *W = j == 0 ? Wk : (j == 1 ? Wv : Wq);
     Wc[idx] = W[row * D + k];
 }
@@ -409,9 +544,14 @@ inline unsigned blocks_for(int64_t n, int per_block) { return (unsigned)((n + pe
 inline size_t pad256(size_t b) { return (b + 255) & ~size_t(255); }
 
 struct HgtBwdWs {
-    float *KV, *Q, *Wqp, *QP, *agg, *partial, *saved, *dagg, *Wmt, *dP, *Sal, *Aac, *Bac, *sfin,
-        *spart, *dQP, *Tq, *dQ, *dKV, *chunks, *OT, *M2, *rec, *Wc, *Wf;
+    float *KV, *Q, *Wqp, *QD, *agg, *partial, *saved, *dagg, *Wmt, *Sal, *Aac, *Bac, *sfin,
+        *spart, *dQP, *Tq, *dKV, *chunks, *OT, *M2, *rec, *Wc, *Wf, *mupart;
 };
+
+// the forward forms its segment queries from Q inside the traversal
+bool forward_queries_in_kernel(const rgnn_graph *g, int D, int H) { return D == 128 && hgt_fused_query_fits(g->R, D, H); }
+// 256-entry blocks of a relation's head blocks
+constexpr int rel_blocks(int D, int H) { return (H * (D / H) * (D / H) + 255) / 256; }
 
 size_t hgt_bwd_layout(const rgnn_graph *g, int D, int H, void *base, HgtBwdWs *w)
 {
@@ -426,17 +566,20 @@ size_t hgt_bwd_layout(const rgnn_graph *g, int D, int H, void *base, HgtBwdWs *w
     const size_t slots = (size_t)g->n_slots;
     const size_t nchunks = (size_t)std::max<int64_t>(std::max(g->n_tiles_outer, g->n_tiles_types_outer), 1);
     HgtBwdWs x{};
-    x.KV = take(N * 2 * D); x.Q = take(N * D); x.Wqp = take(R * D * D); x.QP = take(V * D);
+    const bool typed = g->rel_dst_typed;
+    x.KV = take(N * 2 * D); x.Q = take(typed && !forward_queries_in_kernel(g, D, H) ? 0 : N * D);
+    x.Wqp = take(R * D * D); x.QD = take(V * 2 * D);
     x.agg = take(N * D); x.partial = take(slots * (2 * H + D)); x.saved = take(N * H * 2);
-    x.dagg = take(N * D); x.Wmt = take(R * D * D); x.dP = take(V * D);
+    x.dagg = take(typed ? 0 : N * D); x.Wmt = take(R * D * D);
     x.Sal = take(V * D); x.Aac = take(V * D); x.Bac = take(V * D);
     x.sfin = take(N * H); x.spart = take(slots * H);
-    x.dQP = take(V * D); x.Tq = take(V * D); x.dKV = take(N * 3 * D);
-    x.dQ = x.dKV ? x.dKV + 2 * D : nullptr;   // dK | dV | dQ side by side per node
+    x.dQP = take(V * D); x.Tq = take(V * D);
+    x.dKV = take(N * (typed ? 2 : 3) * D);   // dK | dV (| dQ) side by side per node
     x.Wc = take((size_t)g->T * D * 3 * D);
     x.chunks = take(nchunks * D * D); x.OT = take(R * D * D); x.M2 = take(R * D * D);
     x.rec = take(N * H * 4);
     x.Wf = take(R * D * D);
+    x.mupart = take(R * rel_blocks(D, H));
     if (w) *w = x;
     return off;
 }
@@ -475,20 +618,30 @@ rgnn_status hgt_backward_d(const rgnn_graph *g, const float *h, const float *Wk,
 {
     constexpr int G = D / 4, GPB = 256 / G;
     const bool a_linear = (flags & RGNN_FLAG_A_LINEAR) != 0;
+    const bool typed = g->rel_dst_typed;
     HgtBwdWs w;
     hgt_bwd_layout(g, D, H, ws, &w);
     rgnn_status st;
     hipError_t e;
-    // ---- forward recomputation: K | V | Q, the segment queries and, without the
+    // ---- forward recomputation: K | V (| Q), the segment queries and, without the
     //      forward's statistics, the traversal that yields them and agg
     const float *stats = saved ? saved : w.saved;
+    // the segment queries exactly as the forward forms them (with the query
+    // projection folded into the per-relation weight when the relations
+    // are typed), so that the recomputed scores match its statistics
+    const bool fold_q = typed && !forward_queries_in_kernel(g, D, H);
     {
         GemmArgs ga;
         ga.split_bf16 = 1;
         ga.X = h; ga.ldx = D; ga.gather = g->dev.ntype_perm; ga.scatter = g->dev.ntype_perm;
         ga.K = D;
         ga.tiles = g->gemm_tiles(kRowsNodes);
-        if (D == 64) {   // K | V | Q in one GEMM
+        if (D == 64 && fold_q) {   // K | V in one GEMM
+            ga.W[0] = Wk; ga.W[1] = Wv; ga.nparts = 2;
+            ga.Nc = 2 * D;
+            ga.Y = w.KV; ga.ldy = 2 * D;
+            if ((st = launch_typed_gemm(ga, s)) != RGNN_OK) return st;
+        } else if (D == 64) {   // K | V | Q in one GEMM
             ga.W[0] = Wk; ga.W[1] = Wv; ga.W[2] = Wq; ga.nparts = 3;
             ga.Nc = 3 * D;
             ga.Y = w.KV; ga.ldy = 2 * D;
@@ -499,59 +652,60 @@ rgnn_status hgt_backward_d(const rgnn_graph *g, const float *h, const float *Wk,
             const float *Wp[3] = {Wk, Wv, Wq};
             float *Yp[3] = {w.KV, w.KV + D, w.Q};
             const int64_t ld[3] = {2 * D, 2 * D, D};
-            for (int p = 0; p < 3; ++p) {
+            for (int p = 0; p < (fold_q ? 2 : 3); ++p) {
                 ga.W[0] = Wp[p]; ga.Y = Yp[p]; ga.ldy = ld[p];
                 if ((st = launch_typed_gemm(ga, s)) != RGNN_OK) return st;
             }
         }
     }
-    if ((st = launch_hgt_qp_weights(Watt, mu, att_scale, g->R, D, H, w.Wqp, s)) != RGNN_OK) return st;
+    if (!fold_q && (st = launch_hgt_qp_weights(Watt, mu, att_scale, g->R, D, H, w.Wqp, s)) != RGNN_OK) return st;
+    if (typed &&
+        (st = launch_hgt_qp_fold(Wq, Watt, mu, att_scale, g->dev.rel_dsttype, g->R, D, H, w.Wf, s)) != RGNN_OK)
+        return st;
     {
-        // the segment queries exactly as the forward forms them (with the query
-        // projection folded into the per-relation weight when the relations
-        // are typed), so that the recomputed scores match its statistics
-        const bool fold_q = g->rel_dst_typed && !(D == 128 && hgt_fused_query_fits(g->R, D, H));
-        if (fold_q &&
-            (st = launch_hgt_qp_fold(Wq, Watt, mu, att_scale, g->dev.rel_dsttype, g->R, D, H, w.Wf, s)) != RGNN_OK)
-            return st;
         GemmArgs gq;
         gq.split_bf16 = 1;
         gq.X = fold_q ? h : w.Q; gq.ldx = D; gq.gather = g->dev.vsegdst_byrel; gq.scatter = g->dev.vseg_byrel;
         gq.W[0] = fold_q ? w.Wf : w.Wqp; gq.K = D; gq.Nc = D;
-        gq.tiles = g->gemm_tiles(kRowsVsegs);
-        gq.Y = w.QP; gq.ldy = D; gq.ep.diag_blocks = fold_q ? 1 : H;
+        gq.tiles = g->gemm_tiles(kRowsVsegsDst);
+        gq.Y = w.QD; gq.ldy = 2 * D; gq.ep.diag_blocks = fold_q ? 1 : H;
         if ((st = launch_typed_gemm(gq, s)) != RGNN_OK) return st;
     }
     if (!saved) {
         HgtArgs ha;
-        ha.g = g; ha.KV = w.KV; ha.QP = w.QP; ha.Wmsg = Wmsg;
+        ha.g = g; ha.KV = w.KV; ha.QP = w.QD; ha.ldq = 2 * D; ha.Wmsg = Wmsg;
         ha.heads = H; ha.d = D; ha.agg = w.agg; ha.partial = w.partial; ha.saved = w.saved;
         if ((st = launch_hgt_traverse(ha, s)) != RGNN_OK) return st;
         if ((st = launch_merge_partials(g, D, H, 1, w.partial, w.agg, w.saved, 0, s)) != RGNN_OK) return st;
     }
-    // ---- output linear: dagg = G Wa^T, dWa = sum agg^T G per node type (with
-    //      the forward's statistics agg is rebuilt after the destination pass)
+    // ---- output linear (general path): dagg = G Wa^T, dWa = sum agg^T G per node
+    //      type (with the forward's statistics agg is rebuilt after the destination pass)
     const float *dagg = Gm;
-    if (a_linear) {
+    if (a_linear && !typed) {
         if ((st = node_gemm_t(g, D, Gm, D, Wa, w.dagg, nullptr, 0, s)) != RGNN_OK) return st;
         dagg = w.dagg;
         if (dWa && !saved && (st = type_outer(g, D, w.agg, D, Gm, D, w.chunks, dWa, s)) != RGNN_OK) return st;
     }
-    // ---- dP = dagg_t Wmsg[r]^T per segment (vseg order)
+    // ---- dP = dagg_t Wmsg[r]^T per segment (vseg order); typed: G_t Wg[r], Wg in Wmt
+    const bool fold_a = typed && a_linear;
     if (g->V > 0) {
         {
             const int64_t n = (int64_t)g->R * D * D;
             LaunchScope ls("hgt_msgT_weights", s);
-            hipLaunchKernelGGL(hgt_msgT_weights_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, s, Wmsg, g->R, D, H,
-                               w.Wmt);
+            if (fold_a)
+                hipLaunchKernelGGL(hgt_msg_fold_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, s, Wa, Wmsg,
+                                   g->dev.rel_dsttype, g->R, D, H, w.Wmt);
+            else
+                hipLaunchKernelGGL(hgt_msgT_weights_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, s, Wmsg, g->R, D,
+                                   H, w.Wmt);
         }
         if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "msgT weights launch");
         GemmArgs gp;
         gp.split_bf16 = 1;
         gp.X = dagg; gp.ldx = D; gp.gather = g->dev.vsegdst_byrel; gp.scatter = g->dev.vseg_byrel;
         gp.W[0] = w.Wmt; gp.K = D; gp.Nc = D;
-        gp.tiles = g->gemm_tiles(kRowsVsegs);
-        gp.Y = w.dP; gp.ldy = D; gp.ep.diag_blocks = H;
+        gp.tiles = g->gemm_tiles(kRowsVsegsDst);
+        gp.Y = w.QD + D; gp.ldy = 2 * D; gp.ep.diag_blocks = fold_a ? 1 : H;
         if ((st = launch_typed_gemm(gp, s)) != RGNN_OK) return st;
     }
     // ---- destination-major pass: Salpha, A, B per segment; s per destination
@@ -560,7 +714,7 @@ rgnn_status hgt_backward_d(const rgnn_graph *g, const float *h, const float *Wk,
         k.n_items = g->n_items; k.items = g->dev.items; k.item_slot = g->dev.item_slot;
         k.dst_vsegptr = g->dev.dst_vsegptr; k.vseg_ptr = g->dev.vseg_ptr; k.in_src = g->dev.in_src;
         k.vseg_pos = g->dev.vseg_pos;
-        k.KV = w.KV; k.QP = w.QP; k.dP = w.dP; k.saved = stats;
+        k.KV = w.KV; k.QD = w.QD; k.saved = stats;
         k.Sal = w.Sal; k.Aac = w.Aac; k.Bac = w.Bac; k.sfin = w.sfin; k.spart = w.spart;
         const unsigned nb = blocks_for(g->n_items, GPB);
         {
@@ -585,7 +739,7 @@ rgnn_status hgt_backward_d(const rgnn_graph *g, const float *h, const float *Wk,
     // ---- agg_t = sum over t's segments of Salpha_vs Wmsg[r] (the messages are
     //      linear in V_s, so the alpha-weighted V sums of the destination pass
     //      give the forward's aggregate), then dWa = sum agg^T G per node type
-    if (a_linear && dWa && saved) {
+    if (a_linear && dWa && saved && !typed) {
         if (g->V > 0) {
             GemmArgs gm;
             gm.split_bf16 = 1;
@@ -597,7 +751,8 @@ rgnn_status hgt_backward_d(const rgnn_graph *g, const float *h, const float *Wk,
         if ((st = launch_vseg_reduce(g, w.Tq, nullptr, D, w.agg, 0, 0, s)) != RGNN_OK) return st;
         if ((st = type_outer(g, D, w.agg, D, Gm, D, w.chunks, dWa, s)) != RGNN_OK) return st;
     }
-    // ---- dQP, dQ and the per-relation weight gradients
+    // ---- dQP and its product with the query weights (general: dQ_t's terms dQP
+    //      Wqp[r]^T; typed: dh_t's terms dQP Wf[r]^T), in vseg order
     if (g->V > 0) {
         {
             LaunchScope ls("hgt_bwd_dqp", s);
@@ -607,15 +762,18 @@ rgnn_status hgt_backward_d(const rgnn_graph *g, const float *h, const float *Wk,
         if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "hgt_bwd_dqp launch");
         GemmArgs gt;
         gt.split_bf16 = 1;
-        gt.X = w.dQP; gt.ldx = D; gt.W[0] = w.Wqp; gt.trans_b = 1; gt.K = D; gt.Nc = D;
+        gt.X = w.dQP; gt.ldx = D; gt.W[0] = typed ? w.Wf : w.Wqp; gt.trans_b = 1; gt.K = D; gt.Nc = D;
         gt.tiles = g->gemm_tiles(kRowsVsegs);
-        gt.Y = w.Tq; gt.ldy = D; gt.scatter = g->dev.vseg_byrel; gt.ep.diag_blocks = H;
+        gt.Y = w.Tq; gt.ldy = D; gt.scatter = g->dev.vseg_byrel; gt.ep.diag_blocks = typed ? 1 : H;
         if ((st = launch_typed_gemm(gt, s)) != RGNN_OK) return st;
     }
-    if ((st = launch_vseg_reduce(g, w.Tq, nullptr, D, w.dQ, 0, 0, s, 3 * D)) != RGNN_OK) return st;
+    const int ldk = typed ? 2 * D : 3 * D;
+    if (!typed && (st = launch_vseg_reduce(g, w.Tq, nullptr, D, w.dKV + 2 * D, 0, 0, s, ldk)) != RGNN_OK) return st;
+    // ---- per-relation outer products (typed: with h and G, else with Q and
+    //      dagg) and the weight gradients that follow from them
     if (g->V > 0) {
-        if ((st = launch_outer_chunks(g->dev.tiles_outer, g->n_tiles_outer, g->dev.vsegdst_byrel, 0, w.dQP, D, w.Q,
-                                      D, w.chunks, D, s)) != RGNN_OK)
+        if ((st = launch_outer_chunks(g->dev.tiles_outer, g->n_tiles_outer, g->dev.vsegdst_byrel, 0, w.dQP, D,
+                                      typed ? h : w.Q, D, w.chunks, D, s)) != RGNN_OK)
             return st;
     }
     if ((st = launch_chunk_sum(w.chunks, g->dev.rel_chunkptr, g->R, w.OT, D, s)) != RGNN_OK) return st;
@@ -625,7 +783,23 @@ rgnn_status hgt_backward_d(const rgnn_graph *g, const float *h, const float *Wk,
             return st;
     }
     if ((st = launch_chunk_sum(w.chunks, g->dev.rel_chunkptr, g->R, w.M2, D, s)) != RGNN_OK) return st;
-    if (g->R > 0) {
+    if (g->R > 0 && typed) {
+        const int nrb = rel_blocks(D, H), nb = g->T * D * D / 64, wa = a_linear && dWa ? 1 : 0;
+        {
+            LaunchScope ls("hgt_bwd_rel", s);
+            hipLaunchKernelGGL(hgt_bwd_rel_typed_kernel, dim3((unsigned)g->R, (unsigned)nrb), dim3(256), 0, s, w.OT,
+                               w.M2, Wq, a_linear ? Wa : nullptr, Watt, mu, g->dev.rel_dsttype, att_scale, D, H, dWatt,
+                               dWmsg, w.mupart);
+        }
+        if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "hgt_bwd_rel launch");
+        {
+            LaunchScope ls("hgt_bwd_type", s);
+            hipLaunchKernelGGL(hgt_bwd_type_kernel, dim3((unsigned)((1 + wa) * nb) + blocks_for(g->R, 1024)),
+                               dim3(1024), 0, s, w.OT, w.M2, Watt, Wmsg, mu, g->dev.rel_dsttype, att_scale, g->R, D, H,
+                               nb, wa, w.mupart, nrb, dWq, dWa, dmu);
+        }
+        if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "hgt_bwd_type launch");
+    } else if (g->R > 0) {
         {
             LaunchScope ls("hgt_bwd_rel", s);
             hipLaunchKernelGGL(hgt_bwd_rel_kernel, dim3((unsigned)g->R), dim3(256), 0, s, w.OT, w.M2, Watt, mu,
@@ -647,7 +821,7 @@ rgnn_status hgt_backward_d(const rgnn_graph *g, const float *h, const float *Wk,
         {
             LaunchScope ls("zero", s);
             hipLaunchKernelGGL(zero_rows_kernel, dim3(blocks_for(g->n_osplit * (2 * D / 4), 256)), dim3(256), 0, s,
-                               g->dev.osplit, g->n_osplit, 2 * D, 3 * D, w.dKV);
+                               g->dev.osplit, g->n_osplit, 2 * D, ldk, w.dKV);
         }
         if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "zero launch");
     }
@@ -655,7 +829,7 @@ rgnn_status hgt_backward_d(const rgnn_graph *g, const float *h, const float *Wk,
         SKArgs k{};
         k.n_items = g->n_oitems; k.items = g->dev.oitems; k.out_ptr = g->dev.out_ptr;
         k.out_vs = g->dev.out_vs; k.out_dst = g->dev.out_dst;
-        k.KV = w.KV; k.QP = w.QP; k.dP = w.dP; k.rec = reinterpret_cast<const float4 *>(w.rec); k.dKV = w.dKV;
+        k.KV = w.KV; k.QD = w.QD; k.rec = reinterpret_cast<const float4 *>(w.rec); k.dKV = w.dKV; k.ldk = ldk;
         const unsigned nb = blocks_for(g->n_oitems, GPB);
         {
             LaunchScope ls("hgt_bwd_src", s);
@@ -670,30 +844,32 @@ rgnn_status hgt_backward_d(const rgnn_graph *g, const float *h, const float *Wk,
     }
     // ---- node-level linears: dh and the per-type weight gradients
     const float *res = (flags & RGNN_FLAG_RESIDUAL) ? Gm : nullptr;
-    if constexpr (D <= 64) {   // dh = [dK | dV | dQ] [Wk | Wv | Wq]^T in one GEMM (K = 3D)
+    if constexpr (D <= 64) {   // dh = [dK | dV (| dQ)] [Wk | Wv (| Wq)]^T in one GEMM
+        const int np = typed ? 2 : 3;
         if (g->T > 0) {
-            const int64_t n = (int64_t)g->T * D * 3 * D;
+            const int64_t n = (int64_t)g->T * D * np * D;
             LaunchScope ls("hgt_cat_weights", s);
-            hipLaunchKernelGGL(hgt_cat_weights_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, s, Wk, Wv, Wq, g->T,
+            hipLaunchKernelGGL(hgt_cat_weights_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, s, Wk, Wv, Wq, np, g->T,
                                D, w.Wc);
         }
         if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "cat weights launch");
         GemmArgs ga;
         ga.split_bf16 = 1;
-        ga.X = w.dKV; ga.ldx = 3 * D; ga.gather = g->dev.ntype_perm; ga.scatter = g->dev.ntype_perm;
-        ga.W[0] = w.Wc; ga.trans_b = 1; ga.K = 3 * D; ga.Nc = D;
+        ga.X = w.dKV; ga.ldx = ldk; ga.gather = g->dev.ntype_perm; ga.scatter = g->dev.ntype_perm;
+        ga.W[0] = w.Wc; ga.trans_b = 1; ga.K = np * D; ga.Nc = D;
         ga.tiles = g->gemm_tiles(kRowsNodes);
         ga.Y = dh; ga.ldy = D;
         if (res) { ga.ep.residual = res; ga.ep.ld_res = D; }
         if ((st = launch_typed_gemm(ga, s)) != RGNN_OK) return st;
     } else {   // a 3D-deep weight tile would not fit LDS at D = 128
-        if ((st = node_gemm_t(g, D, w.dKV, 3 * D, Wk, dh, res, 0, s)) != RGNN_OK) return st;
-        if ((st = node_gemm_t(g, D, w.dKV + D, 3 * D, Wv, dh, nullptr, 1, s)) != RGNN_OK) return st;
-        if ((st = node_gemm_t(g, D, w.dQ, 3 * D, Wq, dh, nullptr, 1, s)) != RGNN_OK) return st;
+        if ((st = node_gemm_t(g, D, w.dKV, ldk, Wk, dh, res, 0, s)) != RGNN_OK) return st;
+        if ((st = node_gemm_t(g, D, w.dKV + D, ldk, Wv, dh, nullptr, 1, s)) != RGNN_OK) return st;
+        if (!typed && (st = node_gemm_t(g, D, w.dKV + 2 * D, ldk, Wq, dh, nullptr, 1, s)) != RGNN_OK) return st;
     }
-    if ((st = type_outer(g, D, h, D, w.dKV, 3 * D, w.chunks, dWk, s)) != RGNN_OK) return st;
-    if ((st = type_outer(g, D, h, D, w.dKV + D, 3 * D, w.chunks, dWv, s)) != RGNN_OK) return st;
-    if ((st = type_outer(g, D, h, D, w.dQ, 3 * D, w.chunks, dWq, s)) != RGNN_OK) return st;
+    if (typed && (st = launch_vseg_reduce(g, w.Tq, nullptr, D, dh, 1, 0, s)) != RGNN_OK) return st;
+    if ((st = type_outer(g, D, h, D, w.dKV, ldk, w.chunks, dWk, s)) != RGNN_OK) return st;
+    if ((st = type_outer(g, D, h, D, w.dKV + D, ldk, w.chunks, dWv, s)) != RGNN_OK) return st;
+    if (!typed && (st = type_outer(g, D, h, D, w.dKV + 2 * D, ldk, w.chunks, dWq, s)) != RGNN_OK) return st;
     return RGNN_OK;
 }
 

@@ -429,6 +429,7 @@ struct HgtArgs {
     const float *QP = nullptr;     // [V, d]: mu[r] * scale * Q_t Watt[r]^T per virtual segment,
                                    // or NULL: formed in the kernel from Q, Watt, mu, scale
                                    // (when hgt_fused_query_fits)
+    int ldq = 0;                   // row stride of QP (0: d)
     const float *Q = nullptr, *Watt = nullptr, *mu = nullptr;
     float scale = 1.f;
     const float *Wmsg = nullptr;

@@ -880,3 +880,23 @@ def test_piece_sizes_of_small_graphs(d):
     for use_saved in (False, True):
         check_hgt_grads(run.hgt_backward(heads, 0.25, use_saved=use_saved), ref, heads, d)
     run.close()
+
+
+@pytest.mark.parametrize("flags", [0, 2, 4, 6])
+@pytest.mark.parametrize("d,heads,R,T", [(32, 1, 3, 5), (64, 4, 20, 3), (128, 2, 5, 1), (128, 8, 7, 2)])
+def test_hgt_backward_typed_flags(d, heads, R, T, flags):
+    """The folded node-type weights with each output option: node types without
+    relations (zero dWq and dWa), more relations than the sixteen slices of the
+    per-type sums, one node type, d = 128 with and without in-kernel queries."""
+    g = graph("typed", seed=71, N=400, E=5000, R=R, T=T)
+    t = workloads.tiny_tensors(71, g, d, d, heads=heads)
+    t["mu"] = (1.0 + 0.25 * np.arange(R)).astype(np.float32)
+    print(f"hgt backward typed d={d} heads={heads} R={R} T={T} flags={flags}", flush=True)
+    run = Runner(g, t)
+    got = [run.hgt_backward(heads, 0.3, flags=flags, use_saved=s) for s in (False, True)]
+    run.close()
+    ref = oracle.hgt_backward(g, t["h"], t["Wk"], t["Wq"], t["Wv"], t["Wa"], t["Watt"], t["Wmsg"], t["mu"],
+                              t["grad_out"], heads=heads, att_scale=0.3, residual=bool(flags & 2),
+                              a_linear=bool(flags & 4))
+    for x in got:
+        check_hgt_grads(x, ref, heads, d)
