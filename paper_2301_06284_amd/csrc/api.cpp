@@ -182,7 +182,7 @@ size_t rgat_heads_af_layout(const rgnn_graph *g, int d, int H, void *base, Heads
     return c.off;
 }
 
-struct HgtWs { float *KV, *Q, *QP, *Wqp, *agg, *partial; };
+struct HgtWs { float *KV, *Q, *QP, *Wqp, *agg, *partial, *Sv, *stat; };
 size_t hgt_layout(const rgnn_graph *g, int d, int H, void *base, HgtWs *w)
 {
     Carver c(base);
@@ -192,7 +192,12 @@ size_t hgt_layout(const rgnn_graph *g, int d, int H, void *base, HgtWs *w)
     x.QP = c.take<float>((size_t)g->V * d);
     x.Wqp = c.take<float>((size_t)g->R * d * d);
     x.agg = c.take<float>((size_t)g->N * d);
-    x.partial = c.take<float>((size_t)g->n_slots * (2 * H + d));
+    if (hgt_seg_values(g->R, d, H)) {
+        x.Sv = c.take<float>((size_t)g->V * d);
+        x.stat = c.take<float>((size_t)g->V * H * 2);
+    } else {
+        x.partial = c.take<float>((size_t)g->n_slots * (2 * H + d));
+    }
     if (w) *w = x;
     return c.off;
 }
@@ -638,9 +643,17 @@ extern "C" rgnn_status hgt_forward(const rgnn_graph_t *g, const float *h, const 
         ha.QP = w.QP;
     }
     ha.heads = heads; ha.d = d; ha.agg = w.agg; ha.partial = w.partial; ha.saved = saved;
+    ha.Sv = w.Sv; ha.stat = w.stat; ha.Wt = w.Wqp; ha.T = w.QP;   // both free after the traversal
+    if (hgt_seg_values(g->R, d, heads) && (!(flags & RGNN_FLAG_A_LINEAR) || (heads == 1 && g->rel_dst_typed))) {
+        // the reduction of the segment rows is the layer's output: one head and
+        // typed relations take Wa into the message weights
+        ha.fold_out = (flags & RGNN_FLAG_A_LINEAR) != 0;
+        ha.Wa = Wa;
+        ha.residual = (flags & RGNN_FLAG_RESIDUAL) ? h : nullptr;
+        ha.agg = out;
+        return launch_hgt_traverse(ha, s);
+    }
     if ((st = launch_hgt_traverse(ha, s)) != RGNN_OK) return st;
-    if ((st = launch_merge_partials(g, d, heads, 1, w.partial, w.agg, saved, 0, s)) != RGNN_OK)
-        return st;
     if (flags & RGNN_FLAG_A_LINEAR) {
         GemmArgs gb;
         gb.split_bf16 = 1;

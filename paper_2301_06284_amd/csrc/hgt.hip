@@ -250,6 +250,198 @@ __global__ __launch_bounds__(HS<D>::NTH) void hgt_kernel(HK k)
     while (j < nd) { flush(j); ++j; }
 }
 
+// ---------------------------------------------------------------- wide heads
+// Wmsg is applied by a typed GEMM over the segments instead of in the traversal,
+// whose per-segment product of a dk-vector with a dk x dk matrix from LDS (or,
+// beyond 160 KB of matrices, from L2) takes longer than the segment's gathers when
+// dk is large: on 200 000 nodes and 1.5M edges the traversal took 0.685 ms at d =
+// 64 with one head of 64 against 0.173 ms with four of 16, and 2.41 ms at d = 128
+// with one head (hgt_seg_values has the rule and both sides).  Each segment keeps an online softmax of its
+// own, (max, sum) per head and the value sum relative to that max; the
+// destination's softmax is finished when the transformed rows are summed.
+// No destination boundaries, weights or queries in LDS: 256-thread workgroups at
+// the occupancy that the registers allow.
+struct HSegK {
+    int64_t n_items;
+    const Item *items;
+    const int32_t *vseg_ptr, *vseg_pos, *in_src;
+    const float *KV, *QP;
+    int ldq;
+    float *Sv;      // [V, D] by-relation order: sum exp(a - m) V
+    float *stat;    // [V, H, 2] vseg order: (m, sum exp(a - m))
+};
+
+struct HSegStage {
+    int eidx[kE];          // source node of each edge
+    int vptr[kE + 1];      // item-local edge offset of each virtual segment
+    int vpos[kE];          // by-relation position of each virtual segment
+};
+
+template <int D, int H>
+__global__ __launch_bounds__(256) void hgt_seg_kernel(HSegK k)
+{
+    constexpr int G = D / 4, GPB = 256 / G, LH = G / H;
+    __shared__ HSegStage stage[GPB];
+    const int gl = threadIdx.x % G, gi = threadIdx.x / G;
+    HSegStage &st = stage[gi];
+    const int64_t item = (int64_t)blockIdx.x * GPB + gi;
+    int vs0 = 0, nv = 0, ne = 0;
+    if (item < k.n_items) {
+        const Item x = k.items[item];
+        vs0 = x.vs0; nv = x.vs1 - x.vs0;
+        const int e0 = k.vseg_ptr[x.vs0];
+        ne = k.vseg_ptr[x.vs1] - e0;
+        for (int j = gl; j < nv; j += G) {
+            st.vptr[j] = k.vseg_ptr[vs0 + j] - e0;
+            st.vpos[j] = k.vseg_pos[vs0 + j];
+        }
+        if (gl == 0) st.vptr[nv] = ne;
+        for (int e = gl; e < ne; e += G) st.eidx[e] = k.in_src[e0 + e];
+    }
+    __syncthreads();
+    if (ne == 0) return;
+    const int head = gl / LH;
+    float m = -INFINITY, s = 0.f;
+    float4 vacc = zero4();
+    int jv = 0;
+    // ping-pong batches of K|V rows; each segment's query row one segment ahead
+    const float *qp = k.QP + (size_t)vs0 * k.ldq + gl * 4;
+    float4 qn = ld4(qp), q = zero4();
+    float4 Ak[kU], Av[kU], Bk[kU], Bv[kU];
+    auto load = [&](float4 (&Xk)[kU], float4 (&Xv)[kU], int base) {
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            const int e = base + u < ne ? base + u : ne - 1;
+            const size_t row = (size_t)st.eidx[e] * (2 * D);
+            Xk[u] = ld4(k.KV + row + gl * 4);
+            Xv[u] = ld4(k.KV + row + D + gl * 4);
+        }
+    };
+    auto consume = [&](const float4 (&Xk)[kU], const float4 (&Xv)[kU], int base) {
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            const int e = base + u;
+            if (e < ne) {
+                if (e == st.vptr[jv]) {
+                    q = qn;
+                    if (jv + 1 < nv) qn = ld4(qp + (size_t)(jv + 1) * k.ldq);
+                }
+                const float a = gsum<LH>(dot4(Xk[u], q));
+                const float mn = fmaxf(m, a);
+                const float c1 = __expf(m - mn), c2 = __expf(a - mn);
+                s = s * c1 + c2;
+                vacc = lin4(vacc, c1, Xv[u], c2);
+                m = mn;
+                if (e + 1 == st.vptr[jv + 1]) {
+                    st4(k.Sv + (size_t)st.vpos[jv] * D + gl * 4, vacc);
+                    if (gl % LH == 0)
+                        *reinterpret_cast<float2 *>(k.stat + ((size_t)(vs0 + jv) * H + head) * 2) = make_float2(m, s);
+                    m = -INFINITY; s = 0.f; vacc = zero4();
+                    ++jv;
+                }
+            }
+        }
+    };
+    load(Ak, Av, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    for (int eb = 0; eb < ne; eb += 2 * kU) {
+        load(Bk, Bv, eb + kU);
+        __builtin_amdgcn_sched_barrier(0);
+        consume(Ak, Av, eb);
+        load(Ak, Av, eb + 2 * kU);
+        __builtin_amdgcn_sched_barrier(0);
+        consume(Bk, Bv, eb + kU);
+    }
+}
+
+// out_t = sum_i exp(m_i - M) T_i / Z per head over t's segments i (+ residual), M = max m_i,
+// Z = sum s_i exp(m_i - M), (M, Z) to saved: a group of D / 4 lanes per
+// destination merges its segments' states online, four rows in flight.  Blocks [0,
+// nbig) take the destinations of big_vdst, the groups of a workgroup each a
+// strided share, the groups' states merged in group order.
+template <int D, int H>
+__global__ __launch_bounds__(256) void hgt_seg_reduce_kernel(int64_t N, int64_t nbig, const int32_t *big_vdst,
+                                                             const int32_t *dst_vsegptr, const float *T,
+                                                             const float *stat, const float *residual, float *out,
+                                                             float *saved)
+{
+    constexpr int G = D / 4, NG = 256 / G, LH = G / H, U = 4;
+    __shared__ float4 pacc[NG * G];
+    __shared__ float2 pms[NG * H];
+    const int gl = threadIdx.x % G, gi = threadIdx.x / G, head = gl / LH;
+    const bool big = (int64_t)blockIdx.x < nbig;
+    int64_t v;
+    if (big) v = big_vdst[blockIdx.x];
+    else v = ((int64_t)blockIdx.x - nbig) * NG + gi;
+    if (v >= N) return;   // never in a big workgroup
+    const int b = dst_vsegptr[v], e = dst_vsegptr[v + 1];
+    if (!big && e - b > kBigRange) return;
+    float m = -INFINITY, s = 0.f;
+    float4 acc = zero4();
+    auto merge = [&](float mi, float si, float4 t) {
+        const float mn = fmaxf(m, mi);
+        const float c1 = __expf(m - mn), c2 = __expf(mi - mn);
+        s = s * c1 + si * c2;
+        acc = lin4(acc, c1, t, c2);
+        m = mn;
+    };
+    const int step = big ? NG : 1;
+    for (int i0 = b + (big ? gi : 0); i0 < e; i0 += U * step) {
+        float4 t[U];
+        float2 ms[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = i0 + u * step < e ? i0 + u * step : i0;
+            t[u] = ld4(T + (size_t)i * D + gl * 4);
+            ms[u] = *reinterpret_cast<const float2 *>(stat + ((size_t)i * H + head) * 2);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (i0 + u * step < e) merge(ms[u].x, ms[u].y, t[u]);
+    }
+    if (big) {
+        pacc[gi * G + gl] = acc;
+        if (gl % LH == 0) pms[gi * H + head] = make_float2(m, s);
+        __syncthreads();
+        if (gi != 0) return;
+        for (int j = 1; j < NG; ++j)
+            if (pms[j * H + head].y > 0.f) merge(pms[j * H + head].x, pms[j * H + head].y, pacc[j * G + gl]);
+    }
+    float4 o = scale4(acc, s > 0.f ? 1.f / s : 0.f);
+    if (residual) o = add4(o, ld4(residual + (size_t)v * D + gl * 4));
+    st4(out + (size_t)v * D + gl * 4, o);
+    if (saved && gl % LH == 0)
+        *reinterpret_cast<float2 *>(saved + ((size_t)v * H + head) * 2) = make_float2(s > 0.f ? m : 0.f, s);
+}
+
+// Wf[r][a][g] = sum_b Wmsg[r][a][b] Wa[t(r)][b][g] (one head): the output linear
+// folded into the message weights.
+__global__ __launch_bounds__(256) void hgt_out_fold_kernel(const float *Wmsg, const float *Wa,
+                                                           const int32_t *rel_dsttype, int R, int D, float *Wf)
+{
+    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (idx >= (int64_t)R * D * D) return;
+    const int r = (int)(idx / (D * D)), a = (int)(idx / D % D), g = (int)(idx % D);
+    const float *wm = Wmsg + ((size_t)r * D + a) * D;
+    const float *wa = Wa + (size_t)rel_dsttype[r] * D * D + g;
+    float acc = 0.f;
+#pragma unroll 16
+    for (int b = 0; b < D; ++b) acc = fmaf(wm[b], wa[(size_t)b * D], acc);
+    Wf[idx] = acc;
+}
+
+// Wmt[r][i dk + b][i dk + a] = Wmsg[r][i][a][b]: block-diagonal W_msg^T per head.
+__global__ __launch_bounds__(256) void hgt_msgT_weights_kernel(const float *Wmsg, int R, int D, int heads, float *Wmt)
+{
+    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (idx >= (int64_t)R * D * D) return;
+    const int r = (int)(idx / (D * D)), row = (int)(idx / D % D), col = (int)(idx % D);
+    const int dk = D / heads, i = row / dk;
+    float v = 0.f;
+    if (col / dk == i) v = Wmsg[(((size_t)r * heads + i) * dk + (col - i * dk)) * dk + (row - i * dk)];
+    Wmt[idx] = v;
+}
+
 template <int D, bool FQ>
 size_t stage_bytes() { return (size_t)HS<D>::GPB * sizeof(HStage<FQ>); }
 
@@ -292,6 +484,10 @@ __global__ void hgt_qp_fold_kernel(const float *Wq, const float *Watt, const flo
     Wc[idx] = mu[r] * scale * acc;
 }
 
+// whether the traversal's workgroups hold every relation's Wmsg
+template <int D>
+bool wmsg_in_lds(int R, int heads) { return weight_bytes(D, R, heads) + stage_bytes<D, false>() <= 160 * 1024; }
+
 template <int D, int H>
 hipError_t launch_hgt_shape(const HK &k, int64_t n_items, int R, hipStream_t s)
 {
@@ -308,10 +504,12 @@ hipError_t launch_hgt_shape(const HK &k, int64_t n_items, int R, hipStream_t s)
     if (!k.QP) {   // queries formed in the kernel (the caller checked that both weight sets fit)
         if constexpr (D == 128) HGT_LAUNCH(true, true, (stage_bytes<D, true>() + 2 * wb));
         else e = hipErrorInvalidValue;
-    } else if (wb + stage_bytes<D, false>() <= 160 * 1024) {
+    } else if (wmsg_in_lds<D>(R, H)) {
         HGT_LAUNCH(true, false, (stage_bytes<D, false>() + wb));
-    } else {
+    } else if constexpr (D / H < 32) {   // wide heads with more matrices take the segment GEMM
         HGT_LAUNCH(false, false, (stage_bytes<D, false>()));
+    } else {
+        e = hipErrorInvalidValue;
     }
 #undef HGT_LAUNCH
     return e;
@@ -325,9 +523,110 @@ bool fused_query_fits(int R, int heads)
 
 }  // namespace
 
+// Whether Wmsg leaves the traversal for a GEMM over the segments (see "wide
+// heads"): always for dk >= 64, for dk = 32 at d = 32 and where the matrices do
+// not fit in LDS, never for dk = 16.  ms per forward, traversal -> GEMM, 200 000
+// nodes and 1.5M edges, typed graph of 7 relations / one type and 40 relations:
+//   d = 64,  1 head of 64   0.80 -> 0.32 / 1.46 -> 0.69
+//   d = 128, 1 head of 128  2.72 -> 0.71,  2 heads of 64  1.30 -> 0.75
+//   d = 32,  1 head of 32   0.25 -> 0.16 / 0.47 -> 0.36
+//   d = 64,  2 heads of 32  0.36 -> 0.34 / 0.98 -> 0.73 (12 relations, in LDS: 0.53 -> 0.61)
+//   d = 128, 4 heads of 32  0.65 -> 0.73 / 2.11 -> 1.69
+//   d = 64,  4 heads of 16  0.29 -> 0.35 / 0.70 -> 0.74
+bool hgt_seg_values(int R, int d, int heads)
+{
+    const int dk = d / heads;
+    if (dk >= 64) return true;
+    if (dk < 32) return false;
+    return d == 32 || !(d == 64 ? wmsg_in_lds<64>(R, heads) : wmsg_in_lds<128>(R, heads));
+}
+
+rgnn_status launch_hgt_msgT_weights(const float *Wmsg, int R, int d, int heads, float *Wmt, hipStream_t s)
+{
+    const int64_t n = (int64_t)R * d * d;
+    if (n == 0) return RGNN_OK;
+    LaunchScope ls("hgt_msgT_weights", s);
+    hipLaunchKernelGGL(hgt_msgT_weights_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, Wmsg, R, d, heads,
+                       Wmt);
+    hipError_t e = hipGetLastError();
+    return e == hipSuccess ? RGNN_OK : hip_fail(e, "hgt_msgT_weights launch");
+}
+
+namespace {
+
+// The traversal, message GEMM and reduction of wide heads.  With fold_out (one
+// head, typed relations) the output linear is part of the GEMM's weight.
+rgnn_status launch_hgt_seg(const HgtArgs &a, hipStream_t s)
+{
+    const rgnn_graph *g = a.g;
+    const int d = a.d, H = a.heads;
+    rgnn_status st;
+    hipError_t e;
+    if (a.fold_out && H != 1) return fail(RGNN_EINVAL, "the output linear folds into one head's messages only");
+    if (g->V > 0) {
+        HSegK k{};
+        k.n_items = g->n_items; k.items = g->dev.items; k.vseg_ptr = g->dev.vseg_ptr; k.vseg_pos = g->dev.vseg_pos;
+        k.in_src = g->dev.in_src; k.KV = a.KV; k.QP = a.QP; k.ldq = a.ldq ? a.ldq : d; k.Sv = a.Sv; k.stat = a.stat;
+        const unsigned nb = (unsigned)((g->n_items + 1024 / d - 1) / (1024 / d));
+        bool ok = true;
+        {
+            LaunchScope ls("hgt_traverse", s);
+#define HSEG(D, H) hipLaunchKernelGGL((hgt_seg_kernel<D, H>), dim3(nb), dim3(256), 0, s, k)
+            if (d == 32 && H == 1) HSEG(32, 1);
+            else if (d == 64 && H == 1) HSEG(64, 1);
+            else if (d == 64 && H == 2) HSEG(64, 2);
+            else if (d == 128 && H == 1) HSEG(128, 1);
+            else if (d == 128 && H == 2) HSEG(128, 2);
+            else if (d == 128 && H == 4) HSEG(128, 4);
+            else ok = false;
+#undef HSEG
+        }
+        if (!ok) return fail(RGNN_EUNSUPPORTED, "HGT segment traversal: unsupported (d, heads)");
+        if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "hgt segment traversal launch");
+        GemmArgs gm;
+        gm.split_bf16 = 1;
+        gm.X = a.Sv; gm.ldx = d; gm.W[0] = a.Wt; gm.K = d; gm.Nc = d;
+        gm.tiles = g->gemm_tiles(kRowsVsegs);
+        gm.Y = a.T; gm.ldy = d; gm.scatter = g->dev.vseg_byrel;
+        if (a.fold_out) {
+            const int64_t n = (int64_t)g->R * d * d;
+            {
+                LaunchScope ls("hgt_msgT_weights", s);
+                hipLaunchKernelGGL(hgt_out_fold_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a.Wmsg,
+                                   a.Wa, g->dev.rel_dsttype, g->R, d, a.Wt);
+            }
+            if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "hgt_out_fold launch");
+        } else {
+            if ((st = launch_hgt_msgT_weights(a.Wmsg, g->R, d, H, a.Wt, s)) != RGNN_OK) return st;
+            gm.trans_b = 1; gm.ep.diag_blocks = H;
+        }
+        if ((st = launch_typed_gemm(gm, s)) != RGNN_OK) return st;
+    }
+    if (g->N == 0) return RGNN_OK;
+    const int64_t nbig = g->n_big_vdst;
+    const unsigned nr = (unsigned)(nbig + (g->N + 1024 / d - 1) / (1024 / d));
+    {
+        LaunchScope ls("hgt_seg_reduce", s);
+#define HRED(D, H) hipLaunchKernelGGL((hgt_seg_reduce_kernel<D, H>), dim3(nr), dim3(256), 0, s, g->N, nbig, \
+                                      g->dev.big_vdst, g->dev.dst_vsegptr, a.T, a.stat, a.residual, a.agg, a.saved)
+        if (d == 32) HRED(32, 1);
+        else if (d == 64 && H == 1) HRED(64, 1);
+        else if (d == 64) HRED(64, 2);
+        else if (H == 1) HRED(128, 1);
+        else if (H == 2) HRED(128, 2);
+        else HRED(128, 4);
+#undef HRED
+    }
+    e = hipGetLastError();
+    return e == hipSuccess ? RGNN_OK : hip_fail(e, "hgt_seg_reduce launch");
+}
+
+}  // namespace
+
 rgnn_status launch_hgt_traverse(const HgtArgs &a, hipStream_t s)
 {
     const rgnn_graph *g = a.g;
+    if (hgt_seg_values(g->R, a.d, a.heads)) return launch_hgt_seg(a, s);
     if (g->n_items == 0) return RGNN_OK;
     HK k{};
     k.n_items = g->n_items; k.items = g->dev.items; k.item_slot = g->dev.item_slot;
@@ -342,25 +641,23 @@ rgnn_status launch_hgt_traverse(const HgtArgs &a, hipStream_t s)
     hipError_t e;
     const int64_t n = g->n_items;
     const int R = g->R;
-    if (a.d == 32 && a.heads == 1) e = launch_hgt_shape<32, 1>(k, n, R, s);
-    else if (a.d == 32 && a.heads == 2) e = launch_hgt_shape<32, 2>(k, n, R, s);
-    else if (a.d == 64 && a.heads == 1) e = launch_hgt_shape<64, 1>(k, n, R, s);
+    if (a.d == 32 && a.heads == 2) e = launch_hgt_shape<32, 2>(k, n, R, s);
     else if (a.d == 64 && a.heads == 2) e = launch_hgt_shape<64, 2>(k, n, R, s);
     else if (a.d == 64 && a.heads == 4) e = launch_hgt_shape<64, 4>(k, n, R, s);
-    else if (a.d == 128 && a.heads == 1) e = launch_hgt_shape<128, 1>(k, n, R, s);
-    else if (a.d == 128 && a.heads == 2) e = launch_hgt_shape<128, 2>(k, n, R, s);
     else if (a.d == 128 && a.heads == 4) e = launch_hgt_shape<128, 4>(k, n, R, s);
     else if (a.d == 128 && a.heads == 8) e = launch_hgt_shape<128, 8>(k, n, R, s);
     else return fail(RGNN_EUNSUPPORTED, "HGT traversal: unsupported (d, heads)");
     if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute (HGT LDS)");
     e = hipGetLastError();
-    return e == hipSuccess ? RGNN_OK : hip_fail(e, "hgt traversal launch");
+    if (e != hipSuccess) return hip_fail(e, "hgt traversal launch");
+    return launch_merge_partials(g, a.d, a.heads, 1, a.partial, a.agg, a.saved, 0, s);
 }
 
 bool hgt_fused_query_fits(int R, int d, int heads)
 {
-    // instantiated at d = 128 only, the width where it beats the segment-query GEMM
-    return d == 128 && fused_query_fits<128>(R, heads);
+    // instantiated at d = 128 only, the width where it beats the segment-query
+    // GEMM, and not for wide heads, whose traversal has no weights in LDS
+    return d == 128 && !hgt_seg_values(R, d, heads) && fused_query_fits<128>(R, heads);
 }
 
 rgnn_status launch_hgt_qp_weights(const float *Watt, const float *mu, float scale, int R, int d,

@@ -59,18 +59,6 @@ __device__ __forceinline__ void atomic_add4(float *p, float4 v)
     atomicAdd(p + 0, v.x); atomicAdd(p + 1, v.y); atomicAdd(p + 2, v.z); atomicAdd(p + 3, v.w);
 }
 
-// Wmt[r][i dk + b][i dk + a] = Wmsg[r][i][a][b]: block-diagonal W_msg^T per head.
-__global__ void hgt_msgT_weights_kernel(const float *Wmsg, int R, int D, int heads, float *Wmt)
-{
-    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= (int64_t)R * D * D) return;
-    const int r = (int)(idx / (D * D)), row = (int)(idx / D % D), col = (int)(idx % D);
-    const int dk = D / heads, i = row / dk;
-    float v = 0.f;
-    if (col / dk == i) v = Wmsg[(((size_t)r * heads + i) * dk + (col - i * dk)) * dk + (row - i * dk)];
-    Wmt[idx] = v;
-}
-
 // ---------------------------------------------------------------- destination-major pass
 // dQP = A - s_t B needs s_t, which is known at the destination's last edge only.
 // A destination of this pass with at most kHeldSegs segments (and no more edges
@@ -591,7 +579,7 @@ inline size_t pad256(size_t b) { return (b + 255) & ~size_t(255); }
 
 struct HgtBwdWs {
     float *KV, *Q, *Wqp, *QD, *agg, *partial, *saved, *dagg, *Wmt, *Sal, *Bac, *sfin,
-        *spart, *dQP, *Tq, *dKV, *chunks, *OT, *M2, *rec, *Wc, *Wf, *mupart;
+        *spart, *dQP, *Tq, *dKV, *chunks, *OT, *M2, *rec, *Wc, *Wf, *mupart, *stat;
 };
 
 // the forward forms its segment queries from Q inside the traversal
@@ -626,6 +614,7 @@ size_t hgt_bwd_layout(const rgnn_graph *g, int D, int H, void *base, HgtBwdWs *w
     x.rec = take(N * H * 4);
     x.Wf = take(R * D * D);
     x.mupart = take(R * rel_blocks(D, H));
+    x.stat = take(hgt_seg_values(g->R, D, H) ? V * H * 2 : 0);   // traversal recomputed, wide heads
     if (w) *w = x;
     return off;
 }
@@ -721,8 +710,8 @@ rgnn_status hgt_backward_d(const rgnn_graph *g, const float *h, const float *Wk,
         HgtArgs ha;
         ha.g = g; ha.KV = w.KV; ha.QP = w.QD; ha.ldq = 2 * D; ha.Wmsg = Wmsg;
         ha.heads = H; ha.d = D; ha.agg = w.agg; ha.partial = w.partial; ha.saved = w.saved;
+        ha.Sv = w.Sal; ha.stat = w.stat; ha.Wt = w.Wmt; ha.T = w.Tq;
         if ((st = launch_hgt_traverse(ha, s)) != RGNN_OK) return st;
-        if ((st = launch_merge_partials(g, D, H, 1, w.partial, w.agg, w.saved, 0, s)) != RGNN_OK) return st;
     }
     // ---- output linear (general path): dagg = G Wa^T, dWa = sum agg^T G per node
     //      type (with the forward's statistics agg is rebuilt after the destination pass)
@@ -735,17 +724,17 @@ rgnn_status hgt_backward_d(const rgnn_graph *g, const float *h, const float *Wk,
     // ---- dP = dagg_t Wmsg[r]^T per segment (vseg order); typed: G_t Wg[r], Wg in Wmt
     const bool fold_a = typed && a_linear;
     if (g->V > 0) {
-        {
-            const int64_t n = (int64_t)g->R * D * D;
-            LaunchScope ls("hgt_msgT_weights", s);
-            if (fold_a)
+        if (fold_a) {
+            {
+                const int64_t n = (int64_t)g->R * D * D;
+                LaunchScope ls("hgt_msgT_weights", s);
                 hipLaunchKernelGGL(hgt_msg_fold_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, s, Wa, Wmsg,
                                    g->dev.rel_dsttype, g->R, D, H, w.Wmt);
-            else
-                hipLaunchKernelGGL(hgt_msgT_weights_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, s, Wmsg, g->R, D,
-                                   H, w.Wmt);
+            }
+            if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "msg fold launch");
+        } else if ((st = launch_hgt_msgT_weights(Wmsg, g->R, D, H, w.Wmt, s)) != RGNN_OK) {
+            return st;
         }
-        if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "msgT weights launch");
         GemmArgs gp;
         gp.split_bf16 = 1;
         gp.X = dagg; gp.ldx = D; gp.gather = g->dev.vsegdst_byrel; gp.scatter = g->dev.vseg_byrel;

@@ -437,10 +437,21 @@ struct HgtArgs {
     int d = 64;
     float *agg = nullptr;          // [N, d]
     float *partial = nullptr;      // [slots, 2*heads + d]
-    float *saved = nullptr;        // [N, heads, 2] softmax (max, sum) or NULL (split
-                                   // destinations: written by the partial merge)
+    float *saved = nullptr;        // [N, heads, 2] softmax (max, sum) or NULL
+    // wide heads (hgt_seg_values): value sums [V, d] and statistics [V, heads, 2] per
+    // segment, message weights [R, d, d], transformed rows [V, d] (may be QP's
+    // buffer when ldq is d); optionally the output linear folded into the weights
+    // and a residual added, agg then being the layer's output
+    float *Sv = nullptr, *stat = nullptr, *Wt = nullptr, *T = nullptr;
+    bool fold_out = false;
+    const float *Wa = nullptr, *residual = nullptr;
 };
+// The attention-weighted message sums of every destination (agg) with their
+// softmax statistics.
 rgnn_status launch_hgt_traverse(const HgtArgs &a, hipStream_t s);
+bool hgt_seg_values(int R, int d, int heads);
+// Wmt[r] (d x d) = blockdiag over heads i of Wmsg[r, i]^T.
+rgnn_status launch_hgt_msgT_weights(const float *Wmsg, int R, int d, int heads, float *Wmt, hipStream_t s);
 // Whether the traversal can form the segment queries itself (d = 128, both
 // per-relation weight sets and the work-item stages in one workgroup's LDS).
 bool hgt_fused_query_fits(int R, int d, int heads);

@@ -900,3 +900,28 @@ def test_hgt_backward_typed_flags(d, heads, R, T, flags):
                               a_linear=bool(flags & 4))
     for x in got:
         check_hgt_grads(x, ref, heads, d)
+
+
+@pytest.mark.parametrize("flags", [0, 2, 4, 6])
+@pytest.mark.parametrize("kind", ["hub", "typedhub"])
+@pytest.mark.parametrize("d,heads,R", [(32, 1, 7), (64, 1, 3), (64, 2, 40), (128, 1, 2), (128, 2, 3), (128, 4, 20)])
+def test_hgt_wide_heads(d, heads, R, kind, flags):
+    """Heads whose messages come from a GEMM over the segments: hubs of more
+    than 32 segments, with and without the output linear (folded into one
+    head's weights on typed relations) and the residual, and the statistics."""
+    g = graph(kind, seed=77, N=300, E=12000, R=R, T=2)
+    t = workloads.tiny_tensors(77, g, d, d, heads=heads)
+    print(f"hgt wide heads d={d} heads={heads} R={R} {kind} flags={flags}", flush=True)
+    run = Runner(g, t)
+    got, saved = run.hgt(heads, 0.2, flags=flags, want_saved=True)
+    args = [t[k] for k in ("h", "Wk", "Wq", "Wv", "Wa", "Watt", "Wmsg", "mu")]
+    opt = dict(heads=heads, att_scale=0.2, residual=bool(flags & 2), a_linear=bool(flags & 4))
+    assert row_err(got, oracle.hgt_forward(g, *args, **opt)) <= TOL
+    sv = saved.cpu().numpy()
+    deg = np.bincount(g["dst"], minlength=g["N"])
+    assert (sv[deg == 0] == 0).all() and (sv[deg > 0][..., 1] >= 1 - 1e-5).all()
+    if flags == 6:
+        ref = oracle.hgt_backward(g, *args, t["grad_out"], **opt)
+        for use_saved in (False, True):
+            check_hgt_grads(run.hgt_backward(heads, 0.2, use_saved=use_saved), ref, heads, d)
+    run.close()
