@@ -41,14 +41,15 @@ __device__ __forceinline__ float4 zero4() { return make_float4(0.f, 0.f, 0.f, 0.
 constexpr int kE = kChunkEdges, kDst = kMaxDstPerItem;
 constexpr int kU = 2;                    // gathered K|V rows per batch
 
-// Launch shape at width D: a group of D/4 lanes per work item; 1024-lane
-// workgroups (512 at d = 32, whose 128 item stages would not fit in LDS).
-template <int D>
-struct HS {
-    static constexpr int G = D / 4;
-    static constexpr int NTH = D == 32 ? 512 : 1024;
-    static constexpr int GPB = NTH / G;
-};
+// Threads per workgroup: a group of D/4 lanes per work item, the weights staged
+// once per workgroup.  512 at d <= 64 with heads of 16 (two workgroups per CU: a
+// finer grid than one of 1024 at the same occupancy; 1.9M nodes, d = 64, 4 heads:
+// 1.96 -> 1.91 ms, 85 000 nodes 0.132 -> 0.118, 256 threads 2.12 and 0.116; at d
+// = 32 the 128 item stages of 1024 threads would not fit in LDS), 1024 where the
+// matrices take most of the LDS (d = 64, 2 heads of 32: 2.43 ms against 3.41 with
+// 512 threads).
+template <int D, int H>
+constexpr int hgt_threads() { return D <= 64 && D / H <= 16 ? 512 : 1024; }
 
 template <bool FQ>
 struct HStage {
@@ -110,10 +111,10 @@ __device__ __forceinline__ float4 head_vecmat(float4 x, const float *Mt, int gl)
 // blocks (requires LDSW), with the next segment's Q row already in flight,
 // instead of being read from a materialized [V, d] array.
 template <int D, int H, bool LDSW, bool FQ>
-__global__ __launch_bounds__(HS<D>::NTH) void hgt_kernel(HK k)
+__global__ __launch_bounds__((hgt_threads<D, H>())) void hgt_kernel(HK k)
 {
     static_assert(!FQ || LDSW, "kernel-formed queries keep both weight sets in LDS");
-    constexpr int G = HS<D>::G, GPB = HS<D>::GPB, kBlock = HS<D>::NTH;
+    constexpr int kBlock = hgt_threads<D, H>(), G = D / 4, GPB = kBlock / G;
     constexpr int DK = D / H, LH = DK / 4;
     constexpr int MAT = H * DK * DK;            // floats per relation per matrix
     extern __shared__ float4 smem4[];
@@ -442,8 +443,8 @@ __global__ __launch_bounds__(256) void hgt_msgT_weights_kernel(const float *Wmsg
     Wmt[idx] = v;
 }
 
-template <int D, bool FQ>
-size_t stage_bytes() { return (size_t)HS<D>::GPB * sizeof(HStage<FQ>); }
+template <int D, int H, bool FQ>
+size_t stage_bytes() { return (size_t)(hgt_threads<D, H>() / (D / 4)) * sizeof(HStage<FQ>); }
 
 size_t weight_bytes(int D, int R, int heads)
 {
@@ -485,40 +486,35 @@ __global__ void hgt_qp_fold_kernel(const float *Wq, const float *Watt, const flo
 }
 
 // whether the traversal's workgroups hold every relation's Wmsg
-template <int D>
-bool wmsg_in_lds(int R, int heads) { return weight_bytes(D, R, heads) + stage_bytes<D, false>() <= 160 * 1024; }
+template <int D, int H>
+bool wmsg_in_lds(int R) { return weight_bytes(D, R, H) + stage_bytes<D, H, false>() <= 160 * 1024; }
 
 template <int D, int H>
 hipError_t launch_hgt_shape(const HK &k, int64_t n_items, int R, hipStream_t s)
 {
     const size_t wb = weight_bytes(D, R, H);
-    const unsigned nb = (unsigned)((n_items + HS<D>::GPB - 1) / HS<D>::GPB);
+    constexpr int NTH = hgt_threads<D, H>(), GPB = NTH / (D / 4);
+    const unsigned nb = (unsigned)((n_items + GPB - 1) / GPB);
     hipError_t e;
 #define HGT_LAUNCH(LDSW, FQ, LDS)                                                                          \
     do {                                                                                                   \
         e = hipFuncSetAttribute((const void *)hgt_kernel<D, H, LDSW, FQ>,                                  \
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)(LDS));                   \
         if (e == hipSuccess)                                                                               \
-            hipLaunchKernelGGL((hgt_kernel<D, H, LDSW, FQ>), dim3(nb), dim3(HS<D>::NTH), (LDS), s, k);     \
+            hipLaunchKernelGGL((hgt_kernel<D, H, LDSW, FQ>), dim3(nb), dim3(NTH), (LDS), s, k);            \
     } while (0)
     if (!k.QP) {   // queries formed in the kernel (the caller checked that both weight sets fit)
-        if constexpr (D == 128) HGT_LAUNCH(true, true, (stage_bytes<D, true>() + 2 * wb));
+        if constexpr (D == 128) HGT_LAUNCH(true, true, (stage_bytes<D, H, true>() + 2 * wb));
         else e = hipErrorInvalidValue;
-    } else if (wmsg_in_lds<D>(R, H)) {
-        HGT_LAUNCH(true, false, (stage_bytes<D, false>() + wb));
+    } else if (wmsg_in_lds<D, H>(R)) {
+        HGT_LAUNCH(true, false, (stage_bytes<D, H, false>() + wb));
     } else if constexpr (D / H < 32) {   // wide heads with more matrices take the segment GEMM
-        HGT_LAUNCH(false, false, (stage_bytes<D, false>()));
+        HGT_LAUNCH(false, false, (stage_bytes<D, H, false>()));
     } else {
         e = hipErrorInvalidValue;
     }
 #undef HGT_LAUNCH
     return e;
-}
-
-template <int D>
-bool fused_query_fits(int R, int heads)
-{
-    return stage_bytes<D, true>() + 2 * weight_bytes(D, R, heads) <= 160 * 1024;
 }
 
 }  // namespace
@@ -538,7 +534,7 @@ bool hgt_seg_values(int R, int d, int heads)
     const int dk = d / heads;
     if (dk >= 64) return true;
     if (dk < 32) return false;
-    return d == 32 || !(d == 64 ? wmsg_in_lds<64>(R, heads) : wmsg_in_lds<128>(R, heads));
+    return d == 32 || !(d == 64 ? wmsg_in_lds<64, 2>(R) : wmsg_in_lds<128, 4>(R));
 }
 
 rgnn_status launch_hgt_msgT_weights(const float *Wmsg, int R, int d, int heads, float *Wmt, hipStream_t s)
@@ -657,7 +653,9 @@ bool hgt_fused_query_fits(int R, int d, int heads)
 {
     // instantiated at d = 128 only, the width where it beats the segment-query
     // GEMM, and not for wide heads, whose traversal has no weights in LDS
-    return d == 128 && !hgt_seg_values(R, d, heads) && fused_query_fits<128>(R, heads);
+    if (d != 128 || hgt_seg_values(R, d, heads)) return false;
+    const size_t st = heads == 8 ? stage_bytes<128, 8, true>() : stage_bytes<128, 4, true>();
+    return st + 2 * weight_bytes(d, R, heads) <= 160 * 1024;
 }
 
 rgnn_status launch_hgt_qp_weights(const float *Watt, const float *mu, float scale, int R, int d,

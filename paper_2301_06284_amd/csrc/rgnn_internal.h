@@ -61,7 +61,7 @@ constexpr int64_t kGemmTilesWanted = 768, kGemmTilesWantedWide = 256;
 constexpr int64_t kFusedTilesWanted = 1024, kFusedTilesWantedWide = 256;
 constexpr int64_t kOuterChunksWanted = 1024;
 constexpr int64_t kPairChunksWanted = 2048;
-constexpr int64_t kItemsWanted = 16384;
+constexpr int64_t kItemsWanted = 12288;
 constexpr int64_t kMinBundleEdges = 16;
 
 struct Tile {          // one typed-GEMM tile: rows [row0, row0 + rows) of type `type`

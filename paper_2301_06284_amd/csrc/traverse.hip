@@ -79,12 +79,14 @@ TK make_tk(const TravArgs &a)
     return k;
 }
 
-// Per-group LDS staging area.
-template <int H>
+// Per-group LDS staging area.  EW: with a weight per edge (the RGCN traversal;
+// the RGAT one forms its weights as it goes, and with several heads the array
+// would cost it a workgroup per CU: 2 KB more per item with eight heads).
+template <int H, bool EW>
 struct Stage {
     int eidx[kE];          // per edge: message row (transform-first) or source node
     int evs[kE];           // per edge: item-local virtual segment
-    float ew[kE * H];      // per edge: logit, then weight
+    float ew[EW ? kE : 1]; // per edge: weight
     int dptr[kDst + 1];    // item-local edge offset of each destination's first edge
     int vptr[kE + 1];      // item-local edge offset of each virtual segment's first edge
     int vrel[kE];
@@ -114,7 +116,7 @@ __device__ __forceinline__ ItemHdr item_header(const TK &k, int64_t item)
 // edge indices, all loaded lane-parallel.  MODE 0: vw = destination attention
 // term (H per segment); MODE 1: vw = 1 / c_{v,r}.
 template <int G, int H, int MODE>
-__device__ __forceinline__ void stage_item(const TK &k, const ItemHdr &it, Stage<H> &st,
+__device__ __forceinline__ void stage_item(const TK &k, const ItemHdr &it, Stage<H, MODE == 1> &st,
                                            const int32_t *eidx_src, int gl)
 {
     if (!it.valid) return;
@@ -140,14 +142,12 @@ __device__ __forceinline__ void stage_item(const TK &k, const ItemHdr &it, Stage
 }
 
 // Phase 4 (destination flush): weighted sums of gathered rows, written per
-// destination; pieces of split destinations write (max, sum, acc) partials.
-template <int D, int H, bool SOFTMAX>
-__device__ __forceinline__ void aggregate_item(const TK &k, const ItemHdr &it, const Stage<H> &st,
-                                               const float *rows, int gl, int head, float pm, float ps)
+// destination; pieces of split destinations write partials.
+template <int D>
+__device__ __forceinline__ void aggregate_item(const TK &k, const ItemHdr &it, const Stage<1, true> &st,
+                                               const float *rows, int gl)
 {
-    constexpr int REC = SOFTMAX ? 2 * H + D : 2 + D;
-    constexpr int OFF = SOFTMAX ? 2 * H : 2;
-    constexpr int LH = D / H / 4;
+    constexpr int REC = 2 + D, OFF = 2;
     if (!it.valid) return;
     int j = 0;
     float4 acc = zero4();
@@ -156,9 +156,7 @@ __device__ __forceinline__ void aggregate_item(const TK &k, const ItemHdr &it, c
             const size_t v = (size_t)it.dst0 + jj;
             st4(k.out + v * D + gl * 4, k.relu ? relu4(acc) : acc);
         } else {
-            float *pr = k.partial + (size_t)it.slot * REC;
-            if (SOFTMAX && gl % LH == 0) { pr[head * 2] = pm; pr[head * 2 + 1] = ps; }
-            st4(pr + OFF + gl * 4, acc);
+            st4(k.partial + (size_t)it.slot * REC + OFF + gl * 4, acc);
         }
         acc = zero4();
     };
@@ -181,7 +179,7 @@ __device__ __forceinline__ void aggregate_item(const TK &k, const ItemHdr &it, c
                 const int e = base + u;
                 if (e < it.ne) {
                     while (e >= st.dptr[j + 1]) { flush(j); ++j; }
-                    acc = lin4(acc, 1.f, X[u], st.ew[e * H + head]);
+                    acc = lin4(acc, 1.f, X[u], st.ew[e]);
                 }
             }
         };
@@ -276,10 +274,10 @@ __global__ __launch_bounds__(256) void rgat_tf1_kernel(TK k)
     constexpr int G = D / 4, GPB = 256 / G, LH = G / H;
     constexpr int LDM = ATT ? D + 4 * ((H + 3) / 4) : D;   // row stride of M
     constexpr int kU = 4;   // each entry carries two rows: half the batch of the other traversals
-    __shared__ Stage<H> stage[GPB];
+    __shared__ Stage<H, false> stage[GPB];
     const int gl = threadIdx.x % G, gi = threadIdx.x / G;
     const int head = gl / LH;
-    Stage<H> &st = stage[gi];
+    Stage<H, false> &st = stage[gi];
     const ItemHdr it = item_header(k, (int64_t)blockIdx.x * GPB + gi);
     stage_item<G, H, 0>(k, it, st, k.e2u, gl);
     __syncthreads();
@@ -349,16 +347,16 @@ template <int D>
 __global__ __launch_bounds__(256) void rgcn_tf_kernel(TK k)
 {
     constexpr int G = D / 4, GPB = 256 / G;
-    __shared__ Stage<1> stage[GPB];
+    __shared__ Stage<1, true> stage[GPB];
     const int gl = threadIdx.x % G, gi = threadIdx.x / G;
-    Stage<1> &st = stage[gi];
+    Stage<1, true> &st = stage[gi];
     const ItemHdr it = item_header(k, (int64_t)blockIdx.x * GPB + gi);
     stage_item<G, 1, 1>(k, it, st, k.e2u, gl);
     __syncthreads();
     if (it.valid)
         for (int e = gl; e < it.ne; e += G) st.ew[e] = st.vw[st.evs[e]];
     __syncthreads();
-    aggregate_item<D, 1, false>(k, it, st, k.M, gl, 0, 0.f, 0.f);
+    aggregate_item<D>(k, it, st, k.M, gl);
 }
 
 // The same with the reordered vectors of every relation staged in LDS (when
