@@ -71,6 +71,21 @@ template <int DI, int DO, int MODE, int NWAVE, int KU, int WPE>
 __global__ __launch_bounds__(64 * NWAVE) __attribute__((amdgpu_waves_per_eu(WPE))) void af_fused_kernel(FK k)
 {
     constexpr int NT = 64 * NWAVE;
+    // The 128 x 128 shapes with a transform run two workgroups of eight waves per
+    // CU: 64 KB of weights and the tile's tables in 80 KB of LDS (2048 edges per
+    // tile) and 128 registers, for which they give up the next block's prefetch
+    // and, with the softmax, the second gather buffer.  Sixteen waves with one
+    // batch each hide the gathers better than eight with two and the prefetch
+    // (150 registers, one workgroup per CU): 440 000 nodes, 2.85M edges, softmax
+    // 0.678 -> 0.574 ms, mean 0.676 -> 0.543; twelve waves with both buffers 0.616
+    // and 0.620.  Where nearly every segment has 64 edges only two of a tile's
+    // eight waves have rows and the old shape was the faster one (62 edges per
+    // segment: softmax 0.313 -> 0.346); at 31 edges it no longer was (0.155 ->
+    // 0.144).  The narrower shapes keep both: at 64 x 64 one buffer and six waves per
+    // SIMD gained 2 % on the softmax, lost 5 % on the mean, and the smaller tiles
+    // cost 50 % on long segments.
+    constexpr bool PING = !(wide_shape(DI, DO) && MODE == kModeSoftmax);   // two gather buffers
+    constexpr bool PREF = !(wide_shape(DI, DO) && MODE != kModeSum);       // next block's first batch
     constexpr int KP = DI + 4;       // padded LDS row (conflict-free b128 reads)
     constexpr int KC = DI / 16;      // MFMA k chunks
     constexpr int CH = DI / 32;      // float4 chunks per lane and gathered row
@@ -78,12 +93,13 @@ __global__ __launch_bounds__(64 * NWAVE) __attribute__((amdgpu_waves_per_eu(WPE)
     constexpr int CBP = 2;           // output column blocks per MFMA pass
     constexpr int NW = DI * DO / 4 / NT;
     constexpr int NR = (kFusedTileRows + NT - 1) / NT;   // segment entries per thread
-    constexpr int NS = (kFusedTileEdges + NT - 1) / NT;  // source indices per thread
+    constexpr int TE = wide_shape(DI, DO) ? kFusedTileEdgesWide : kFusedTileEdges;
+    constexpr int NS = (TE + NT - 1) / NT;               // source indices per thread
     static_assert(NW * NT * 4 == DI * DO, "weight tile must split evenly over the workgroup");
     __shared__ float Wt[MODE == kModeSum ? 1 : DO * KP];
     __shared__ float wsl[MODE == kModeSoftmax ? DI : 1];
     __shared__ FusedRow srow[kFusedTileRows];
-    __shared__ int32_t ssrc[kFusedTileEdges];
+    __shared__ int32_t ssrc[TE];
 
     const Tile tile = k.tiles[blockIdx.x];
     const int tid = threadIdx.x;
@@ -173,7 +189,7 @@ __global__ __launch_bounds__(64 * NWAVE) __attribute__((amdgpu_waves_per_eu(WPE)
     };
     // batches of KU edges of both rows (indices from LDS); a row already
     // finished issues no gathers (most segments are one or two edges long)
-    float4 A[KU][2][CH], B[KU][2][CH];
+    float4 A[KU][2][CH], B[PING ? KU : 1][2][CH];
     auto load = [&](const Blk &b, float4 (&X)[KU][2][CH], int t) {
 #pragma unroll
         for (int u = 0; u < KU; ++u)
@@ -248,22 +264,27 @@ __global__ __launch_bounds__(64 * NWAVE) __attribute__((amdgpu_waves_per_eu(WPE)
                 }
             }
         };
-        // ping-pong: batch 0 is already in A; batches past the block's
-        // longest segment are neither loaded nor consumed (wave-uniform tests)
+        // batch 0 is already in A; batches past the block's longest segment are
+        // neither loaded nor consumed (wave-uniform tests)
         __builtin_amdgcn_sched_barrier(0);
-        for (int t = 0; t < nmax; t += 2 * KU) {
+        for (int t = 0; !PING && t < nmax; t += KU) {
+            consume(A, t);
+            if (t + KU < nmax) load(cur, A, t + KU);
+        }
+        for (int t = 0; PING && t < nmax; t += 2 * KU) {
             const bool more_b = t + KU < nmax;
-            if (more_b) load(cur, B, t + KU);
+            if constexpr (PING)
+                if (more_b) load(cur, B, t + KU);
             __builtin_amdgcn_sched_barrier(0);
             consume(A, t);
             if (!more_b) break;
             if (t + 2 * KU < nmax) load(cur, A, t + 2 * KU);
             __builtin_amdgcn_sched_barrier(0);
-            consume(B, t + KU);
+            if constexpr (PING) consume(B, t + KU);
         }
-        // the next block's first batch goes out now
+        // the next block's first batch goes out now (PREF)
         Blk nxt = cur;
-        if (rb + NWAVE < nrb) {
+        if (PREF && rb + NWAVE < nrb) {
             setup(rb + NWAVE, nxt);
             load(nxt, A, 0);
         }
@@ -374,15 +395,20 @@ __global__ __launch_bounds__(64 * NWAVE) __attribute__((amdgpu_waves_per_eu(WPE)
                 }
             }
         }
-        cur = nxt;
+        if (PREF) cur = nxt;
+        else if (rb + NWAVE < nrb) {
+            __builtin_amdgcn_sched_barrier(0);
+            setup(rb + NWAVE, cur);
+            load(cur, A, 0);
+        }
     }
 }
 
 template <int DI, int DO, int MODE>
 void launch_shape(const FK &k, int64_t ntiles, hipStream_t s)
 {
-    // d = 128: the 64 KB weight tile is shared by eight waves; one batch of
-    // rows per wave in flight keeps the gathered rows within the VGPR budget
+    // d = 128: the 64 KB weight tile is shared by eight waves; one edge per row
+    // and batch keeps the gathered rows within the VGPR budget
     constexpr int NWAVE = (DI == 128 || DO == 128) ? 8 : 4;
     constexpr int KU = DI == 128 ? 1 : 2;
     // waves per SIMD the LDS allows; the 128 x 64 mean shape gets the register

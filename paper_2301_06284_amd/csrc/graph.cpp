@@ -255,7 +255,7 @@ rgnn_status build_host_index(int64_t N, int32_t T, int32_t R, int64_t E, const i
                 for (int32_t j = 0; j < n; ++j) x.fused_src[(size_t)fpos + j] = x.in_src[(size_t)b + j];
                 fpos += n;
             }
-            auto cut = [&](int max_rows, std::vector<Tile> &out) {
+            auto cut = [&](int max_rows, int max_edges, std::vector<Tile> &out) {
                 out.clear();
                 for (int32_t r = 0; r < R; ++r) {
                     const int32_t end = x.rel_vsegptr[r + 1];
@@ -266,7 +266,7 @@ rgnn_status build_host_index(int64_t N, int32_t T, int32_t R, int64_t E, const i
                             const int32_t nb = std::min<int32_t>(16, end - (r0 + rows));
                             int32_t be = 0;
                             for (int32_t j = 0; j < nb; ++j) be += x.fused_rows[r0 + rows + j].ne;
-                            if (rows > 0 && edges + be > kFusedTileEdges) break;
+                            if (rows > 0 && edges + be > max_edges) break;
                             rows += nb;
                             edges += be;
                         }
@@ -275,10 +275,8 @@ rgnn_status build_host_index(int64_t N, int32_t T, int32_t R, int64_t E, const i
                     }
                 }
             };
-            const int fr = tile_rows_for(g->V, kFusedTilesWanted, kFusedTileRows);
-            const int frw = tile_rows_for(g->V, kFusedTilesWantedWide, kFusedTileRows);
-            cut(fr, x.tiles_fused);
-            if (frw != fr) cut(frw, x.tiles_fused_wide);
+            cut(tile_rows_for(g->V, kFusedTilesWanted, kFusedTileRows), kFusedTileEdges, x.tiles_fused);
+            cut(tile_rows_for(g->V, kFusedTilesWantedWide, kFusedTileRows), kFusedTileEdgesWide, x.tiles_fused_wide);
             g->n_tiles_fused_wide = (int64_t)x.tiles_fused_wide.size();
             g->n_tiles_fused = (int64_t)x.tiles_fused.size();
         }

@@ -22,6 +22,8 @@ constexpr int kGemmTileRows = 512;
 // beyond the first 16-row block, at most this many in-edges
 constexpr int kFusedTileRows = 256;
 constexpr int kFusedTileEdges = 4096;
+// the 128 x 128 tiles' edges, so that two workgroups fit a CU's LDS (fused.hip)
+constexpr int kFusedTileEdgesWide = 2048;
 // Reductions over more records than this (partials of a split destination,
 // segments of one destination) get a whole workgroup instead of one group.
 constexpr int kBigRange = 32;
@@ -52,9 +54,8 @@ constexpr int kPairChunkRows = 1024;
 // outer chunks: HGT backward on 950 000 nodes 5.11 -> 5.21 ms; twice the GEMM
 // tiles: HGT forward at d = 128 on 172 000 nodes 1.21 -> 1.24 ms).
 // The 128-wide shapes of the typed GEMM and of the fused kernel stage 104 KB
-// and 68 KB of weights per workgroup and so run one workgroup per CU: they
-// take tables of their own ("wide") with about one tile per CU.  On
-// the tables of the narrow shapes they were slower than with the largest tiles
+// and 68 KB of weights per workgroup and run one and two workgroups per CU: they
+// take tables of their own ("wide") with about one tile per CU.  On the tables of the narrow shapes they were slower than with the largest tiles
 // (RGCN forward at d = 128 on 48 000 nodes 103 -> 117 us, HGT on 254 000 nodes
 // 841 -> 870).
 constexpr int64_t kGemmTilesWanted = 768, kGemmTilesWantedWide = 256;
@@ -76,7 +77,7 @@ struct TileTable {
     const Tile *wide = nullptr;
     int64_t n_wide = 0;
 };
-// weights beyond 64 x 128 leave room for one workgroup per CU
+// weights beyond 64 x 128
 constexpr bool wide_shape(int K, int Nc) { return K * Nc > 64 * 128; }
 
 // typed-GEMM row sets: compact pairs, virtual segments (by relation; by
@@ -129,7 +130,7 @@ struct HostIndex {
     std::vector<int32_t> vseg_fpos;    // position of each vseg in fused_rows [V]
     std::vector<int32_t> vseg_seg;     // (dst, rel) segment of each vseg [V]
     std::vector<Tile> gemm_tiles[kNumGemmRows][2];   // narrow, wide (empty: the narrow one)
-    std::vector<Tile> tiles_fused_wide;              // empty: tiles_fused
+    std::vector<Tile> tiles_fused_wide;
     std::vector<Tile> tiles_outer;
     std::vector<int32_t> rel_chunkptr;   // outer-product chunks per relation [R+1]
     std::vector<float> invcnt_byrel;      // 1 / c_{v,r} of each virtual segment, by-relation order
@@ -226,9 +227,7 @@ struct rgnn_graph {
     }
     rgnn::TileTable fused_tiles() const
     {
-        const bool w = n_tiles_fused_wide != 0;
-        return {dev.tiles_fused, n_tiles_fused, w ? dev.tiles_fused_wide : dev.tiles_fused,
-                w ? n_tiles_fused_wide : n_tiles_fused};
+        return {dev.tiles_fused, n_tiles_fused, dev.tiles_fused_wide, n_tiles_fused_wide};
     }
 };
 

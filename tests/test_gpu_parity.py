@@ -925,3 +925,19 @@ def test_hgt_wide_heads(d, heads, R, kind, flags):
         for use_saved in (False, True):
             check_hgt_grads(run.hgt_backward(heads, 0.2, use_saved=use_saved), ref, heads, d)
     run.close()
+
+
+@pytest.mark.parametrize("R,E,N", [(1, 6000, 40), (2, 2048, 32), (3, 9000, 300)])
+@pytest.mark.parametrize("d", [64, 128])
+def test_fused_tile_edges(d, R, E, N):
+    """Aggregate-first tiles cut by their edges: segments of 64 edges (16-row
+    blocks of 1024, 2048 per 128-wide tile) beside short and empty ones."""
+    g = workloads.tiny_graph(83, N=N, E=E, R=R, T=1, kind="hub")
+    t = workloads.tiny_tensors(83, g, d, d)
+    print(f"fused tiles d={d} R={R} E={E}", flush=True)
+    run = Runner(g, t)
+    assert row_err(run.rgcn(plan=2), oracle.rgcn_forward(g, t["h"], t["W"], t["W0"])) <= TOL
+    for scope in (0, 1):
+        ref = oracle.rgat_forward(g, t["h"], t["W"], t["w_src"], t["w_dst"], scope=scope)
+        assert row_err(run.rgat(plan=2, scope=scope), ref) <= TOL
+    run.close()
