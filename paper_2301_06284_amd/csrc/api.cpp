@@ -204,8 +204,10 @@ size_t hgt_layout(const rgnn_graph *g, int d, int H, void *base, HgtWs *w)
 
 size_t segment_gemm_layout(int64_t M, int32_t T, void *base, Tile **tiles, int64_t *ntiles)
 {
-    // upper bound on the tile count: every type may add one partial tile
-    const int64_t n = (M + kGemmTileRows - 1) / kGemmTileRows + T;
+    // upper bound on the tile count: every type may add one partial tile (the
+    // wide shapes' tiles are never smaller)
+    const int rows = tile_rows_for(M, kGemmTilesWanted, kGemmTileRows);
+    const int64_t n = (M + rows - 1) / rows + T;
     Carver c(base);
     Tile *t = c.take<Tile>((size_t)std::max<int64_t>(n, 1));
     if (tiles) *tiles = t;
@@ -773,24 +775,18 @@ extern "C" rgnn_status rgnn_segment_gemm(const float *X, int64_t ldx, const int3
     const size_t need = segment_gemm_layout(M, num_types, nullptr, nullptr, nullptr);
     if (!ws || ws_bytes < need)
         return fail(RGNN_EINVAL, "workspace too small: need " + std::to_string(need) + " bytes");
-    std::vector<int32_t> tp(num_types + 1);
-    for (int t = 0; t <= num_types; ++t) tp[t] = (int32_t)type_ptr[t];
-    std::vector<Tile> tiles;
-    build_tiles(tp, kGemmTileRows, tiles);
+    if (M == 0) return RGNN_OK;
     Tile *dt = nullptr;
     segment_gemm_layout(M, num_types, ws, &dt, nullptr);
     hipStream_t s = (hipStream_t)stream;
-    if (tiles.empty()) return RGNN_OK;
-    // The tile table is enqueued on the stream; the host vector must outlive the
-    // copy, so this call waits for it (a few KB).
-    hipError_t e = hipMemcpyAsync(dt, tiles.data(), tiles.size() * sizeof(Tile),
-                                  hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (e != hipSuccess) return hip_fail(e, "tile table upload");
+    const int64_t want = wide_shape(K, Nc) ? kGemmTilesWantedWide : kGemmTilesWanted;
+    int64_t ntiles = 0;
+    rgnn_status st = launch_segment_tiles(type_ptr, num_types, tile_rows_for(M, want, kGemmTileRows), dt, &ntiles, s);
+    if (st != RGNN_OK) return st;
     GemmArgs ga;
     ga.split_bf16 = 1;
     ga.X = X; ga.ldx = ldx; ga.gather = gather; ga.W[0] = W; ga.K = K; ga.Nc = Nc;
-    ga.tiles = TileTable{dt, (int64_t)tiles.size(), dt, (int64_t)tiles.size()};
+    ga.tiles = TileTable{dt, ntiles, dt, ntiles};
     ga.Y = Y; ga.ldy = ldy; ga.scatter = scatter;
     return launch_typed_gemm(ga, s);
 }

@@ -52,6 +52,8 @@
 // l%16 and four consecutive columns 4*(l/16) .. +3: one float4 store per
 // column block.  The k-slot q = l/16 of step (c, t) is mapped to the actual
 // reduction index kk = 16c + 4q + t, identically for A and B.
+#include <algorithm>
+
 #include "rgnn_internal.h"
 #include "wave_ops.h"
 
@@ -451,6 +453,43 @@ __global__ __launch_bounds__((64 * wg_waves<K, NC, S3>())) void typed_gemm_kerne
     }
 }
 
+// The tile table of the segment GEMM's entry, made on the device: the type
+// offsets ride in the kernel's arguments (kTypesPerLaunch of them per launch, each
+// launch its own part of the table), so the call neither copies from host memory
+// nor waits for the stream (a pageable copy and its wait cost 13 us per call,
+// half of a call on a few thousand rows).  One workgroup: tiles per type, their
+// prefix sum, then every thread writes tiles, finding each one's type by bisection.
+constexpr int kTypesPerLaunch = 512;
+struct TypeOffsets { int32_t row[kTypesPerLaunch + 1]; };   // 2 KB of the 4 KB a launch may pass
+
+__global__ __launch_bounds__(kTypesPerLaunch) void segment_tiles_kernel(TypeOffsets p, int n, int type0, int rows,
+                                                                        Tile *tiles)
+{
+    __shared__ int32_t pre[2][kTypesPerLaunch + 1];   // tiles before each type, ping-pong
+    const int t = threadIdx.x;
+    pre[0][t + 1] = t < n ? (p.row[t + 1] - p.row[t] + rows - 1) / rows : 0;
+    if (t == 0) pre[0][0] = pre[1][0] = 0;
+    __syncthreads();
+    int cur = 0;
+    for (int o = 1; o < kTypesPerLaunch; o <<= 1) {
+        const int i = t + 1;
+        pre[cur ^ 1][i] = pre[cur][i] + (i > o ? pre[cur][i - o] : 0);
+        cur ^= 1;
+        __syncthreads();
+    }
+    const int total = pre[cur][kTypesPerLaunch];
+    for (int i = t; i < total; i += kTypesPerLaunch) {
+        int lo = 0, hi = n;   // the last type with pre[lo] <= i (types without rows share a value)
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (pre[cur][mid] <= i) lo = mid;
+            else hi = mid;
+        }
+        const int r0 = p.row[lo] + (i - pre[cur][lo]) * rows;
+        tiles[i] = Tile{type0 + lo, r0, min(rows, p.row[lo + 1] - r0), 0};
+    }
+}
+
 template <int K, int NC, int EP, int DH = 1, bool S3 = false>
 void launch_k(const GemmK &k, int64_t ntiles, hipStream_t s)
 {
@@ -513,6 +552,30 @@ bool dispatch_rect(int ep, const GemmK &k, int64_t n, hipStream_t s)
 }
 
 }  // namespace
+
+rgnn_status launch_segment_tiles(const int64_t *type_ptr, int ntypes, int rows, Tile *tiles, int64_t *ntiles,
+                                 hipStream_t s)
+{
+    int64_t done = 0;
+    for (int t0 = 0; t0 < ntypes; t0 += kTypesPerLaunch) {
+        const int n = std::min(kTypesPerLaunch, ntypes - t0);
+        TypeOffsets p;
+        int64_t here = 0;
+        for (int t = 0; t <= n; ++t) {
+            p.row[t] = (int32_t)type_ptr[t0 + t];
+            if (t) here += (type_ptr[t0 + t] - type_ptr[t0 + t - 1] + rows - 1) / rows;
+        }
+        for (int t = n + 1; t <= kTypesPerLaunch; ++t) p.row[t] = p.row[n];
+        if (here) {
+            LaunchScope ls("segment_tiles", s);
+            hipLaunchKernelGGL(segment_tiles_kernel, dim3(1), dim3(kTypesPerLaunch), 0, s, p, n, t0, rows, tiles + done);
+        }
+        done += here;
+    }
+    *ntiles = done;
+    hipError_t e = hipGetLastError();
+    return e == hipSuccess ? RGNN_OK : hip_fail(e, "segment_tiles launch");
+}
 
 rgnn_status launch_typed_gemm(const GemmArgs &a, hipStream_t s)
 {

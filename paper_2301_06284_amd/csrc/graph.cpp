@@ -32,8 +32,7 @@ void counting_sort(std::vector<int32_t> &perm, const int32_t *key, int64_t K,
     perm.swap(tmp);
 }
 
-}  // namespace
-
+// tiles of at most tile_rows rows, none across types
 void build_tiles(const std::vector<int32_t> &type_ptr, int tile_rows, std::vector<Tile> &out)
 {
     out.clear();
@@ -43,8 +42,8 @@ void build_tiles(const std::vector<int32_t> &type_ptr, int tile_rows, std::vecto
             out.push_back(Tile{t, r0, std::min<int32_t>(tile_rows, type_ptr[t + 1] - r0), 0});
 }
 
-// Rows per tile of a table over `total` rows: a multiple of 64 that gives about
-// `want` tiles, between 64 and `most`.
+}  // namespace
+
 int tile_rows_for(int64_t total, int64_t want, int most)
 {
     const int64_t rows = (total + 64 * want - 1) / (64 * want) * 64;

@@ -241,7 +241,9 @@ rgnn_status hip_fail(hipError_t e, const char *what);
 rgnn_status build_host_index(int64_t N, int32_t T, int32_t R, int64_t E, const int32_t *src,
                              const int32_t *dst, const int32_t *rel, const int32_t *ntype,
                              int32_t flags, rgnn_graph *g);
-void build_tiles(const std::vector<int32_t> &type_ptr, int tile_rows, std::vector<Tile> &out);
+// Rows per tile of a table over `total` rows: a multiple of 64 that gives about
+// `want` tiles, between 64 and `most`.
+int tile_rows_for(int64_t total, int64_t want, int most);
 rgnn_status launch_add(float *out, const float *a, const float *b, int64_t n, hipStream_t s);
 // out [rows, d] = in with the columns outside [c0, c1) set to 0
 rgnn_status launch_mask_cols(const float *in, float *out, int64_t rows, int d, int c0, int c1, hipStream_t s);
@@ -303,6 +305,10 @@ struct GemmArgs {
     int split_bf16 = 0;
 };
 rgnn_status launch_typed_gemm(const GemmArgs &a, hipStream_t s);
+// Writes the tiles (at most `rows` rows, in type order) of the rows [type_ptr[t],
+// type_ptr[t + 1]) of every type; type_ptr is host memory, read during the call.
+rgnn_status launch_segment_tiles(const int64_t *type_ptr, int ntypes, int rows, Tile *tiles, int64_t *ntiles,
+                                 hipStream_t s);
 
 // Reordered attention vectors: out1[r, k, :] = W_r[:, k-cols] v1[r, k-cols]
 // and the same for v2 into out2 when v2 is not NULL (one launch).

@@ -941,3 +941,46 @@ def test_fused_tile_edges(d, R, E, N):
         ref = oracle.rgat_forward(g, t["h"], t["W"], t["w_src"], t["w_dst"], scope=scope)
         assert row_err(run.rgat(plan=2, scope=scope), ref) <= TOL
     run.close()
+
+
+@pytest.mark.parametrize("T", [1, 511, 512, 513, 1030])
+@pytest.mark.parametrize("K,Nc", [(32, 32), (64, 128), (128, 128)])
+def test_segment_gemm_many_types(K, Nc, T):
+    """The device-made tile table: type counts around a launch's 512, types of
+    0, 1, 63..65 and several hundred rows; eagerly and captured in a graph that is
+    replayed with new inputs between eager calls."""
+    import torch
+    from paper_2301_06284_amd import rgnn
+    rng = np.random.default_rng(T + K)
+    counts = rng.choice([0, 0, 1, 2, 63, 64, 65, 130, 700], T, p=[.3, .2, .2, .1, .05, .05, .05, .03, .02])
+    counts[-1] = 66
+    type_ptr = np.concatenate([[0], np.cumsum(counts)]).astype(np.int64)
+    M = int(type_ptr[-1])
+    print(f"segment_gemm types T={T} M={M} {K}x{Nc}", flush=True)
+    dev = torch.device("cuda:0")
+    W = torch.from_numpy(rng.standard_normal((T, K, Nc)).astype(np.float32)).to(dev)
+    X, Y = torch.empty(M, K, device=dev), torch.empty(M, Nc, device=dev)
+    ws = torch.empty(rgnn.segment_gemm_workspace_size(M, T), dtype=torch.uint8, device=dev)
+    seg = np.repeat(np.arange(T), counts)
+
+    def check(call):
+        x = rng.standard_normal((M, K)).astype(np.float32)
+        X.copy_(torch.from_numpy(x))
+        Y.fill_(float("nan"))
+        call()
+        torch.cuda.synchronize()
+        got = Y.cpu().numpy()
+        for t in rng.permutation(np.flatnonzero(counts))[:40]:
+            ref = x[seg == t].astype(np.float64) @ W[t].double().cpu().numpy()
+            assert row_err(got[seg == t], ref) <= TOL
+        assert np.isfinite(got).all()
+
+    def call():
+        rgnn.segment_gemm(X, None, type_ptr, W, Y, None, ws, K, Nc)
+    check(call)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        call()
+    for _ in range(3):
+        check(g.replay)
+        check(call)
