@@ -594,8 +594,10 @@ __global__ __launch_bounds__(256) void outer_gemm_kernel(const Tile *chunks, con
                                                          const float *Sa, int lda,
                                                          const float *Gm, int ldb, const float *h,
                                                          const float *ysum, float *partial,
-                                                         float *yvec)
+                                                         float *yvec, const float *Sa2, const float *Gm2,
+                                                         float *partial2)
 {
+    if (blockIdx.z) { Sa = Sa2; Gm = Gm2; partial = partial2; }   // the launch's second set
     constexpr int KB = 64, P = 68;
     constexpr int SL = KB * 16 / 256;   // float4 slots of each operand per thread and step
     constexpr int NT = D > 64 ? D / 64 : 1;   // tiles per side
@@ -717,8 +719,10 @@ __global__ __launch_bounds__(256) void outer_gemm128_kernel(const Tile *chunks, 
                                                             const float *Sa, int lda,
                                                             const float *Gm, int ldb, const float *h,
                                                             const float *ysum, float *partial,
-                                                            float *yvec)
+                                                            float *yvec, const float *Sa2, const float *Gm2,
+                                                            float *partial2)
 {
+    if (blockIdx.z) { Sa = Sa2; Gm = Gm2; partial = partial2; }   // the launch's second set
     constexpr int D = 128, KB = 32, RG = 16;    // rows per step; rows per thread and step
     constexpr int KP = KB + 8;                  // padded bf16 row of a transposed plane
     constexpr int PL = D * KP;                  // bf16 per plane
@@ -968,49 +972,51 @@ constexpr unsigned outer_tiles(int D) { return D > 64 ? (unsigned)(D / 64) * (D 
 
 template <int D>
 void outer_chunks_d(const Tile *chunks, int64_t nchunks, const int32_t *gather, int gather_x, const float *X,
-                    int ldx, const float *Gm, int ldg, float *partial, hipStream_t s)
+                    int ldx, const float *Gm, int ldg, float *partial, hipStream_t s, const float *X2,
+                    const float *Gm2, float *partial2)
 {
+    const unsigned sets = X2 ? 2 : 1;
     if constexpr (D == 128) {
-        const dim3 grid((unsigned)nchunks);
+        const dim3 grid((unsigned)nchunks, 1, sets);
         if (gather && gather_x == 2)
             hipLaunchKernelGGL((outer_gemm128_kernel<false, false, true>), grid, dim3(256), 0, s,
-                               chunks, gather, X, ldx, Gm, ldg, nullptr, nullptr, partial, nullptr);
+                               chunks, gather, X, ldx, Gm, ldg, nullptr, nullptr, partial, nullptr, X2, Gm2, partial2);
         else if (gather && gather_x)
             hipLaunchKernelGGL((outer_gemm128_kernel<false, true, true>), grid, dim3(256), 0, s,
-                               chunks, gather, X, ldx, Gm, ldg, nullptr, nullptr, partial, nullptr);
+                               chunks, gather, X, ldx, Gm, ldg, nullptr, nullptr, partial, nullptr, X2, Gm2, partial2);
         else if (gather)
             hipLaunchKernelGGL((outer_gemm128_kernel<false, true, false>), grid, dim3(256), 0, s,
-                               chunks, gather, X, ldx, Gm, ldg, nullptr, nullptr, partial, nullptr);
+                               chunks, gather, X, ldx, Gm, ldg, nullptr, nullptr, partial, nullptr, X2, Gm2, partial2);
         else
             hipLaunchKernelGGL((outer_gemm128_kernel<false, false, false>), grid, dim3(256), 0, s,
-                               chunks, nullptr, X, ldx, Gm, ldg, nullptr, nullptr, partial, nullptr);
+                               chunks, nullptr, X, ldx, Gm, ldg, nullptr, nullptr, partial, nullptr, X2, Gm2, partial2);
     } else {
-        const dim3 grid((unsigned)nchunks, outer_tiles(D));
+        const dim3 grid((unsigned)nchunks, outer_tiles(D), sets);
         if (gather && gather_x == 2)   // only the first operand gathered
             hipLaunchKernelGGL((outer_gemm_kernel<D, false, false, true>), grid, dim3(256), 0, s,
-                               chunks, gather, X, ldx, Gm, ldg, nullptr, nullptr, partial, nullptr);
+                               chunks, gather, X, ldx, Gm, ldg, nullptr, nullptr, partial, nullptr, X2, Gm2, partial2);
         else if (gather && gather_x)
             hipLaunchKernelGGL((outer_gemm_kernel<D, false, true, true>), grid, dim3(256), 0, s,
-                               chunks, gather, X, ldx, Gm, ldg, nullptr, nullptr, partial, nullptr);
+                               chunks, gather, X, ldx, Gm, ldg, nullptr, nullptr, partial, nullptr, X2, Gm2, partial2);
         else if (gather)
             hipLaunchKernelGGL((outer_gemm_kernel<D, false, true, false>), grid, dim3(256), 0, s,
-                               chunks, gather, X, ldx, Gm, ldg, nullptr, nullptr, partial, nullptr);
+                               chunks, gather, X, ldx, Gm, ldg, nullptr, nullptr, partial, nullptr, X2, Gm2, partial2);
         else
             hipLaunchKernelGGL((outer_gemm_kernel<D, false, false, false>), grid, dim3(256), 0, s,
-                               chunks, nullptr, X, ldx, Gm, ldg, nullptr, nullptr, partial, nullptr);
+                               chunks, nullptr, X, ldx, Gm, ldg, nullptr, nullptr, partial, nullptr, X2, Gm2, partial2);
     }
 }
 
 rgnn_status launch_outer_chunks(const Tile *chunks, int64_t nchunks, const int32_t *gather, int gather_x,
                                 const float *X, int ldx, const float *Gm, int ldg, float *partial, int d,
-                                hipStream_t s)
+                                hipStream_t s, const float *X2, const float *Gm2, float *partial2)
 {
     if (nchunks == 0) return RGNN_OK;
     {
         LaunchScope ls("outer_gemm", s);
-        if (d == 32) outer_chunks_d<32>(chunks, nchunks, gather, gather_x, X, ldx, Gm, ldg, partial, s);
-        else if (d == 64) outer_chunks_d<64>(chunks, nchunks, gather, gather_x, X, ldx, Gm, ldg, partial, s);
-        else if (d == 128) outer_chunks_d<128>(chunks, nchunks, gather, gather_x, X, ldx, Gm, ldg, partial, s);
+        if (d == 32) outer_chunks_d<32>(chunks, nchunks, gather, gather_x, X, ldx, Gm, ldg, partial, s, X2, Gm2, partial2);
+        else if (d == 64) outer_chunks_d<64>(chunks, nchunks, gather, gather_x, X, ldx, Gm, ldg, partial, s, X2, Gm2, partial2);
+        else if (d == 128) outer_chunks_d<128>(chunks, nchunks, gather, gather_x, X, ldx, Gm, ldg, partial, s, X2, Gm2, partial2);
         else return fail(RGNN_EUNSUPPORTED, "outer products: d must be 32, 64 or 128");
     }
     hipError_t e = hipGetLastError();
@@ -1102,8 +1108,10 @@ __global__ __launch_bounds__(1024) void slot_sum_kernel(int64_t n, int64_t nwide
 // every 16th chunk (eight loads in flight), the slice sums are added in slice
 // order.
 template <int D>
-__global__ __launch_bounds__(1024) void chunk_sum_kernel(const float *partial, const int32_t *chunkptr, float *dW)
+__global__ __launch_bounds__(1024) void chunk_sum_kernel(const float *partial, const int32_t *chunkptr, float *dW,
+                                                         const float *partial2, float *dW2)
 {
+    if (blockIdx.z) { partial = partial2; dW = dW2; }   // the launch's second set
     constexpr int NS = 16, U = 8;
     __shared__ float4 red[NS][64];
     const int t = blockIdx.x, li = threadIdx.x % 64, c = threadIdx.x / 64;
@@ -1169,13 +1177,13 @@ rgnn_status launch_src_merge(const rgnn_graph *g, const float *part, float *dh, 
 }
 
 rgnn_status launch_chunk_sum(const float *partial, const int32_t *chunkptr, int R, float *dW, int d,
-                             hipStream_t s)
+                             hipStream_t s, const float *partial2, float *dW2)
 {
     if (R == 0) return RGNN_OK;
     {
         LaunchScope ls("chunk_sum", s);
-#define CS(D) hipLaunchKernelGGL((chunk_sum_kernel<D>), dim3((unsigned)R, D * D / 256), dim3(1024), 0, s, \
-                                 partial, chunkptr, dW)
+#define CS(D) hipLaunchKernelGGL((chunk_sum_kernel<D>), dim3((unsigned)R, D * D / 256, dW2 ? 2 : 1), \
+                                 dim3(1024), 0, s, partial, chunkptr, dW, partial2, dW2)
         if (d == 32) CS(32);
         else if (d == 64) CS(64);
         else if (d == 128) CS(128);
@@ -1300,12 +1308,12 @@ rgnn_status rgat_backward_d(const rgnn_graph *g, const float *h, const float *W,
             hipLaunchKernelGGL((outer_gemm128_kernel<true, true, false>), dim3((unsigned)g->n_tiles_outer),
                                dim3(256), 0, s,
                                g->dev.tiles_outer, g->dev.vsegdst_byrel, w.Sa, D, Gm, D, h, w.ysum,
-                               w.partial, w.yvec);
+                               w.partial, w.yvec, nullptr, nullptr, nullptr);
         else
             hipLaunchKernelGGL((outer_gemm_kernel<D, true, true, false>), dim3((unsigned)g->n_tiles_outer, outer_tiles(D)),
                                dim3(256), 0, s,
                                g->dev.tiles_outer, g->dev.vsegdst_byrel, w.Sa, D, Gm, D, h, w.ysum,
-                               w.partial, w.yvec);
+                               w.partial, w.yvec, nullptr, nullptr, nullptr);
     }
     if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "outer_gemm launch");
     {

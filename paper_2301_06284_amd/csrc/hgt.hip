@@ -20,6 +20,7 @@
 // sources and segment / destination boundaries in LDS, then streams the
 // K|V rows of its edges, kU at a time with the next kU in flight; each
 // segment's query row is loaded once, while the segment before it runs.
+#include "hgt_weights.h"
 #include "rgnn_internal.h"
 #include "wave_ops.h"
 
@@ -431,16 +432,10 @@ __global__ __launch_bounds__(256) void hgt_out_fold_kernel(const float *Wmsg, co
     Wf[idx] = acc;
 }
 
-// Wmt[r][i dk + b][i dk + a] = Wmsg[r][i][a][b]: block-diagonal W_msg^T per head.
 __global__ __launch_bounds__(256) void hgt_msgT_weights_kernel(const float *Wmsg, int R, int D, int heads, float *Wmt)
 {
     const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= (int64_t)R * D * D) return;
-    const int r = (int)(idx / (D * D)), row = (int)(idx / D % D), col = (int)(idx % D);
-    const int dk = D / heads, i = row / dk;
-    float v = 0.f;
-    if (col / dk == i) v = Wmsg[(((size_t)r * heads + i) * dk + (col - i * dk)) * dk + (row - i * dk)];
-    Wmt[idx] = v;
+    if (idx < (int64_t)R * D * D) Wmt[idx] = hgt_msgT_entry(idx, Wmsg, D, heads);
 }
 
 template <int D, int H, bool FQ>
@@ -467,22 +462,12 @@ __global__ void hgt_qp_weights_kernel(const float *Watt, const float *mu, float 
     Wqp[idx] = v;
 }
 
-// Wc[r][j][n] = sum_k Wq[t][j][k] Wqp[r][k][n], t = rel_dsttype[r]: only the
-// k of n's head block contribute (Wqp[r] is block-diagonal), so each entry is
-// a dk-term product of a Wq row piece with a row of Watt[r, i].
-__global__ void hgt_qp_fold_kernel(const float *Wq, const float *Watt, const float *mu, float scale,
-                                   const int32_t *rel_dsttype, int R, int D, int heads, float *Wc)
+__global__ __launch_bounds__(256) void hgt_qp_fold_kernel(const float *Wq, const float *Watt, const float *mu,
+                                                          float scale, const int32_t *rel_dsttype, int R, int D,
+                                                          int heads, float *Wc)
 {
     const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= (int64_t)R * D * D) return;
-    const int r = (int)(idx / (D * D)), j = (int)(idx / D % D), n = (int)(idx % D);
-    const int dk = D / heads, i = n / dk;
-    const float *wq = Wq + ((size_t)rel_dsttype[r] * D + j) * D + i * dk;
-    const float *wa = Watt + (((size_t)r * heads + i) * dk + (n - i * dk)) * dk;
-    float acc = 0.f;
-#pragma unroll 16
-    for (int k = 0; k < dk; ++k) acc = fmaf(wq[k], wa[k], acc);
-    Wc[idx] = mu[r] * scale * acc;
+    if (idx < (int64_t)R * D * D) Wc[idx] = hgt_qp_fold_entry(idx, Wq, Watt, mu, scale, rel_dsttype, D, heads);
 }
 
 // whether the traversal's workgroups hold every relation's Wmsg

@@ -36,6 +36,7 @@
 // the per-relation ones instead (see "typed relations" below): no Q, dagg,
 // rebuilt aggregate or dQ, and two outer products over all nodes fewer.
 // 950 000 nodes, 10.5M edges, d = 64, 4 heads: 5.11 -> 4.28 ms.
+#include "hgt_weights.h"
 #include "rgnn_internal.h"
 #include "wave_ops.h"
 
@@ -86,7 +87,8 @@ struct DKArgs {
     const Item *items;
     const int32_t *item_slot, *dst_vsegptr, *vseg_ptr, *in_src, *vseg_pos;
     const float *KV, *QD, *saved;   // QD [V, 2D]: QP | dP of each virtual segment
-    float *Sal, *dQP, *Bac, *sfin, *spart;
+    float *Sal, *dQP, *Bac, *spart;
+    float4 *rec;   // [N, H] (max, 1 / sum, s, 0) per destination and head, for the source-major pass
 };
 
 template <int D, int H>
@@ -137,7 +139,7 @@ __global__ __launch_bounds__(256) void hgt_bwd_dst_kernel(DKArgs k)
     };
     auto flush_dst = [&](int jj) {
         if (gl % LH == 0) {
-            if (slot < 0) k.sfin[(size_t)(dst0 + jj) * H + head] = sacc;
+            if (slot < 0) k.rec[(size_t)(dst0 + jj) * H + head] = make_float4(dm, dzi, sacc, 0.f);
             else k.spart[(size_t)slot * H + head] = sacc;
         }
         sacc = 0.f;
@@ -225,11 +227,12 @@ __global__ __launch_bounds__(256) void hgt_bwd_dst_kernel(DKArgs k)
     while (j < nd) { flush_dst(j); ++j; }
 }
 
-// s of destinations split over several items: their slots summed in order.
+// The record of destinations split over several items: their s from their slots
+// in order.
 __global__ __launch_bounds__(256) void hgt_bwd_merge_s_kernel(int64_t n_split, int heads,
                                                               const int32_t *split_dst,
                                                               const int32_t *split_slotptr,
-                                                              const float *spart, float *sfin)
+                                                              const float *spart, const float *saved, float4 *rec)
 {
     const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (idx >= n_split * heads) return;
@@ -237,18 +240,9 @@ __global__ __launch_bounds__(256) void hgt_bwd_merge_s_kernel(int64_t n_split, i
     const int hh = (int)(idx % heads);
     float s = 0.f;
     for (int sl = split_slotptr[i]; sl < split_slotptr[i + 1]; ++sl) s += spart[(size_t)sl * heads + hh];
-    sfin[(size_t)split_dst[i] * heads + hh] = s;
-}
-
-// Per destination and head, (max, 1 / sum, s, 0) in one 16-byte record, so that
-// the source-major pass reads one line per out-edge for them instead of two.
-__global__ __launch_bounds__(256) void hgt_bwd_pack_kernel(int64_t n, const float *saved, const float *sfin,
-                                                           float4 *rec)
-{
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    const float2 mz = *reinterpret_cast<const float2 *>(saved + i * 2);
-    rec[i] = make_float4(mz.x, mz.y > 0.f ? 1.f / mz.y : 0.f, sfin[i], 0.f);
+    const size_t o = (size_t)split_dst[i] * heads + hh;
+    const float2 mz = *reinterpret_cast<const float2 *>(saved + o * 2);
+    rec[o] = make_float4(mz.x, mz.y > 0.f ? 1.f / mz.y : 0.f, s, 0.f);
 }
 
 // dQP = A - s_t B (A in dQP on entry) for the by-relation segment rows of the
@@ -257,7 +251,7 @@ __global__ __launch_bounds__(256) void hgt_bwd_pack_kernel(int64_t n, const floa
 constexpr int kDqpRows = 4;
 __global__ __launch_bounds__(256) void hgt_bwd_dqp_kernel(int64_t V, int D, int heads, const int32_t *vsegdst_byrel,
                                                           const int32_t *dst_vsegptr, const int32_t *rowptr,
-                                                          const float *B, const float *sfin, float *dQP)
+                                                          const float *B, const float4 *rec, float *dQP)
 {
     const int g = D / 4, gl = (int)threadIdx.x % g;
     const int64_t row0 = ((int64_t)blockIdx.x * (256 / g) + threadIdx.x / g) * kDqpRows;
@@ -274,7 +268,7 @@ __global__ __launch_bounds__(256) void hgt_bwd_dqp_kernel(int64_t V, int D, int 
     for (int i = 0; i < kDqpRows; ++i) {
         if (!todo[i]) continue;
         const size_t o = (size_t)(row0 + i) * D + gl * 4;
-        st4(dQP + o, axpy4(ld4(dQP + o), -sfin[(size_t)v[i] * heads + (gl * 4) / (D / heads)], ld4(B + o)));
+        st4(dQP + o, axpy4(ld4(dQP + o), -rec[(size_t)v[i] * heads + (gl * 4) / (D / heads)].z, ld4(B + o)));
     }
 }
 
@@ -443,21 +437,27 @@ __global__ __launch_bounds__(256) void hgt_bwd_rel_kernel(const float *OT, const
 // drops the Q and dagg projections, the rebuilt aggregate (a GEMM over the
 // segments and a reduction), dQ and two outer products over all nodes.
 
-// Wg[r][g][i dk + a] = sum_b Wa[t(r)][i dk + b][g] Wmsg[r, i][a][b].
-__global__ __launch_bounds__(256) void hgt_msg_fold_kernel(const float *Wa, const float *Wmsg,
-                                                           const int32_t *rel_dsttype, int R, int D, int heads,
-                                                           float *Wg)
+// Every per-relation and per-type weight of the typed path in one launch: blocks
+// [0, nr) Wf, [nr, 2 nr) Wg (Wa NULL: the block-diagonal Wmsg^T), then Wc[t][n][j D +
+// k] = (Wk, Wv)[j][t][n][k], for dh = [dK | dV] Wc^T.
+__global__ __launch_bounds__(256) void hgt_bwd_weights_kernel(const float *Wk, const float *Wv, const float *Wq,
+                                                              const float *Wa, const float *Watt, const float *Wmsg,
+                                                              const float *mu, const int32_t *rel_dsttype, float scale,
+                                                              int R, int T, int D, int heads, int nr, float *Wf,
+                                                              float *Wg, float *Wc)
 {
-    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= (int64_t)R * D * D) return;
-    const int r = (int)(idx / (D * D)), g = (int)(idx / D % D), n = (int)(idx % D);
-    const int dk = D / heads, i = n / dk;
-    const float *wa = Wa + ((size_t)rel_dsttype[r] * D + i * dk) * D + g;
-    const float *wm = Wmsg + (((size_t)r * heads + i) * dk + (n - i * dk)) * dk;
-    float acc = 0.f;
-#pragma unroll 16
-    for (int b = 0; b < dk; ++b) acc = fmaf(wa[(size_t)b * D], wm[b], acc);
-    Wg[idx] = acc;
+    const int b = (int)blockIdx.x, part = b < nr ? 0 : (b < 2 * nr ? 1 : 2);
+    const int64_t idx = (int64_t)(b - part * nr) * 256 + threadIdx.x;
+    if (part < 2) {
+        if (idx >= (int64_t)R * D * D) return;
+        if (part == 0) Wf[idx] = hgt_qp_fold_entry(idx, Wq, Watt, mu, scale, rel_dsttype, D, heads);
+        else if (Wa) Wg[idx] = hgt_msg_fold_entry(idx, Wa, Wmsg, rel_dsttype, D, heads);
+        else Wg[idx] = hgt_msgT_entry(idx, Wmsg, D, heads);
+    } else if (idx < (int64_t)T * D * 2 * D) {
+        const int64_t row = idx / (2 * D);
+        const int c = (int)(idx % (2 * D));
+        Wc[idx] = (c < D ? Wk : Wv)[row * D + (c < D ? c : c - D)];
+    }
 }
 
 // Per relation (blockIdx.x) and 256 entries of its head blocks (blockIdx.y):
@@ -561,15 +561,15 @@ __global__ __launch_bounds__(256) void zero_rows_kernel(const int32_t *rows, int
     if (i < n * q) st4(p + (size_t)rows[i / q] * ld + (i % q) * 4, zero4());
 }
 
-// Wc[t][n][j D + k] = W_j[t][n][k], j < np, for (W_0, W_1, W_2) = (Wk, Wv, Wq): the
-// transposed weights side by side, so that dh = [dK | dV (| dQ)] Wc^T is one GEMM.
+// Wc[t][n][j D + k] = W_j[t][n][k] for (W_0, W_1, W_2) = (Wk, Wv, Wq): the three
+// transposed weights side by side, so that dh = [dK | dV | dQ] Wc^T is one GEMM.
 __global__ __launch_bounds__(256) void hgt_cat_weights_kernel(const float *Wk, const float *Wv, const float *Wq,
-                                                              int np, int T, int D, float *Wc)
+                                                              int T, int D, float *Wc)
 {
     const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= (int64_t)T * D * np * D) return;
-    const int64_t row = idx / (np * D);
-    const int c = (int)(idx % (np * D)), j = c / D, k = c % D;
+    if (idx >= (int64_t)T * D * 3 * D) return;
+    const int64_t row = idx / (3 * D);
+    const int c = (int)(idx % (3 * D)), j = c / D, k = c % D;
     const float *W = j == 0 ? Wk : (j == 1 ? Wv : Wq);
     Wc[idx] = W[row * D + k];
 }
@@ -578,8 +578,8 @@ inline unsigned blocks_for(int64_t n, int per_block) { return (unsigned)((n + pe
 inline size_t pad256(size_t b) { return (b + 255) & ~size_t(255); }
 
 struct HgtBwdWs {
-    float *KV, *Q, *Wqp, *QD, *agg, *partial, *saved, *dagg, *Wmt, *Sal, *Bac, *sfin,
-        *spart, *dQP, *Tq, *dKV, *chunks, *OT, *M2, *rec, *Wc, *Wf, *mupart, *stat;
+    float *KV, *Q, *Wqp, *QD, *agg, *partial, *saved, *dagg, *Wmt, *Sal, *Bac,
+        *spart, *dQP, *Tq, *dKV, *chunks, *OT, *M2, *rec, *Wc, *Wf, *Wg, *mupart, *stat, *chunks2;
 };
 
 // the forward forms its segment queries from Q inside the traversal
@@ -606,13 +606,13 @@ size_t hgt_bwd_layout(const rgnn_graph *g, int D, int H, void *base, HgtBwdWs *w
     x.agg = take(N * D); x.partial = take(slots * (2 * H + D)); x.saved = take(N * H * 2);
     x.dagg = take(typed ? 0 : N * D); x.Wmt = take(R * D * D);
     x.Sal = take(V * D); x.Bac = take(V * D);
-    x.sfin = take(N * H); x.spart = take(slots * H);
+    x.spart = take(slots * H);
     x.dQP = take(V * D); x.Tq = take(V * D);
     x.dKV = take(N * (typed ? 2 : 3) * D);   // dK | dV (| dQ) side by side per node
     x.Wc = take((size_t)g->T * D * 3 * D);
-    x.chunks = take(nchunks * D * D); x.OT = take(R * D * D); x.M2 = take(R * D * D);
+    x.chunks = take(nchunks * D * D); x.chunks2 = take(nchunks * D * D); x.OT = take(R * D * D); x.M2 = take(R * D * D);
     x.rec = take(N * H * 4);
-    x.Wf = take(R * D * D);
+    x.Wf = take(R * D * D); x.Wg = take(typed ? R * D * D : 0);
     x.mupart = take(R * rel_blocks(D, H));
     x.stat = take(hgt_seg_values(g->R, D, H) ? V * H * 2 : 0);   // traversal recomputed, wide heads
     if (w) *w = x;
@@ -694,9 +694,17 @@ rgnn_status hgt_backward_d(const rgnn_graph *g, const float *h, const float *Wk,
         }
     }
     if (!fold_q && (st = launch_hgt_qp_weights(Watt, mu, att_scale, g->R, D, H, w.Wqp, s)) != RGNN_OK) return st;
-    if (typed &&
-        (st = launch_hgt_qp_fold(Wq, Watt, mu, att_scale, g->dev.rel_dsttype, g->R, D, H, w.Wf, s)) != RGNN_OK)
-        return st;
+    const bool fold_a = typed && a_linear;
+    if (typed) {
+        const unsigned nr = blocks_for((int64_t)g->R * D * D, 256);
+        {
+            LaunchScope ls("hgt_bwd_weights", s);
+            hipLaunchKernelGGL(hgt_bwd_weights_kernel, dim3(2 * nr + blocks_for((int64_t)g->T * D * 2 * D, 256)),
+                               dim3(256), 0, s, Wk, Wv, Wq, fold_a ? Wa : nullptr, Watt, Wmsg, mu, g->dev.rel_dsttype,
+                               att_scale, g->R, g->T, D, H, (int)nr, w.Wf, w.Wg, w.Wc);
+        }
+        if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "hgt_bwd_weights launch");
+    }
     {
         GemmArgs gq;
         gq.split_bf16 = 1;
@@ -721,24 +729,13 @@ rgnn_status hgt_backward_d(const rgnn_graph *g, const float *h, const float *Wk,
         dagg = w.dagg;
         if (dWa && !saved && (st = type_outer(g, D, w.agg, D, Gm, D, w.chunks, dWa, s)) != RGNN_OK) return st;
     }
-    // ---- dP = dagg_t Wmsg[r]^T per segment (vseg order); typed: G_t Wg[r], Wg in Wmt
-    const bool fold_a = typed && a_linear;
+    // ---- dP = dagg_t Wmsg[r]^T per segment (vseg order); typed: G_t Wg[r]
     if (g->V > 0) {
-        if (fold_a) {
-            {
-                const int64_t n = (int64_t)g->R * D * D;
-                LaunchScope ls("hgt_msgT_weights", s);
-                hipLaunchKernelGGL(hgt_msg_fold_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, s, Wa, Wmsg,
-                                   g->dev.rel_dsttype, g->R, D, H, w.Wmt);
-            }
-            if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "msg fold launch");
-        } else if ((st = launch_hgt_msgT_weights(Wmsg, g->R, D, H, w.Wmt, s)) != RGNN_OK) {
-            return st;
-        }
+        if (!typed && (st = launch_hgt_msgT_weights(Wmsg, g->R, D, H, w.Wmt, s)) != RGNN_OK) return st;
         GemmArgs gp;
         gp.split_bf16 = 1;
         gp.X = dagg; gp.ldx = D; gp.gather = g->dev.vsegdst_byrel; gp.scatter = g->dev.vseg_byrel;
-        gp.W[0] = w.Wmt; gp.K = D; gp.Nc = D;
+        gp.W[0] = typed ? w.Wg : w.Wmt; gp.K = D; gp.Nc = D;
         gp.tiles = g->gemm_tiles(kRowsVsegsDst);
         gp.Y = w.QD + D; gp.ldy = 2 * D; gp.ep.diag_blocks = fold_a ? 1 : H;
         if ((st = launch_typed_gemm(gp, s)) != RGNN_OK) return st;
@@ -750,7 +747,7 @@ rgnn_status hgt_backward_d(const rgnn_graph *g, const float *h, const float *Wk,
         k.dst_vsegptr = g->dev.dst_vsegptr; k.vseg_ptr = g->dev.vseg_ptr; k.in_src = g->dev.in_src;
         k.vseg_pos = g->dev.vseg_pos;
         k.KV = w.KV; k.QD = w.QD; k.saved = stats;
-        k.Sal = w.Sal; k.dQP = w.dQP; k.Bac = w.Bac; k.sfin = w.sfin; k.spart = w.spart;
+        k.Sal = w.Sal; k.dQP = w.dQP; k.Bac = w.Bac; k.spart = w.spart; k.rec = reinterpret_cast<float4 *>(w.rec);
         const unsigned nb = blocks_for(g->n_items, GPB);
         {
             LaunchScope ls("hgt_bwd_dst", s);
@@ -767,7 +764,8 @@ rgnn_status hgt_backward_d(const rgnn_graph *g, const float *h, const float *Wk,
         {
             LaunchScope ls("hgt_bwd_merge_s", s);
             hipLaunchKernelGGL(hgt_bwd_merge_s_kernel, dim3(blocks_for(g->n_split * H, 256)), dim3(256), 0, s,
-                               g->n_split, H, g->dev.split_dst, g->dev.split_slotptr, w.spart, w.sfin);
+                               g->n_split, H, g->dev.split_dst, g->dev.split_slotptr, w.spart, stats,
+                               reinterpret_cast<float4 *>(w.rec));
         }
         if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "hgt_bwd_merge_s launch");
     }
@@ -792,7 +790,7 @@ rgnn_status hgt_backward_d(const rgnn_graph *g, const float *h, const float *Wk,
         {
             LaunchScope ls("hgt_bwd_dqp", s);
             hipLaunchKernelGGL(hgt_bwd_dqp_kernel, dim3(blocks_for(g->V, GPB * kDqpRows)), dim3(256), 0, s,
-                               g->V, D, H, g->dev.vsegdst_byrel, g->dev.dst_vsegptr, g->dev.rowptr, w.Bac, w.sfin, w.dQP);
+                               g->V, D, H, g->dev.vsegdst_byrel, g->dev.dst_vsegptr, g->dev.rowptr, w.Bac, reinterpret_cast<const float4 *>(w.rec), w.dQP);
         }
         if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "hgt_bwd_dqp launch");
         GemmArgs gt;
@@ -806,18 +804,10 @@ rgnn_status hgt_backward_d(const rgnn_graph *g, const float *h, const float *Wk,
     if (!typed && (st = launch_vseg_reduce(g, w.Tq, nullptr, D, w.dKV + 2 * D, 0, 0, s, ldk)) != RGNN_OK) return st;
     // ---- per-relation outer products (typed: with h and G, else with Q and
     //      dagg) and the weight gradients that follow from them
-    if (g->V > 0) {
-        if ((st = launch_outer_chunks(g->dev.tiles_outer, g->n_tiles_outer, g->dev.vsegdst_byrel, 0, w.dQP, D,
-                                      typed ? h : w.Q, D, w.chunks, D, s)) != RGNN_OK)
-            return st;
-    }
-    if ((st = launch_chunk_sum(w.chunks, g->dev.rel_chunkptr, g->R, w.OT, D, s)) != RGNN_OK) return st;
-    if (g->V > 0) {
-        if ((st = launch_outer_chunks(g->dev.tiles_outer, g->n_tiles_outer, g->dev.vsegdst_byrel, 0, w.Sal, D, dagg,
-                                      D, w.chunks, D, s)) != RGNN_OK)
-            return st;
-    }
-    if ((st = launch_chunk_sum(w.chunks, g->dev.rel_chunkptr, g->R, w.M2, D, s)) != RGNN_OK) return st;
+    if (g->V > 0 && (st = launch_outer_chunks(g->dev.tiles_outer, g->n_tiles_outer, g->dev.vsegdst_byrel, 0, w.dQP, D,
+                                              typed ? h : w.Q, D, w.chunks, D, s, w.Sal, dagg, w.chunks2)) != RGNN_OK)
+        return st;
+    if ((st = launch_chunk_sum(w.chunks, g->dev.rel_chunkptr, g->R, w.OT, D, s, w.chunks2, w.M2)) != RGNN_OK) return st;
     if (g->R > 0 && typed) {
         const int nrb = rel_blocks(D, H), nb = g->T * D * D / 64, wa = a_linear && dWa ? 1 : 0;
         {
@@ -841,14 +831,6 @@ rgnn_status hgt_backward_d(const rgnn_graph *g, const float *h, const float *Wk,
                                att_scale, D, H, dWatt, dWmsg, dmu);
         }
         if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "hgt_bwd_rel launch");
-    }
-    if (g->N > 0) {
-        {
-            LaunchScope ls("hgt_bwd_pack", s);
-            hipLaunchKernelGGL(hgt_bwd_pack_kernel, dim3(blocks_for(g->N * H, 256)), dim3(256), 0, s, g->N * H,
-                               stats, w.sfin, reinterpret_cast<float4 *>(w.rec));
-        }
-        if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "hgt_bwd_pack launch");
     }
     // ---- source-major pass: dK | dV per source (the rows of sources split over
     //      several items are summed with atomics and start from zero)
@@ -881,11 +863,11 @@ rgnn_status hgt_backward_d(const rgnn_graph *g, const float *h, const float *Wk,
     const float *res = (flags & RGNN_FLAG_RESIDUAL) ? Gm : nullptr;
     if constexpr (D <= 64) {   // dh = [dK | dV (| dQ)] [Wk | Wv (| Wq)]^T in one GEMM
         const int np = typed ? 2 : 3;
-        if (g->T > 0) {
-            const int64_t n = (int64_t)g->T * D * np * D;
+        if (g->T > 0 && !typed) {
+            const int64_t n = (int64_t)g->T * D * 3 * D;
             LaunchScope ls("hgt_cat_weights", s);
-            hipLaunchKernelGGL(hgt_cat_weights_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, s, Wk, Wv, Wq, np, g->T,
-                               D, w.Wc);
+            hipLaunchKernelGGL(hgt_cat_weights_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, s, Wk, Wv, Wq, g->T, D,
+                               w.Wc);
         }
         if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "cat weights launch");
         GemmArgs ga;
@@ -902,8 +884,10 @@ rgnn_status hgt_backward_d(const rgnn_graph *g, const float *h, const float *Wk,
         if (!typed && (st = node_gemm_t(g, D, w.dKV + 2 * D, ldk, Wq, dh, nullptr, 1, s)) != RGNN_OK) return st;
     }
     if (typed && (st = launch_vseg_reduce(g, w.Tq, nullptr, D, dh, 1, 0, s)) != RGNN_OK) return st;
-    if ((st = type_outer(g, D, h, D, w.dKV, ldk, w.chunks, dWk, s)) != RGNN_OK) return st;
-    if ((st = type_outer(g, D, h, D, w.dKV + D, ldk, w.chunks, dWv, s)) != RGNN_OK) return st;
+    if ((st = launch_outer_chunks(g->dev.tiles_types_outer, g->n_tiles_types_outer, g->dev.ntype_perm, 1, h, D, w.dKV,
+                                  ldk, w.chunks, D, s, h, w.dKV + D, w.chunks2)) != RGNN_OK)
+        return st;
+    if ((st = launch_chunk_sum(w.chunks, g->dev.types_chunkptr, g->T, dWk, D, s, w.chunks2, dWv)) != RGNN_OK) return st;
     if (!typed && (st = type_outer(g, D, h, D, w.dKV + 2 * D, ldk, w.chunks, dWq, s)) != RGNN_OK) return st;
     return RGNN_OK;
 }

@@ -404,7 +404,8 @@ rgnn_status launch_af_fused(const FusedArgs &a, hipStream_t s);
 // strides.
 rgnn_status launch_outer_chunks(const Tile *chunks, int64_t nchunks, const int32_t *gather, int gather_x,
                                 const float *X, int ldx, const float *Gm, int ldg, float *partial, int d,
-                                hipStream_t s);
+                                hipStream_t s, const float *X2 = nullptr, const float *Gm2 = nullptr,
+                                float *partial2 = nullptr);   // a second set of the same shape
 // dW[r] = sum of partial[c] for c in [chunkptr[r], chunkptr[r+1]) in order (d x d each).
 // Pieces of split sources: dh[osplit[i]] += the partial rows of its slots
 // [osplit_slotptr[i], osplit_slotptr[i + 1]) in a fixed order (d in {32, 64, 128}).
@@ -418,7 +419,7 @@ rgnn_status launch_slot_sum(int64_t n, int64_t nwide, const int32_t *order, cons
                             const int32_t *slotptr, const float *part, float *out, int w, bool accumulate,
                             const char *name, hipStream_t s);
 rgnn_status launch_chunk_sum(const float *partial, const int32_t *chunkptr, int R, float *dW, int d,
-                             hipStream_t s);
+                             hipStream_t s, const float *partial2 = nullptr, float *dW2 = nullptr);
 // RGAT backward with several heads (2 to 8, d / heads >= 16) in one pass over
 // the graph; need != NULL: only the workspace size.
 rgnn_status rgat_backward_heads_impl(const rgnn_graph *g, const float *h, const float *W, const float *w_src,
