@@ -202,17 +202,22 @@ size_t hgt_layout(const rgnn_graph *g, int d, int H, void *base, HgtWs *w)
     return c.off;
 }
 
-size_t segment_gemm_layout(int64_t M, int32_t T, void *base, Tile **tiles, int64_t *ntiles)
+// Tiles of `rows` rows over M rows of T types: every type may add one partial tile.
+int64_t segment_tiles_bound(int64_t M, int32_t T, int64_t rows) { return std::max<int64_t>((M + rows - 1) / rows + T, 1); }
+
+// The size of the tile table for any number of rows up to M: tile_rows_for's
+// count rises to kGemmTilesWanted, drops where the rows per tile step up, and
+// ends at M / kGemmTileRows.
+size_t segment_gemm_need(int64_t M, int32_t T)
 {
-    // upper bound on the tile count: every type may add one partial tile (the
-    // wide shapes' tiles are never smaller)
-    const int rows = tile_rows_for(M, kGemmTilesWanted, kGemmTileRows);
-    const int64_t n = (M + rows - 1) / rows + T;
-    Carver c(base);
-    Tile *t = c.take<Tile>((size_t)std::max<int64_t>(n, 1));
-    if (tiles) *tiles = t;
-    if (ntiles) *ntiles = n;
-    return c.off;
+    const int64_t small = segment_tiles_bound(std::min<int64_t>(M, 64 * kGemmTilesWanted), T, 64);
+    return pad256((size_t)std::max(small, segment_tiles_bound(M, T, kGemmTileRows)) * sizeof(Tile));
+}
+
+// What the call insists on: the table with the largest tiles.
+size_t segment_gemm_least(int64_t M, int32_t T)
+{
+    return pad256((size_t)segment_tiles_bound(M, T, kGemmTileRows) * sizeof(Tile));
 }
 
 }  // namespace
@@ -753,7 +758,7 @@ extern "C" rgnn_status rgcn_backward(const rgnn_graph_t *g, const float *h, cons
 extern "C" rgnn_status rgnn_segment_gemm_workspace_size(int64_t M, int32_t num_types, size_t *bytes)
 {
     if (!bytes || M < 0 || num_types <= 0) return fail(RGNN_EINVAL, "bad argument");
-    *bytes = segment_gemm_layout(M, num_types, nullptr, nullptr, nullptr);
+    *bytes = segment_gemm_need(M, num_types);
     return RGNN_OK;
 }
 
@@ -772,16 +777,19 @@ extern "C" rgnn_status rgnn_segment_gemm(const float *X, int64_t ldx, const int3
         if (type_ptr[t + 1] < type_ptr[t]) return fail(RGNN_EINVAL, "type_ptr is not monotone");
     const int64_t M = type_ptr[num_types];
     if (M >= (int64_t(1) << 31) - 1) return fail(RGNN_ERANGE, "too many rows");
-    const size_t need = segment_gemm_layout(M, num_types, nullptr, nullptr, nullptr);
+    const size_t need = segment_gemm_least(M, num_types);
     if (!ws || ws_bytes < need)
         return fail(RGNN_EINVAL, "workspace too small: need " + std::to_string(need) + " bytes");
     if (M == 0) return RGNN_OK;
-    Tile *dt = nullptr;
-    segment_gemm_layout(M, num_types, ws, &dt, nullptr);
+    Tile *dt = (Tile *)ws;
     hipStream_t s = (hipStream_t)stream;
     const int64_t want = wide_shape(K, Nc) ? kGemmTilesWantedWide : kGemmTilesWanted;
+    // larger tiles where the workspace has no room for as many as the shape wants
+    // (kGemmTileRows always fits)
+    int rows = tile_rows_for(M, want, kGemmTileRows);
+    while (rows < kGemmTileRows && segment_tiles_bound(M, num_types, rows) * sizeof(Tile) > ws_bytes) rows += 64;
     int64_t ntiles = 0;
-    rgnn_status st = launch_segment_tiles(type_ptr, num_types, tile_rows_for(M, want, kGemmTileRows), dt, &ntiles, s);
+    rgnn_status st = launch_segment_tiles(type_ptr, num_types, rows, dt, &ntiles, s);
     if (st != RGNN_OK) return st;
     GemmArgs ga;
     ga.split_bf16 = 1;

@@ -154,3 +154,15 @@ def test_graph_without_compaction_host_only():
     for k in ("dst_rowptr", "in_src", "in_rel", "in_eid", "seg_ptr", "out_pos"):
         np.testing.assert_array_equal(a.export(k), b.export(k), err_msg=k)
     a.close(); b.close()
+
+
+@pytest.mark.parametrize("T", [1, 96])
+def test_segment_gemm_workspace_grows_with_rows(T):
+    """A workspace sized for the most rows serves every smaller call: the size
+    never falls as the rows grow, also where the tiles' rows step up."""
+    rgnn = _rgnn()
+    rows = [0, 1, 63, 64, 65, 1000]
+    for k in range(1, 10):   # the steps lie at multiples of 64 * 768 rows
+        rows += [k * 49152 - 1, k * 49152, k * 49152 + 1, k * 49152 + 20000]
+    sizes = [rgnn.segment_gemm_workspace_size(m, T) for m in rows + [1000003, 10000000]]
+    assert sizes == sorted(sizes)

@@ -943,6 +943,34 @@ def test_fused_tile_edges(d, R, E, N):
     run.close()
 
 
+@pytest.mark.parametrize("K,Nc", [(64, 64), (128, 128)])
+@pytest.mark.parametrize("ws_rows", ["more", "least"])
+def test_segment_gemm_workspace_of_other_rows(K, Nc, ws_rows):
+    """Workspaces made for more rows than the call has, and of the smallest size
+    taken (one 16-byte entry per 512 rows and type, a multiple of 256 bytes)."""
+    import torch
+    from paper_2301_06284_amd import rgnn
+    M, T = 49152, 5
+    type_ptr = np.array([0, 1, 1, 20000, 49000, M], np.int64)
+    least = (((M + 511) // 512 + T) * 16 + 255) // 256 * 256
+    n = rgnn.segment_gemm_workspace_size(60000, T) if ws_rows == "more" else least
+    print(f"segment_gemm workspace {ws_rows} {n} bytes {K}x{Nc}", flush=True)
+    rng = np.random.default_rng(K)
+    dev = torch.device("cuda:0")
+    X = torch.from_numpy(rng.standard_normal((M, K)).astype(np.float32)).to(dev)
+    W = torch.from_numpy(rng.standard_normal((T, K, Nc)).astype(np.float32)).to(dev)
+    Y = torch.full((M, Nc), float("nan"), device=dev)
+    buf = torch.full((n + 4096,), 7, dtype=torch.uint8, device=dev)
+    rgnn.segment_gemm(X, None, type_ptr, W, Y, None, buf[:n], K, Nc)
+    torch.cuda.synchronize()
+    assert bool((buf[n:] == 7).all())
+    Xh, Wh, got = X.cpu().double(), W.cpu().double(), Y.cpu().numpy()
+    for t in range(T):
+        b, e = type_ptr[t], type_ptr[t + 1]
+        if e > b:
+            assert row_err(got[b:e], (Xh[b:e] @ Wh[t]).numpy()) <= TOL
+
+
 @pytest.mark.parametrize("T", [1, 511, 512, 513, 1030])
 @pytest.mark.parametrize("K,Nc", [(32, 32), (64, 128), (128, 128)])
 def test_segment_gemm_many_types(K, Nc, T):
