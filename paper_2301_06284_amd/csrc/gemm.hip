@@ -467,7 +467,7 @@ __global__ __launch_bounds__(kTypesPerLaunch) void segment_tiles_kernel(TypeOffs
 {
     __shared__ int32_t pre[2][kTypesPerLaunch + 1];   // tiles before each type, ping-pong
     const int t = threadIdx.x;
-    pre[0][t + 1] = t < n ? (p.row[t + 1] - p.row[t] + rows - 1) / rows : 0;
+    pre[0][t + 1] = t < n ? tile_count(p.row[t + 1] - p.row[t], rows) : 0;
     if (t == 0) pre[0][0] = pre[1][0] = 0;
     __syncthreads();
     int cur = 0;
@@ -563,7 +563,7 @@ rgnn_status launch_segment_tiles(const int64_t *type_ptr, int ntypes, int rows, 
         int64_t here = 0;
         for (int t = 0; t <= n; ++t) {
             p.row[t] = (int32_t)type_ptr[t0 + t];
-            if (t) here += (type_ptr[t0 + t] - type_ptr[t0 + t - 1] + rows - 1) / rows;
+            if (t) here += tile_count(p.row[t] - p.row[t - 1], rows);
         }
         for (int t = n + 1; t <= kTypesPerLaunch; ++t) p.row[t] = p.row[n];
         if (here) {

@@ -68,6 +68,9 @@ constexpr int64_t kMinBundleEdges = 16;
 struct Tile {          // one typed-GEMM tile: rows [row0, row0 + rows) of type `type`
     int32_t type, row0, rows, pad;
 };
+// Tiles of at most `rows` rows over n rows of one type, on the host and on the
+// device alike; without the sum n + rows - 1, which overflows near 2^31 rows.
+constexpr int32_t tile_count(int32_t n, int32_t rows) { return n / rows + (n % rows != 0); }
 
 // The two tables over one set of rows: for the narrow weight shapes, and for
 // the wide ones (the same table when both come out with the same tiles).

@@ -14,6 +14,7 @@
 //   index <in> <out>   build the graph described by <in> (see read_graph) and
 //                      write its info and every exported index array to <out>
 //   errors             invalid inputs -> the documented status codes
+//   tiles              the tile count of one type at the ends of its range
 //   nomem <in>         fail the k-th allocation of a graph creation, for every
 //                      k until a creation runs without failure
 #include <cstdint>
@@ -26,6 +27,7 @@
 #include <hip/hip_runtime_api.h>
 
 #include "rgnn.h"
+#include "rgnn_internal.h"
 
 // ---------------------------------------------------------------- no device
 hipError_t hipMalloc(void **p, size_t) { if (p) *p = nullptr; return hipErrorNoDevice; }
@@ -195,6 +197,27 @@ static int mode_errors()
     return bad ? 1 : 0;
 }
 
+// Counts of one type's tiles against 64-bit arithmetic, up to the most rows the
+// segment GEMM accepts (2^31 - 2): a count that overflows 32 bits on the device
+// would leave tiles unwritten that the host launches.
+static int mode_tiles()
+{
+    const int64_t rows[] = {0, 1, 63, 64, 65, 511, 512, 513, (int64_t(1) << 31) - 514, (int64_t(1) << 31) - 513,
+                            (int64_t(1) << 31) - 512, (int64_t(1) << 31) - 66, (int64_t(1) << 31) - 64,
+                            (int64_t(1) << 31) - 63, (int64_t(1) << 31) - 2};
+    for (int64_t n : rows)
+        for (int32_t per = 64; per <= rgnn::kGemmTileRows; per += 64) {
+            const int64_t want = (n + per - 1) / per;
+            const int32_t got = rgnn::tile_count((int32_t)n, per);
+            if (got != want) {
+                std::printf("FAIL %lld rows in tiles of %d: %d (want %lld)\n", (long long)n, per, got, (long long)want);
+                return 1;
+            }
+        }
+    std::printf("ok tile counts\n");
+    return 0;
+}
+
 static int mode_nomem(const char *in)
 {
     GraphIn g;
@@ -227,7 +250,8 @@ int main(int argc, char **argv)
 {
     if (argc >= 4 && !std::strcmp(argv[1], "index")) return mode_index(argv[2], argv[3]);
     if (argc >= 2 && !std::strcmp(argv[1], "errors")) return mode_errors();
+    if (argc >= 2 && !std::strcmp(argv[1], "tiles")) return mode_tiles();
     if (argc >= 3 && !std::strcmp(argv[1], "nomem")) return mode_nomem(argv[2]);
-    std::fprintf(stderr, "usage: %s index <in> <out> | errors | nomem <in>\n", argv[0]);
+    std::fprintf(stderr, "usage: %s index <in> <out> | errors | tiles | nomem <in>\n", argv[0]);
     return 2;
 }

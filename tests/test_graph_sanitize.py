@@ -112,6 +112,11 @@ def test_error_codes_under_sanitizers(exe):
     assert log.count("ok ") >= 25, log
 
 
+def test_tile_counts_under_sanitizers(exe):
+    rc, log = run(exe, "tiles")
+    assert rc == 0 and "ok tile counts" in log, log
+
+
 @pytest.mark.parametrize("kind,csr", [("hub", False), ("dups", True)])
 def test_allocation_failure_enomem_no_leak(exe, tmp_path, kind, csr):
     """Every host allocation of a graph creation is failed in turn: each
