@@ -406,8 +406,8 @@ __global__ __launch_bounds__(256) void hgt_seg_reduce_kernel(int64_t N, int64_t 
         if (gl % LH == 0) pms[gi * H + head] = make_float2(m, s);
         __syncthreads();
         if (gi != 0) return;
-        for (int j = 1; j < NG; ++j)
-            if (pms[j * H + head].y > 0.f) merge(pms[j * H + head].x, pms[j * H + head].y, pacc[j * G + gl]);
+        for (int j = 1; j < NG; ++j)   // groups without segments skipped; a NaN sum is merged
+            if (!(pms[j * H + head].y == 0.f)) merge(pms[j * H + head].x, pms[j * H + head].y, pacc[j * G + gl]);
     }
     float4 o = scale4(acc, s > 0.f ? 1.f / s : 0.f);
     if (residual) o = add4(o, ld4(residual + (size_t)v * D + gl * 4));

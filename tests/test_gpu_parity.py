@@ -1012,3 +1012,32 @@ def test_segment_gemm_many_types(K, Nc, T):
     for _ in range(3):
         check(g.replay)
         check(call)
+
+
+@pytest.mark.parametrize("flags", [0, 4])
+@pytest.mark.parametrize("d", [32, 64, 128])
+def test_hgt_wide_heads_nan_row(d, flags):
+    """A source row of NaN reaches every destination it has an edge to, also those
+    of more than 32 segments whose shares several groups of lanes merge (one item:
+    at most 64 in-edges), and no other destination."""
+    N, R, bad = 80, 64, 70
+    rng = np.random.default_rng(91)
+    dst = np.concatenate([np.full(n, v) for v, n in enumerate((33, 40, 64, 48))] + [np.arange(4, 64)])
+    rel = np.concatenate([np.arange(n) for n in (33, 40, 64, 48)] + [np.zeros(60, int)])
+    src = rng.integers(0, 64, len(dst))
+    hit = [0 * 33 + 5, 33 + 39, 33 + 40 + 17, 33 + 40 + 64 + 48 + 3]   # one edge of nodes 0, 1, 2 and 7
+    src[hit] = bad
+    g = dict(N=N, E=len(src), R=R, T=1, src=src.astype(np.int32), dst=dst.astype(np.int32),
+             rel=rel.astype(np.int32), ntype=np.zeros(N, np.int32))
+    t = workloads.tiny_tensors(91, g, d, d, heads=1)
+    print(f"hgt NaN row d={d} flags={flags}", flush=True)
+    run = Runner(g, t)
+    clean = run.hgt(1, 0.2, flags=flags)
+    run.close()
+    t["h"][bad] = np.nan
+    run = Runner(g, t)
+    got = run.hgt(1, 0.2, flags=flags)
+    run.close()
+    reached = np.isin(np.arange(N), dst[hit])
+    assert np.isnan(got[reached]).all()
+    np.testing.assert_array_equal(got[~reached], clean[~reached])
