@@ -462,11 +462,14 @@ __global__ __launch_bounds__(256) void hgt_bwd_weights_kernel(const float *Wk, c
 
 // Per relation (blockIdx.x) and 256 entries of its head blocks (blockIdx.y):
 // dWatt = c_r (P1 Wq[t])[blocks], dWmsg = (P2 Wa[t]^T)[blocks] (Wa NULL: P2's
-// blocks), and the block's share of <P1 Wq[t], Watt> for dmu.
+// blocks), and the block's share of <P1 Wq[t], Watt> for dmu.  A relation without
+// segments (rel_ptr) has zero products whatever the weights of the node type that
+// stands in for its own hold.
 __global__ __launch_bounds__(256) void hgt_bwd_rel_typed_kernel(const float *P1, const float *P2, const float *Wq,
                                                                 const float *Wa, const float *Watt, const float *mu,
-                                                                const int32_t *rel_dsttype, float scale, int D,
-                                                                int heads, float *dWatt, float *dWmsg, float *mupart)
+                                                                const int32_t *rel_dsttype, const int32_t *rel_ptr,
+                                                                float scale, int D, int heads, float *dWatt,
+                                                                float *dWmsg, float *mupart)
 {
     __shared__ float red[4];
     const int r = blockIdx.x, tid = threadIdx.x;
@@ -480,14 +483,16 @@ __global__ __launch_bounds__(256) void hgt_bwd_rel_typed_kernel(const float *P1,
         const float *p2 = P2 + ((size_t)r * D + i * dk + p) * D;
         const float *wq = Wq + t * D + i * dk + q;
         float ot = 0.f, m2 = 0.f;
+        if (rel_ptr[r + 1] > rel_ptr[r]) {
 #pragma unroll 16
-        for (int k = 0; k < D; ++k) ot = fmaf(p1[k], wq[(size_t)k * D], ot);
-        if (Wa) {
-            const float *wa = Wa + (t + i * dk + q) * D;
+            for (int k = 0; k < D; ++k) ot = fmaf(p1[k], wq[(size_t)k * D], ot);
+            if (Wa) {
+                const float *wa = Wa + (t + i * dk + q) * D;
 #pragma unroll 16
-            for (int k = 0; k < D; ++k) m2 = fmaf(p2[k], wa[k], m2);
-        } else {
-            m2 = p2[i * dk + q];
+                for (int k = 0; k < D; ++k) m2 = fmaf(p2[k], wa[k], m2);
+            } else {
+                m2 = p2[i * dk + q];
+            }
         }
         dWatt[(size_t)r * n + idx] = mu[r] * scale * ot;
         dWmsg[(size_t)r * n + idx] = m2;
@@ -502,12 +507,15 @@ __global__ __launch_bounds__(256) void hgt_bwd_rel_typed_kernel(const float *P1,
 
 // Blocks [0, nb): 64 entries of dWq[t], nb = T D^2 / 64; then, with Wmsg, nb
 // blocks for dWa[t]; the last ones dmu.  Sixteen slices of threads take every
-// sixteenth relation, their sums are added in slice order.
+// sixteenth relation, their sums are added in slice order.  Relations without
+// segments are left out: their weights have no part in the layer and may hold
+// anything.
 __global__ __launch_bounds__(1024) void hgt_bwd_type_kernel(const float *P1, const float *P2, const float *Watt,
                                                             const float *Wmsg, const float *mu,
-                                                            const int32_t *rel_dsttype, float scale, int R, int D,
-                                                            int heads, int nb, int want_wa, const float *mupart,
-                                                            int nmu, float *dWq, float *dWa, float *dmu)
+                                                            const int32_t *rel_dsttype, const int32_t *rel_ptr,
+                                                            float scale, int R, int D, int heads, int nb, int want_wa,
+                                                            const float *mupart, int nmu, float *dWq, float *dWa,
+                                                            float *dmu)
 {
     __shared__ float red[16][64];
     const int tid = threadIdx.x, li = tid & 63, sl = tid >> 6;
@@ -528,7 +536,7 @@ __global__ __launch_bounds__(1024) void hgt_bwd_type_kernel(const float *P1, con
     const int t = (int)(idx / (D * D)), row = (int)(idx / D % D), col = (int)(idx % D);
     float acc = 0.f;
     for (int r = sl; r < R; r += 16) {
-        if (rel_dsttype[r] != t) continue;
+        if (rel_dsttype[r] != t || rel_ptr[r + 1] == rel_ptr[r]) continue;
         if (which == 0) {   // dWq[j][i dk + q] += c_r sum_p P1[i dk + p][j] Watt[i][p][q]
             const int i = col / dk;
             const float *p1 = P1 + ((size_t)r * D + i * dk) * D + row;
@@ -813,15 +821,15 @@ rgnn_status hgt_backward_d(const rgnn_graph *g, const float *h, const float *Wk,
         {
             LaunchScope ls("hgt_bwd_rel", s);
             hipLaunchKernelGGL(hgt_bwd_rel_typed_kernel, dim3((unsigned)g->R, (unsigned)nrb), dim3(256), 0, s, w.OT,
-                               w.M2, Wq, a_linear ? Wa : nullptr, Watt, mu, g->dev.rel_dsttype, att_scale, D, H, dWatt,
-                               dWmsg, w.mupart);
+                               w.M2, Wq, a_linear ? Wa : nullptr, Watt, mu, g->dev.rel_dsttype, g->dev.rel_vsegptr,
+                               att_scale, D, H, dWatt, dWmsg, w.mupart);
         }
         if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "hgt_bwd_rel launch");
         {
             LaunchScope ls("hgt_bwd_type", s);
             hipLaunchKernelGGL(hgt_bwd_type_kernel, dim3((unsigned)((1 + wa) * nb) + blocks_for(g->R, 1024)),
-                               dim3(1024), 0, s, w.OT, w.M2, Watt, Wmsg, mu, g->dev.rel_dsttype, att_scale, g->R, D, H,
-                               nb, wa, w.mupart, nrb, dWq, dWa, dmu);
+                               dim3(1024), 0, s, w.OT, w.M2, Watt, Wmsg, mu, g->dev.rel_dsttype, g->dev.rel_vsegptr,
+                               att_scale, g->R, D, H, nb, wa, w.mupart, nrb, dWq, dWa, dmu);
         }
         if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "hgt_bwd_type launch");
     } else if (g->R > 0) {

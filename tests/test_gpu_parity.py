@@ -1041,3 +1041,37 @@ def test_hgt_wide_heads_nan_row(d, flags):
     reached = np.isin(np.arange(N), dst[hit])
     assert np.isnan(got[reached]).all()
     np.testing.assert_array_equal(got[~reached], clean[~reached])
+
+
+@pytest.mark.parametrize("flags", [2, 6])
+@pytest.mark.parametrize("d,heads", [(32, 2), (64, 4), (128, 1)])
+def test_hgt_backward_unused_weights(d, heads, flags):
+    """The weights of a relation without edges and of a node type without nodes
+    have no part in the layer: whatever they hold, the gradients of everything
+    else are what they are with ordinary values there."""
+    N, R, T = 300, 6, 4
+    g = workloads.tiny_graph(93, N=N, E=5000, R=R, T=T, kind="random")
+    g["ntype"] = (1 + np.arange(N) % 3).astype(np.int32)                    # none of type 0
+    g["rel"] = np.where(g["ntype"][g["dst"]] == 1, g["rel"] % 2, 1 + g["ntype"][g["dst"]]).astype(np.int32)
+    assert not (g["rel"] == 5).any() and len(np.unique(g["rel"])) == 4      # 5 (and one type's 4) unused
+    unused = np.setdiff1d(np.arange(R), g["rel"])
+    t = workloads.tiny_tensors(93, g, d, d, heads=heads)
+    print(f"hgt backward unused weights d={d} heads={heads} flags={flags}", flush=True)
+    run = Runner(g, t)
+    clean = [run.hgt_backward(heads, 0.3, flags=flags, use_saved=s) for s in (False, True)]
+    run.close()
+    for k in ("Wk", "Wq", "Wv", "Wa"):
+        t[k][0] = np.nan
+    for k in ("Watt", "Wmsg"):
+        t[k][unused] = np.inf
+    t["mu"][unused] = np.nan
+    run = Runner(g, t)
+    got = [run.hgt_backward(heads, 0.3, flags=flags, use_saved=s) for s in (False, True)]
+    run.close()
+    used = np.setdiff1d(np.arange(R), unused)
+    for a, b in zip(got, clean):
+        for k in a:
+            if a[k] is None:
+                continue
+            rows = used if k in ("dWatt", "dmu") else slice(None)   # those scale with the weights themselves
+            np.testing.assert_array_equal(a[k][rows], b[k][rows], err_msg=k)
