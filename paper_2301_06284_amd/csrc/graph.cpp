@@ -57,7 +57,7 @@ int tile_rows_for(int64_t total, int64_t want, int most)
 // the tiles of one range -- one per relation that enters it -- land on the same
 // XCD (workgroups are dealt to the eight XCDs in turn) at about the same time:
 // a destination row gathered by several relations' tiles is read from HBM once
-// and from that XCD's L2 after that.
+// and from that XCD's L2 after that.  Only for graphs that dst_ranges_pay accepts.
 void build_tiles_dst_ranges(const std::vector<int32_t> &rel_ptr, const std::vector<int32_t> &row_dst, int32_t span,
                             int tile_rows, std::vector<Tile> &out)
 {
@@ -100,6 +100,26 @@ void build_tiles_dst_ranges(const std::vector<int32_t> &rel_ptr, const std::vect
             }
         a = b;
     }
+}
+
+// Whether the segments of each relation lie in runs of at least kDstRangeRows per
+// range of `span` destinations, weighted by rows (the run that a row is in).  Every
+// run is a tile of its own that stages a whole weight, and their number grows with
+// the relations, not with the rows: by destination range a graph of 300 000 nodes
+// and 535 relations has 216 000 tiles of 5 rows, by relation 2 500.
+bool dst_ranges_pay(const std::vector<int32_t> &rel_ptr, const std::vector<int32_t> &row_dst, int32_t span)
+{
+    const int R = (int)rel_ptr.size() - 1;
+    double sq = 0;
+    for (int r = 0; r < R; ++r)
+        for (int32_t i = rel_ptr[r]; i < rel_ptr[r + 1];) {
+            const int32_t rg = row_dst[i] / span;
+            int32_t j = i;
+            while (j < rel_ptr[r + 1] && row_dst[j] / span == rg) ++j;
+            sq += (double)(j - i) * (j - i);
+            i = j;
+        }
+    return sq >= (double)kDstRangeRows * (double)row_dst.size();
 }
 
 rgnn_status build_host_index(int64_t N, int32_t T, int32_t R, int64_t E, const int32_t *src,
@@ -440,13 +460,13 @@ rgnn_status build_host_index(int64_t N, int32_t T, int32_t R, int64_t E, const i
             const int64_t total = type_ptr[t]->back();
             const int rows[2] = {tile_rows_for(total, kGemmTilesWanted, kGemmTileRows),
                                  tile_rows_for(total, kGemmTilesWantedWide, kGemmTileRows)};
-            for (int w = 0; w < (rows[1] != rows[0] ? 2 : 1); ++w) {
-                if (t == kRowsVsegsDst)
-                    build_tiles_dst_ranges(x.rel_vsegptr, x.vsegdst_byrel, rows[w], rows[w], x.gemm_tiles[t][w]);
-                else
-                    build_tiles(*type_ptr[t], rows[w], x.gemm_tiles[t][w]);
-                g->n_gemm_tiles[t][w] = (int64_t)x.gemm_tiles[t][w].size();
+            if (t == kRowsVsegsDst) {   // the narrow shapes of large graphs; else gemm_tiles() gives kRowsVsegs
+                if (rows[0] < kGemmTileRows || !dst_ranges_pay(x.rel_vsegptr, x.vsegdst_byrel, kGemmTileRows)) continue;
+                build_tiles_dst_ranges(x.rel_vsegptr, x.vsegdst_byrel, kGemmTileRows, kGemmTileRows, x.gemm_tiles[t][0]);
             }
+            for (int w = 0; w < (rows[1] != rows[0] ? 2 : 1) && t != kRowsVsegsDst; ++w)
+                build_tiles(*type_ptr[t], rows[w], x.gemm_tiles[t][w]);
+            for (int w = 0; w < 2; ++w) g->n_gemm_tiles[t][w] = (int64_t)x.gemm_tiles[t][w].size();
         }
         auto outer_rows = [](int64_t rows) { return tile_rows_for(rows, kOuterChunksWanted, kOuterRows); };
         build_tiles(x.rel_vsegptr, outer_rows(g->V), x.tiles_outer);

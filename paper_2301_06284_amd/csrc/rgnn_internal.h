@@ -65,6 +65,18 @@ constexpr int64_t kPairChunksWanted = 2048;
 constexpr int64_t kItemsWanted = 12288;
 constexpr int64_t kMinBundleEdges = 16;
 
+// The segment GEMMs of HGT (queries, dP) take their tiles by destination range
+// where a row's run (one relation, one range of 512 destinations) has at least this
+// many rows on average, on graphs with full-sized tiles and narrow weights.  HGT
+// backward, ms by range / by relation: d = 64, 950 000 typed nodes, runs of 207 rows
+// 3.96 / 3.98; 200 000 nodes, 7, 12, 20, 40, 96 relations, runs of 337, 238, 161,
+// 88, 39: 1.348 / 1.354, 1.548 / 1.547, 1.697 / 1.684, 1.88 / 1.82, 2.09 / 1.91;
+// 300 000 nodes, 535 relations 3.86 / 2.03.  With 128 x 128 weights 9.60 / 9.38 on
+// the first and 12.7 / 4.28 on the last; on graphs of 10 000 to 100 000 nodes, whose
+// rows stay in L2 either way, by relation was never slower (mag-like 12 000 nodes
+// 148.9 / 142.4 us, 20 000 nodes and 100 relations 385 / 327).
+constexpr int kDstRangeRows = 192;
+
 struct Tile {          // one typed-GEMM tile: rows [row0, row0 + rows) of type `type`
     int32_t type, row0, rows, pad;
 };
@@ -223,10 +235,14 @@ struct rgnn_graph {
     rgnn::HostIndex host;
     rgnn::DeviceIndex dev;
 
+    // kRowsVsegsDst: by destination range where the graph has that table (narrow
+    // shapes), else by relation
     rgnn::TileTable gemm_tiles(rgnn::GemmRows r) const
     {
-        const int w = n_gemm_tiles[r][1] ? 1 : 0;
-        return {dev.gemm_tiles[r][0], n_gemm_tiles[r][0], dev.gemm_tiles[r][w], n_gemm_tiles[r][w]};
+        const rgnn::GemmRows b = r == rgnn::kRowsVsegsDst ? rgnn::kRowsVsegs : r;
+        const rgnn::GemmRows a = n_gemm_tiles[r][0] ? r : b;
+        const int w = n_gemm_tiles[b][1] ? 1 : 0;
+        return {dev.gemm_tiles[a][0], n_gemm_tiles[a][0], dev.gemm_tiles[b][w], n_gemm_tiles[b][w]};
     }
     rgnn::TileTable fused_tiles() const
     {

@@ -15,6 +15,8 @@
 //                      write its info and every exported index array to <out>
 //   errors             invalid inputs -> the documented status codes
 //   tiles              the tile count of one type at the ends of its range
+//   tables <in>        the typed-GEMM tile tables of the graph described by <in>:
+//                      every row in one tile of its type, and the tile counts
 //   nomem <in>         fail the k-th allocation of a graph creation, for every
 //                      k until a creation runs without failure
 #include <cstdint>
@@ -218,6 +220,51 @@ static int mode_tiles()
     return 0;
 }
 
+// Rows covered by the tiles of a table, which must lie within one type each.
+static bool covers(const std::vector<rgnn::Tile> &tiles, const std::vector<int32_t> &type_ptr)
+{
+    std::vector<char> seen((size_t)type_ptr.back(), 0);
+    for (const rgnn::Tile &t : tiles) {
+        if (t.rows == 0) continue;
+        if (t.rows < 0 || t.rows > rgnn::kGemmTileRows || t.type < 0 || t.type + 1 >= (int32_t)type_ptr.size() ||
+            t.row0 < type_ptr[t.type] || t.row0 + t.rows > type_ptr[t.type + 1])
+            return false;
+        for (int32_t r = t.row0; r < t.row0 + t.rows; ++r)
+            if (seen[(size_t)r]++) return false;
+    }
+    for (char c : seen)
+        if (!c) return false;
+    return true;
+}
+
+static int mode_tables(const char *in)
+{
+    GraphIn gi;
+    if (!read_graph(in, gi)) { std::fprintf(stderr, "cannot read %s\n", in); return 2; }
+    rgnn_graph_t *G = nullptr;
+    if (create(gi, &G) != RGNN_OK) return 3;
+    const rgnn::HostIndex &x = G->host;
+    const std::vector<int32_t> all{0, (int32_t)gi.N};
+    const std::vector<int32_t> *ptr[rgnn::kNumGemmRows] = {&x.uniq_rel_ptr, &x.rel_vsegptr, &x.rel_vsegptr,
+                                                           &x.ntype_ptr, &all};
+    const char *name[rgnn::kNumGemmRows] = {"pairs", "vsegs", "vsegs_dst", "nodes", "all"};
+    int rc = 0;
+    for (int t = 0; t < rgnn::kNumGemmRows; ++t) {
+        for (int w = 0; w < 2; ++w) {
+            const auto &tt = x.gemm_tiles[t][w];
+            if ((int64_t)tt.size() != G->n_gemm_tiles[t][w] || (!tt.empty() && !covers(tt, *ptr[t]))) {
+                std::printf("FAIL table %s %d\n", name[t], w);
+                rc = 1;
+            }
+        }
+        const rgnn::TileTable u = G->gemm_tiles((rgnn::GemmRows)t);
+        std::printf("%s %lld %lld %lld\n", name[t], (long long)ptr[t]->back(), (long long)u.n_narrow, (long long)u.n_wide);
+    }
+    std::printf("own_dst_ranges %d\n", (int)(G->n_gemm_tiles[rgnn::kRowsVsegsDst][0] > 0));
+    rgnn_graph_destroy(G);
+    return rc;
+}
+
 static int mode_nomem(const char *in)
 {
     GraphIn g;
@@ -251,7 +298,8 @@ int main(int argc, char **argv)
     if (argc >= 4 && !std::strcmp(argv[1], "index")) return mode_index(argv[2], argv[3]);
     if (argc >= 2 && !std::strcmp(argv[1], "errors")) return mode_errors();
     if (argc >= 2 && !std::strcmp(argv[1], "tiles")) return mode_tiles();
+    if (argc >= 3 && !std::strcmp(argv[1], "tables")) return mode_tables(argv[2]);
     if (argc >= 3 && !std::strcmp(argv[1], "nomem")) return mode_nomem(argv[2]);
-    std::fprintf(stderr, "usage: %s index <in> <out> | errors | tiles | nomem <in>\n", argv[0]);
+    std::fprintf(stderr, "usage: %s index <in> <out> | errors | tiles | tables <in> | nomem <in>\n", argv[0]);
     return 2;
 }

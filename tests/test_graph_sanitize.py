@@ -117,6 +117,31 @@ def test_tile_counts_under_sanitizers(exe):
     assert rc == 0 and "ok tile counts" in log, log
 
 
+@pytest.mark.parametrize("N,E,R,dst_ranges", [(0, 0, 3, False), (40, 0, 3, False), (200, 3000, 5, False),
+                                              (10000, 80000, 40, False), (60000, 300000, 300, False),
+                                              (110000, 500000, 40, False), (110000, 800000, 7, True)])
+def test_gemm_tables_under_sanitizers(exe, tmp_path, N, E, R, dst_ranges):
+    """Every typed-GEMM table covers its rows once, within their types, and has
+    about as many tiles as the rule wants (768 narrow, 256 wide, at most 512 rows
+    each, one partial tile per type) however many relations the graph has; tiles by
+    destination range only where the runs are long."""
+    rng = np.random.default_rng(R)
+    g = dict(N=N, E=E, R=R, T=2, src=rng.integers(0, max(N, 1), E, dtype=np.int32),
+             dst=rng.integers(0, max(N, 1), E, dtype=np.int32), rel=rng.integers(0, R, E, dtype=np.int32),
+             ntype=rng.integers(0, 2, N, dtype=np.int32))
+    inp = str(tmp_path / "g.bin")
+    write_graph(inp, g)
+    rc, log = run(exe, "tables", inp)
+    assert rc == 0 and "FAIL" not in log, log
+    lines = [ln.split() for ln in log.splitlines() if not ln.startswith("own")]
+    assert [ln[0] for ln in lines] == ["pairs", "vsegs", "vsegs_dst", "nodes", "all"], log
+    assert ("own_dst_ranges 1" in log) == dst_ranges, log
+    for name, rows, narrow, wide in lines:
+        per = 192 if name == "vsegs_dst" and dst_ranges else 512
+        assert int(narrow) <= 768 + int(rows) / per + R, log
+        assert int(wide) <= 256 + int(rows) / 512 + R, log
+
+
 @pytest.mark.parametrize("kind,csr", [("hub", False), ("dups", True)])
 def test_allocation_failure_enomem_no_leak(exe, tmp_path, kind, csr):
     """Every host allocation of a graph creation is failed in turn: each
