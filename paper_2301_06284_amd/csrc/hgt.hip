@@ -42,16 +42,6 @@ __device__ __forceinline__ float4 zero4() { return make_float4(0.f, 0.f, 0.f, 0.
 constexpr int kE = kChunkEdges, kDst = kMaxDstPerItem;
 constexpr int kU = 2;                    // gathered K|V rows per batch
 
-// Threads per workgroup: a group of D/4 lanes per work item, the weights staged
-// once per workgroup.  512 at d <= 64 with heads of 16 (two workgroups per CU: a
-// finer grid than one of 1024 at the same occupancy; 1.9M nodes, d = 64, 4 heads:
-// 1.96 -> 1.91 ms, 85 000 nodes 0.132 -> 0.118, 256 threads 2.12 and 0.116; at d
-// = 32 the 128 item stages of 1024 threads would not fit in LDS), 1024 where the
-// matrices take most of the LDS (d = 64, 2 heads of 32: 2.43 ms against 3.41 with
-// 512 threads).
-template <int D, int H>
-constexpr int hgt_threads() { return D <= 64 && D / H <= 16 ? 512 : 1024; }
-
 template <bool FQ>
 struct HStage {
     int eidx[kE];          // source node of each edge
@@ -111,11 +101,11 @@ __device__ __forceinline__ float4 head_vecmat(float4 x, const float *Mt, int gl)
 // is formed in the kernel at the segment's first edge from LDS-resident
 // blocks (requires LDSW), with the next segment's Q row already in flight,
 // instead of being read from a materialized [V, d] array.
-template <int D, int H, bool LDSW, bool FQ>
-__global__ __launch_bounds__((hgt_threads<D, H>())) void hgt_kernel(HK k)
+template <int D, int H, bool LDSW, bool FQ, int kBlock>
+__global__ __launch_bounds__(kBlock) void hgt_kernel(HK k)
 {
     static_assert(!FQ || LDSW, "kernel-formed queries keep both weight sets in LDS");
-    constexpr int kBlock = hgt_threads<D, H>(), G = D / 4, GPB = kBlock / G;
+    constexpr int G = D / 4, GPB = kBlock / G;
     constexpr int DK = D / H, LH = DK / 4;
     constexpr int MAT = H * DK * DK;            // floats per relation per matrix
     extern __shared__ float4 smem4[];
@@ -438,17 +428,41 @@ __global__ __launch_bounds__(256) void hgt_msgT_weights_kernel(const float *Wmsg
     if (idx < (int64_t)R * D * D) Wmt[idx] = hgt_msgT_entry(idx, Wmsg, D, heads);
 }
 
-template <int D, int H, bool FQ>
-size_t stage_bytes() { return (size_t)(hgt_threads<D, H>() / (D / 4)) * sizeof(HStage<FQ>); }
+constexpr size_t kLds = 160 * 1024;   // of a CU
 
-size_t weight_bytes(int D, int R, int heads)
+constexpr size_t weight_bytes(int D, int R, int heads)
 {
-    const int dk = D / heads;
-    return (size_t)R * heads * dk * dk * sizeof(float);
+    return (size_t)R * heads * (D / heads) * (D / heads) * sizeof(float);
 }
 
-// Wqp[r][j][n] = mu[r] * scale * Watt[r, i][n - i dk][j - i dk] when j and n
-// both fall in head i's columns, else 0.
+template <int D, bool FQ>
+constexpr size_t stage_bytes(int threads) { return (size_t)(threads / (D / 4)) * sizeof(HStage<FQ>); }
+
+// Threads per workgroup of the traversal, which stages the weights once per
+// workgroup.  1024 where the matrices take most of the LDS (d = 64, 2 heads of 32:
+// 2.43 ms against 3.41 with 512), 512 at d = 32, whose 128 item stages of 1024
+// threads would not fit.  With d = 64 and heads of 16 two workgroups of 512 are a
+// finer grid than one of 1024 at the same occupancy (7 relations, 1.9M nodes: 1.96
+// -> 1.91 ms, 85 000 nodes 0.132 -> 0.118; 256 threads 2.12 and 0.116) as long as
+// both keep their matrices in LDS, up to 12 relations; from 13 on one of 512 would
+// leave the CU half empty where one of 1024 fits, up to 25; one of 512 with its
+// matrices in LDS beats reading them from L2, up to 32; beyond that the stages are
+// all the LDS it takes.  Forward on 200 000 nodes, 1.5M edges, us, 1024 / 512
+// threads: 12 relations 437 / 428, 13 443 / 478, 20 475 / 507, 25 493 / 523, 26
+// (1024: matrices from L2) 657 / 526, 32 676 / 541, 40 700 / 693.
+template <int D, int H>
+constexpr int traverse_threads(int R)
+{
+    if (D == 32) return 512;
+    if (D / H > 16 || D == 128) return 1024;
+    const size_t wb = weight_bytes(D, R, H);
+    const bool two = 2 * (stage_bytes<D, false>(512) + wb) <= kLds;
+    return !two && stage_bytes<D, false>(1024) + wb <= kLds ? 1024 : 512;
+}
+static_assert(traverse_threads<64, 4>(12) == 512 && traverse_threads<64, 4>(13) == 1024 &&
+                  traverse_threads<64, 4>(25) == 1024 && traverse_threads<64, 4>(26) == 512,
+              "the comment above has the relation counts");
+
 __global__ void hgt_qp_weights_kernel(const float *Watt, const float *mu, float scale, int R, int D,
                                       int heads, float *Wqp)
 {
@@ -472,34 +486,44 @@ __global__ __launch_bounds__(256) void hgt_qp_fold_kernel(const float *Wq, const
 
 // whether the traversal's workgroups hold every relation's Wmsg
 template <int D, int H>
-bool wmsg_in_lds(int R) { return weight_bytes(D, R, H) + stage_bytes<D, H, false>() <= 160 * 1024; }
+bool wmsg_in_lds(int R) { return weight_bytes(D, R, H) + stage_bytes<D, false>(traverse_threads<D, H>(R)) <= kLds; }
 
-template <int D, int H>
-hipError_t launch_hgt_shape(const HK &k, int64_t n_items, int R, hipStream_t s)
+template <int D, int H, int NTH>
+hipError_t launch_hgt_threads(const HK &k, int64_t n_items, int R, hipStream_t s)
 {
     const size_t wb = weight_bytes(D, R, H);
-    constexpr int NTH = hgt_threads<D, H>(), GPB = NTH / (D / 4);
+    constexpr int GPB = NTH / (D / 4);
     const unsigned nb = (unsigned)((n_items + GPB - 1) / GPB);
     hipError_t e;
 #define HGT_LAUNCH(LDSW, FQ, LDS)                                                                          \
     do {                                                                                                   \
-        e = hipFuncSetAttribute((const void *)hgt_kernel<D, H, LDSW, FQ>,                                  \
+        e = hipFuncSetAttribute((const void *)hgt_kernel<D, H, LDSW, FQ, NTH>,                             \
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)(LDS));                   \
         if (e == hipSuccess)                                                                               \
-            hipLaunchKernelGGL((hgt_kernel<D, H, LDSW, FQ>), dim3(nb), dim3(NTH), (LDS), s, k);            \
+            hipLaunchKernelGGL((hgt_kernel<D, H, LDSW, FQ, NTH>), dim3(nb), dim3(NTH), (LDS), s, k);       \
     } while (0)
     if (!k.QP) {   // queries formed in the kernel (the caller checked that both weight sets fit)
-        if constexpr (D == 128) HGT_LAUNCH(true, true, (stage_bytes<D, H, true>() + 2 * wb));
+        if constexpr (D == 128) HGT_LAUNCH(true, true, (stage_bytes<D, true>(NTH) + 2 * wb));
         else e = hipErrorInvalidValue;
     } else if (wmsg_in_lds<D, H>(R)) {
-        HGT_LAUNCH(true, false, (stage_bytes<D, H, false>() + wb));
-    } else if constexpr (D / H < 32) {   // wide heads with more matrices take the segment GEMM
-        HGT_LAUNCH(false, false, (stage_bytes<D, H, false>()));
+        HGT_LAUNCH(true, false, (stage_bytes<D, false>(NTH) + wb));
+    } else if constexpr (D / H < 32 && NTH == traverse_threads<D, H>(1 << 16)) {
+        HGT_LAUNCH(false, false, (stage_bytes<D, false>(NTH)));   // (wide heads with more matrices take the segment GEMM)
     } else {
         e = hipErrorInvalidValue;
     }
 #undef HGT_LAUNCH
     return e;
+}
+
+template <int D, int H>
+hipError_t launch_hgt_shape(const HK &k, int64_t n_items, int R, hipStream_t s)
+{
+    if constexpr (D == 64 && D / H == 16)
+        return traverse_threads<D, H>(R) == 512 ? launch_hgt_threads<D, H, 512>(k, n_items, R, s)
+                                                : launch_hgt_threads<D, H, 1024>(k, n_items, R, s);
+    else
+        return launch_hgt_threads<D, H, traverse_threads<D, H>(1)>(k, n_items, R, s);
 }
 
 }  // namespace
@@ -639,8 +663,7 @@ bool hgt_fused_query_fits(int R, int d, int heads)
     // instantiated at d = 128 only, the width where it beats the segment-query
     // GEMM, and not for wide heads, whose traversal has no weights in LDS
     if (d != 128 || hgt_seg_values(R, d, heads)) return false;
-    const size_t st = heads == 8 ? stage_bytes<128, 8, true>() : stage_bytes<128, 4, true>();
-    return st + 2 * weight_bytes(d, R, heads) <= 160 * 1024;
+    return stage_bytes<128, true>(1024) + 2 * weight_bytes(d, R, heads) <= kLds;
 }
 
 rgnn_status launch_hgt_qp_weights(const float *Watt, const float *mu, float scale, int R, int d,

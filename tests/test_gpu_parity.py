@@ -1075,3 +1075,19 @@ def test_hgt_backward_unused_weights(d, heads, flags):
                 continue
             rows = used if k in ("dWatt", "dmu") else slice(None)   # those scale with the weights themselves
             np.testing.assert_array_equal(a[k][rows], b[k][rows], err_msg=k)
+
+
+@pytest.mark.parametrize("kind", ["hub", "typedhub"])
+@pytest.mark.parametrize("R", [12, 13, 25, 26, 32, 33])
+def test_hgt_traversal_threads(R, kind):
+    """Relation counts at which the d = 64 traversal with heads of 16 changes its
+    workgroup (two of 512 threads, one of 1024, one of 512, matrices from L2)."""
+    g = graph(kind, seed=95, N=500, E=9000, R=R, T=2)
+    t = workloads.tiny_tensors(95, g, 64, 64, heads=4)
+    print(f"hgt traversal threads R={R} {kind}", flush=True)
+    run = Runner(g, t)
+    got, saved = run.hgt(4, 0.25, want_saved=True)
+    run.close()
+    args = [t[k] for k in ("h", "Wk", "Wq", "Wv", "Wa", "Watt", "Wmsg", "mu")]
+    assert row_err(got, oracle.hgt_forward(g, *args, heads=4, att_scale=0.25)) <= TOL
+    assert np.isfinite(saved.cpu().numpy()).all()
