@@ -651,9 +651,15 @@ extern "C" rgnn_status hgt_forward(const rgnn_graph_t *g, const float *h, const 
     }
     ha.heads = heads; ha.d = d; ha.agg = w.agg; ha.partial = w.partial; ha.saved = saved;
     ha.Sv = w.Sv; ha.stat = w.stat; ha.Wt = w.Wqp; ha.T = w.QP;   // both free after the traversal
-    if (hgt_seg_values(g->R, d, heads) && (!(flags & RGNN_FLAG_A_LINEAR) || (heads == 1 && g->rel_dst_typed))) {
-        // the reduction of the segment rows is the layer's output: one head and
-        // typed relations take Wa into the message weights
+    // one head and typed relations take Wa into the message weights: R d^3
+    // multiply-adds on the vector units instead of a GEMM over the nodes.  us per
+    // forward of one-type graphs with 6.5 N edges, folded / not:
+    //   N = 3 000   d = 64, R = 40 52 / 57,   R = 150 74 / 72;   d = 128, R = 40 121 / 117
+    //   N = 50 000  d = 128, R = 40 389 / 405,  R = 150 576 / 543
+    //   N = 200 000 d = 128, R = 150 1531 / 1539,  R = 535 2155 / 2025
+    const bool fold_wa = heads == 1 && g->rel_dst_typed && (int64_t)g->R * d * d <= 450000 + 14 * g->N;
+    if (hgt_seg_values(g->R, d, heads) && (!(flags & RGNN_FLAG_A_LINEAR) || fold_wa)) {
+        // the reduction of the segment rows is the layer's output
         ha.fold_out = (flags & RGNN_FLAG_A_LINEAR) != 0;
         ha.Wa = Wa;
         ha.residual = (flags & RGNN_FLAG_RESIDUAL) ? h : nullptr;

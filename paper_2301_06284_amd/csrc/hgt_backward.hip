@@ -32,7 +32,8 @@
 // gradients by typed GEMMs and outer-product chunks.
 //
 // With typed relations (every relation's destinations of one node type, the
-// case of heterogeneous graphs) the node-type weights Wq and Wa are folded into
+// case of heterogeneous graphs) and not too many of them for the graph's size
+// (fold_types) the node-type weights Wq and Wa are folded into
 // the per-relation ones instead (see "typed relations" below): no Q, dagg,
 // rebuilt aggregate or dQ, and two outer products over all nodes fewer.
 // 950 000 nodes, 10.5M edges, d = 64, 4 heads: 5.11 -> 4.28 ms.
@@ -592,6 +593,21 @@ struct HgtBwdWs {
 
 // the forward forms its segment queries from Q inside the traversal
 bool forward_queries_in_kernel(const rgnn_graph *g, int D, int H) { return D == 128 && hgt_fused_query_fits(g->R, D, H); }
+// Whether the node-type weights are folded into the per-relation ones (typed
+// relations only).  The folded weights and the weight gradients that follow from
+// P1 and P2 are products of about R D^2 dk terms each on the vector units, against
+// the general path's passes over the nodes (N D^2 on the matrix cores and N D
+// values written and read several times), so the line lies at R dk against N, with
+// the constant that the general path's seven more launches are worth.  Backward of
+// one-type graphs with 6.5 N edges, us, folded / general:
+//   N = 3 000    R dk = 2 400 (d = 64, dk = 16)  146 / 163,   4 800 (128, 32)   393 / 343
+//   N = 12 000   R dk = 5 120 (128, 128)         502 / 533,   8 560 (128, 16)   852 / 754
+//   N = 50 000   R dk = 9 600 (64, 64)           598 / 642,   17 120 (128, 32) 1960 / 1775
+//   N = 200 000  R dk = 34 240 (64, 64)         2166 / 2209,  68 480 (128, 128) 6619 / 5484
+bool fold_types(const rgnn_graph *g, int D, int H)
+{
+    return g->rel_dst_typed && (int64_t)g->R * (D / H) <= 4000 + g->N * 3 / 16;
+}
 // 256-entry blocks of a relation's head blocks
 constexpr int rel_blocks(int D, int H) { return (H * (D / H) * (D / H) + 255) / 256; }
 
@@ -608,7 +624,7 @@ size_t hgt_bwd_layout(const rgnn_graph *g, int D, int H, void *base, HgtBwdWs *w
     const size_t slots = (size_t)g->n_slots;
     const size_t nchunks = (size_t)std::max<int64_t>(std::max(g->n_tiles_outer, g->n_tiles_types_outer), 1);
     HgtBwdWs x{};
-    const bool typed = g->rel_dst_typed;
+    const bool typed = fold_types(g, D, H);   // as hgt_backward_d
     x.KV = take(N * 2 * D); x.Q = take(typed && !forward_queries_in_kernel(g, D, H) ? 0 : N * D);
     x.Wqp = take(R * D * D); x.QD = take(V * 2 * D);
     x.agg = take(N * D); x.partial = take(slots * (2 * H + D)); x.saved = take(N * H * 2);
@@ -661,7 +677,7 @@ rgnn_status hgt_backward_d(const rgnn_graph *g, const float *h, const float *Wk,
 {
     constexpr int G = D / 4, GPB = 256 / G;
     const bool a_linear = (flags & RGNN_FLAG_A_LINEAR) != 0;
-    const bool typed = g->rel_dst_typed;
+    const bool typed = fold_types(g, D, H);
     HgtBwdWs w;
     hgt_bwd_layout(g, D, H, ws, &w);
     rgnn_status st;
@@ -670,16 +686,18 @@ rgnn_status hgt_backward_d(const rgnn_graph *g, const float *h, const float *Wk,
     //      forward's statistics, the traversal that yields them and agg
     const float *stats = saved ? saved : w.saved;
     // the segment queries exactly as the forward forms them (with the query
-    // projection folded into the per-relation weight when the relations
-    // are typed), so that the recomputed scores match its statistics
-    const bool fold_q = typed && !forward_queries_in_kernel(g, D, H);
+    // projection folded into the per-relation weight when the relations are
+    // typed, whether or not the rest is), so that the recomputed scores match its
+    // statistics
+    const bool fold_q = g->rel_dst_typed && !forward_queries_in_kernel(g, D, H);
+    const bool need_q = !fold_q || !typed;
     {
         GemmArgs ga;
         ga.split_bf16 = 1;
         ga.X = h; ga.ldx = D; ga.gather = g->dev.ntype_perm; ga.scatter = g->dev.ntype_perm;
         ga.K = D;
         ga.tiles = g->gemm_tiles(kRowsNodes);
-        if (D == 64 && fold_q) {   // K | V in one GEMM
+        if (D == 64 && !need_q) {   // K | V in one GEMM
             ga.W[0] = Wk; ga.W[1] = Wv; ga.nparts = 2;
             ga.Nc = 2 * D;
             ga.Y = w.KV; ga.ldy = 2 * D;
@@ -695,13 +713,16 @@ rgnn_status hgt_backward_d(const rgnn_graph *g, const float *h, const float *Wk,
             const float *Wp[3] = {Wk, Wv, Wq};
             float *Yp[3] = {w.KV, w.KV + D, w.Q};
             const int64_t ld[3] = {2 * D, 2 * D, D};
-            for (int p = 0; p < (fold_q ? 2 : 3); ++p) {
+            for (int p = 0; p < (need_q ? 3 : 2); ++p) {
                 ga.W[0] = Wp[p]; ga.Y = Yp[p]; ga.ldy = ld[p];
                 if ((st = launch_typed_gemm(ga, s)) != RGNN_OK) return st;
             }
         }
     }
-    if (!fold_q && (st = launch_hgt_qp_weights(Watt, mu, att_scale, g->R, D, H, w.Wqp, s)) != RGNN_OK) return st;
+    if (need_q && (st = launch_hgt_qp_weights(Watt, mu, att_scale, g->R, D, H, w.Wqp, s)) != RGNN_OK) return st;
+    if (fold_q && !typed &&
+        (st = launch_hgt_qp_fold(Wq, Watt, mu, att_scale, g->dev.rel_dsttype, g->R, D, H, w.Wf, s)) != RGNN_OK)
+        return st;
     const bool fold_a = typed && a_linear;
     if (typed) {
         const unsigned nr = blocks_for((int64_t)g->R * D * D, 256);

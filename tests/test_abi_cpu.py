@@ -166,3 +166,27 @@ def test_segment_gemm_workspace_grows_with_rows(T):
         rows += [k * 49152 - 1, k * 49152, k * 49152 + 1, k * 49152 + 20000]
     sizes = [rgnn.segment_gemm_workspace_size(m, T) for m in rows + [1000003, 10000000]]
     assert sizes == sorted(sizes)
+
+
+@pytest.mark.parametrize("d,heads", [(32, 2), (64, 4), (128, 1)])
+def test_hgt_backward_folds_by_size(d, heads):
+    """One-type graphs with few relations keep no queries, output gradients or
+    query gradients per node (three [N, d] arrays less); with relations that
+    outweigh the nodes they take the general path's workspace, as mixed
+    destination types do."""
+    rgnn = _rgnn()
+    rng = np.random.default_rng(d)
+    N, E = 2000, 6000
+    ends = [rng.integers(0, N, E, dtype=np.int32) for _ in range(2)]
+    for R, folded in ((5, True), (600, False)):
+        rel = rng.integers(0, R, E, dtype=np.int32)
+        sizes = []
+        for T, ntype in ((1, np.zeros(N, np.int32)), (2, rng.integers(0, 2, N, dtype=np.int32))):
+            g = rgnn.Graph.from_coo(N, T, R, ends[0], ends[1], rel, ntype, host_only=True)
+            sizes.append(rgnn.workspace_size(g, rgnn.LAYER_HGT_BACKWARD, d, d, heads) - T * d * 3 * d * 4)
+            g.close()
+        chunks = 2 * 2 * d * d * 4 * 32 + 4096   # at most one chunk more per node type, and padding
+        if folded:
+            assert sizes[1] - sizes[0] > 2 * N * d * 4
+        else:
+            assert abs(sizes[1] - sizes[0]) <= chunks

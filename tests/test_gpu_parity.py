@@ -1091,3 +1091,26 @@ def test_hgt_traversal_threads(R, kind):
     args = [t[k] for k in ("h", "Wk", "Wq", "Wv", "Wa", "Watt", "Wmsg", "mu")]
     assert row_err(got, oracle.hgt_forward(g, *args, heads=4, att_scale=0.25)) <= TOL
     assert np.isfinite(saved.cpu().numpy()).all()
+
+
+@pytest.mark.parametrize("flags", [0, 2, 4, 6])
+@pytest.mark.parametrize("d,heads,R", [(32, 1, 127), (32, 1, 128), (32, 2, 255), (32, 2, 300), (64, 1, 63), (64, 1, 130),
+                                       (64, 4, 254), (64, 4, 260), (128, 1, 27), (128, 1, 31), (128, 1, 40),
+                                       (128, 4, 127), (128, 4, 130), (128, 8, 254), (128, 8, 260)])
+def test_hgt_folded_weights_rule(d, heads, R, flags):
+    """One-type graphs on both sides of the rules that fold the node-type weights
+    into the per-relation ones (400 nodes: R dk up to 4075 in the backward, R d^2 up
+    to 455 600 for the forward's output linear), many relations without edges."""
+    g = workloads.tiny_graph(97, N=400, E=3000, R=R, T=1, kind="hub")
+    t = workloads.tiny_tensors(97, g, d, d, heads=heads)
+    print(f"hgt folded weights d={d} heads={heads} R={R} flags={flags}", flush=True)
+    args = [t[k] for k in ("h", "Wk", "Wq", "Wv", "Wa", "Watt", "Wmsg", "mu")]
+    opt = dict(heads=heads, att_scale=0.25, residual=bool(flags & 2), a_linear=bool(flags & 4))
+    run = Runner(g, t)
+    out = run.hgt(heads, 0.25, flags=flags)
+    got = [run.hgt_backward(heads, 0.25, flags=flags, use_saved=s) for s in (False, True)]
+    run.close()
+    assert row_err(out, oracle.hgt_forward(g, *args, **opt)) <= TOL
+    ref = oracle.hgt_backward(g, *args, t["grad_out"], **opt)
+    for x in got:
+        check_hgt_grads(x, ref, heads, d)
