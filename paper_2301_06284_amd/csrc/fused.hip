@@ -17,9 +17,9 @@
 // instruction), summed, and moved into the B-operand layout of
 // v_mfma_f32_16x16x4f32 by lane permutes; the products are permuted back to
 // the row layout for the stores.  Because the 16 segments of a block have
-// nearly equal edge counts, the edge loop wastes few lane-steps, and the first
-// gathers of a wave's next block are issued before the current block's
-// transform so that loads stay in flight.
+// nearly equal edge counts, the edge loop wastes few lane-steps.  Except in the
+// 128 x 128 shapes (see the kernel), the first gathers of a wave's next block are
+// issued before the current block's transform so that loads stay in flight.
 //
 // RGAT: per edge the source term h_u . (W_r w_src[r]) (reordered) is summed
 // over the eight lanes of the row; with the segment's destination term it
@@ -61,13 +61,13 @@ struct FK {
 };
 
 // DI: input features, DO: output features, NWAVE: waves per workgroup,
-// KU: edges per gathered batch (two batches in flight).
+// KU: edges per gathered batch, LONG: the 128 x 128 shape for long segments.
 //
 // Gather layout: lane l serves rows l/8 and l/8 + 8 of the 16-row block, and
 // within each the features 32c + 4(l%8) .. +3 (c < DI/32), so one dwordx4
 // load instruction covers whole 128-byte lines of eight rows.  The finished
 // row sums are moved into the MFMA operand layout by lane permutes.
-template <int DI, int DO, int MODE, int NWAVE, int KU, int WPE>
+template <int DI, int DO, int MODE, int NWAVE, int KU, int WPE, bool LONG>
 __global__ __launch_bounds__(64 * NWAVE) __attribute__((amdgpu_waves_per_eu(WPE))) void af_fused_kernel(FK k)
 {
     constexpr int NT = 64 * NWAVE;
@@ -78,14 +78,15 @@ __global__ __launch_bounds__(64 * NWAVE) __attribute__((amdgpu_waves_per_eu(WPE)
     // batch each hide the gathers better than eight with two and the prefetch
     // (150 registers, one workgroup per CU): 440 000 nodes, 2.85M edges, softmax
     // 0.678 -> 0.574 ms, mean 0.676 -> 0.543; twelve waves with both buffers 0.616
-    // and 0.620.  Where nearly every segment has 64 edges only two of a tile's
-    // eight waves have rows and the old shape was the faster one (62 edges per
-    // segment: softmax 0.313 -> 0.346); at 31 edges it no longer was (0.155 ->
-    // 0.144).  The narrower shapes keep both: at 64 x 64 one buffer and six waves per
-    // SIMD gained 2 % on the softmax, lost 5 % on the mean, and the smaller tiles
-    // cost 50 % on long segments.
-    constexpr bool PING = !(wide_shape(DI, DO) && MODE == kModeSoftmax);   // two gather buffers
-    constexpr bool PREF = !(wide_shape(DI, DO) && MODE != kModeSum);       // next block's first batch
+    // and 0.620.  Where nearly every segment has 64 edges, 2048 of them are two
+    // blocks, so two of a tile's eight waves have rows: LONG keeps one workgroup
+    // per CU with both buffers, the prefetch and tiles of 4096 edges
+    // (kFusedLongEdges has the rule and both sides).  The narrower shapes keep
+    // both: at 64 x 64 one buffer and six waves per SIMD gained 2 % on the softmax,
+    // lost 5 % on the mean, and the smaller tiles cost 50 % on long segments.
+    constexpr bool WIDE = wide_shape(DI, DO) && !LONG;
+    constexpr bool PING = !(WIDE && MODE == kModeSoftmax);   // two gather buffers
+    constexpr bool PREF = !(WIDE && MODE != kModeSum);       // next block's first batch
     constexpr int KP = DI + 4;       // padded LDS row (conflict-free b128 reads)
     constexpr int KC = DI / 16;      // MFMA k chunks
     constexpr int CH = DI / 32;      // float4 chunks per lane and gathered row
@@ -93,7 +94,7 @@ __global__ __launch_bounds__(64 * NWAVE) __attribute__((amdgpu_waves_per_eu(WPE)
     constexpr int CBP = 2;           // output column blocks per MFMA pass
     constexpr int NW = DI * DO / 4 / NT;
     constexpr int NR = (kFusedTileRows + NT - 1) / NT;   // segment entries per thread
-    constexpr int TE = wide_shape(DI, DO) ? kFusedTileEdgesWide : kFusedTileEdges;
+    constexpr int TE = WIDE ? kFusedTileEdgesWide : kFusedTileEdges;
     constexpr int NS = (TE + NT - 1) / NT;               // source indices per thread
     static_assert(NW * NT * 4 == DI * DO, "weight tile must split evenly over the workgroup");
     __shared__ float Wt[MODE == kModeSum ? 1 : DO * KP];
@@ -404,7 +405,7 @@ __global__ __launch_bounds__(64 * NWAVE) __attribute__((amdgpu_waves_per_eu(WPE)
     }
 }
 
-template <int DI, int DO, int MODE>
+template <int DI, int DO, int MODE, bool LONG = false>
 void launch_shape(const FK &k, int64_t ntiles, hipStream_t s)
 {
     // d = 128: the 64 KB weight tile is shared by eight waves; one edge per row
@@ -414,29 +415,30 @@ void launch_shape(const FK &k, int64_t ntiles, hipStream_t s)
     // waves per SIMD the LDS allows; the 128 x 64 mean shape gets the register
     // budget of three
     constexpr int WPE = (DI == 128 && DO == 64) ? 3 : 4;
-    hipLaunchKernelGGL((af_fused_kernel<DI, DO, MODE, NWAVE, KU, WPE>), dim3((unsigned)ntiles),
+    hipLaunchKernelGGL((af_fused_kernel<DI, DO, MODE, NWAVE, KU, WPE, LONG>), dim3((unsigned)ntiles),
                        dim3(64 * NWAVE), 0, s, k);
 }
 
 template <int MODE>
-bool dispatch(int di, int dout, const FK &k, int64_t n, hipStream_t s)
+bool dispatch(int di, int dout, bool lng, const FK &k, int64_t n, hipStream_t s)
 {
     if constexpr (MODE == kModeSum) {   // no transform: the output width is d_in
         if (di == 32) launch_shape<32, 32, MODE>(k, n, s);
         else if (di == 64) launch_shape<64, 64, MODE>(k, n, s);
         else if (di == 128) launch_shape<128, 128, MODE>(k, n, s);
         else return false;
-        return true;
-    }
-    if (di == 32 && dout == 32) launch_shape<32, 32, MODE>(k, n, s);
-    else if (di == 64 && dout == 64) launch_shape<64, 64, MODE>(k, n, s);
-    else if (di == 128 && dout == 128) launch_shape<128, 128, MODE>(k, n, s);
-    else if constexpr (MODE == kModeMean) {   // RGCN only: RGAT needs d_in == d_out
-        if (di == 64 && dout == 128) launch_shape<64, 128, MODE>(k, n, s);
-        else if (di == 128 && dout == 64) launch_shape<128, 64, MODE>(k, n, s);
-        else return false;
     } else {
-        return false;
+        if (di == 32 && dout == 32) launch_shape<32, 32, MODE>(k, n, s);
+        else if (di == 64 && dout == 64) launch_shape<64, 64, MODE>(k, n, s);
+        else if (di == 128 && dout == 128 && lng) launch_shape<128, 128, MODE, true>(k, n, s);
+        else if (di == 128 && dout == 128) launch_shape<128, 128, MODE>(k, n, s);
+        else if constexpr (MODE == kModeMean) {   // RGCN only: RGAT needs d_in == d_out
+            if (di == 64 && dout == 128) launch_shape<64, 128, MODE>(k, n, s);
+            else if (di == 128 && dout == 64) launch_shape<128, 64, MODE>(k, n, s);
+            else return false;
+        } else {
+            return false;
+        }
     }
     return true;
 }
@@ -447,7 +449,9 @@ rgnn_status launch_af_fused(const FusedArgs &a, hipStream_t s)
 {
     const rgnn_graph *g = a.g;
     const TileTable tt = g->fused_tiles();
-    const bool wide = wide_shape(a.d_in, a.d_out);
+    // the long-segment variant works on the narrow shapes' tiles
+    const bool lng = g->fused_long && !a.S;
+    const bool wide = wide_shape(a.d_in, a.d_out) && !lng;
     const int64_t ntiles = wide ? tt.n_wide : tt.n_narrow;
     if (ntiles == 0) return RGNN_OK;
     FK k{};
@@ -462,9 +466,9 @@ rgnn_status launch_af_fused(const FusedArgs &a, hipStream_t s)
     bool ok;
     {
         LaunchScope ls(a.softmax ? "rgat_af_fused" : (a.S ? "segment_means" : "rgcn_af_fused"), s);
-        ok = a.softmax ? dispatch<kModeSoftmax>(a.d_in, a.d_out, k, ntiles, s)
-             : a.S     ? dispatch<kModeSum>(a.d_in, a.d_out, k, ntiles, s)
-                       : dispatch<kModeMean>(a.d_in, a.d_out, k, ntiles, s);
+        ok = a.softmax ? dispatch<kModeSoftmax>(a.d_in, a.d_out, lng, k, ntiles, s)
+             : a.S     ? dispatch<kModeSum>(a.d_in, a.d_out, lng, k, ntiles, s)
+                       : dispatch<kModeMean>(a.d_in, a.d_out, lng, k, ntiles, s);
     }
     if (!ok) return fail(RGNN_EUNSUPPORTED, "fused aggregation: unsupported (d_in, d_out)");
     hipError_t e = hipGetLastError();

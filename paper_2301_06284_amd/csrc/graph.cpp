@@ -264,6 +264,7 @@ rgnn_status build_host_index(int64_t N, int32_t T, int32_t R, int64_t E, const i
             x.fused_src.resize((size_t)E);
             x.vseg_fpos.resize((size_t)g->V);
             int32_t fpos = 0;
+            int64_t sq = 0;   // sum over the edges of their segment's length
             for (int64_t i = 0; i < g->V; ++i) {
                 const int32_t vs = fperm[i];
                 const int32_t b = x.vseg_ptr[vs], n = x.vseg_ptr[vs + 1] - b;
@@ -273,7 +274,9 @@ rgnn_status build_host_index(int64_t N, int32_t T, int32_t R, int64_t E, const i
                 x.vseg_fpos[vs] = (int32_t)i;
                 for (int32_t j = 0; j < n; ++j) x.fused_src[(size_t)fpos + j] = x.in_src[(size_t)b + j];
                 fpos += n;
+                sq += (int64_t)n * n;
             }
+            g->fused_long = E > 0 && sq >= kFusedLongEdges * E;
             auto cut = [&](int max_rows, int max_edges, std::vector<Tile> &out) {
                 out.clear();
                 for (int32_t r = 0; r < R; ++r) {

@@ -24,6 +24,12 @@ constexpr int kFusedTileRows = 256;
 constexpr int kFusedTileEdges = 4096;
 // the 128 x 128 tiles' edges, so that two workgroups fit a CU's LDS (fused.hip)
 constexpr int kFusedTileEdgesWide = 2048;
+// A graph whose in-edges lie in virtual segments of at least this many edges (mean
+// over the edges) runs the 128 x 128 fused kernels with full-sized tiles at one
+// workgroup per CU.  RGAT forward, us, 2048 edges and two workgroups / this: mean 32
+// 93 / 114, 41 162 / 179, 49 and 51 109 / 108 and 104 / 104, 58 202 / 177, 60
+// 191 / 181.
+constexpr int kFusedLongEdges = 54;
 // Reductions over more records than this (partials of a split destination,
 // segments of one destination) get a whole workgroup instead of one group.
 constexpr int kBigRange = 32;
@@ -231,6 +237,7 @@ struct rgnn_graph {
     int64_t n_oitems = 0, n_osplit = 0, n_oslots = 0, n_split_items = 0, n_tiles_outer_pairs = 0;
     int64_t n_vpairs = 0, n_tiles_vpairs = 0;
     int64_t n_split_wide = 0, n_osplit_wide = 0;   // split lists' entries with > kWaveSlots slots
+    bool fused_long = false;      // long segments: see kFusedLongEdges
     bool rel_dst_typed = false;   // every relation's destinations share one node type
     rgnn::HostIndex host;
     rgnn::DeviceIndex dev;

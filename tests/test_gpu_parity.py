@@ -1114,3 +1114,27 @@ def test_hgt_folded_weights_rule(d, heads, R, flags):
     ref = oracle.hgt_backward(g, *args, t["grad_out"], **opt)
     for x in got:
         check_hgt_grads(x, ref, heads, d)
+
+
+@pytest.mark.parametrize("per_seg", [53, 54, 64, 200])
+def test_fused_long_segments(per_seg):
+    """Graphs on both sides of the rule for long segments (54 edges on average) at
+    128 x 128: RGCN and both softmaxes aggregate-first, RGCN backward (the segment
+    means keep the short tiles), with relations of 1 to 40 destinations."""
+    rng = np.random.default_rng(per_seg)
+    N, R = 200, 5
+    pairs = [(v, r) for r, n in enumerate((1, 15, 16, 17, 40)) for v in rng.choice(N, n, replace=False)]
+    dst, rel = np.repeat(np.array(pairs), per_seg, axis=0).T
+    mix = rng.permutation(len(dst))
+    g = dict(N=N, E=len(dst), R=R, T=1, src=rng.integers(0, N, len(dst), dtype=np.int32),
+             dst=dst[mix].astype(np.int32), rel=rel[mix].astype(np.int32), ntype=np.zeros(N, np.int32))
+    t = workloads.tiny_tensors(per_seg, g, 128, 128)
+    print(f"fused long segments {per_seg}", flush=True)
+    run = Runner(g, t)
+    assert row_err(run.rgcn(plan=2), oracle.rgcn_forward(g, t["h"], t["W"], t["W0"])) <= TOL
+    for scope in (0, 1):
+        ref = oracle.rgat_forward(g, t["h"], t["W"], t["w_src"], t["w_dst"], scope=scope)
+        assert row_err(run.rgat(plan=2, scope=scope), ref) <= TOL
+    for a, b in zip(run.rgcn_backward(), oracle.rgcn_backward(g, t["h"], t["W"], t["W0"], t["grad_out"])):
+        assert row_err(a.reshape(-1, 128), b.reshape(-1, 128)) <= TOL
+    run.close()
