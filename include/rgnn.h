@@ -324,7 +324,10 @@ rgnn_status hgt_backward(const rgnn_graph_t *g, const float *h, const float *Wk,
  *   X [*, ldx >= K], W [T, K, Nc], Y [*, ldy >= Nc]; gather, scatter: DEVICE
  *   int32 [M] or NULL for the identity.  K in {64, 128}, Nc in {64, 128}, or
  *   K = Nc = 32.
- *   The call only enqueues work (it can be captured in a HIP graph).
+ *   The call only enqueues work, except that with more than 3072 types it copies
+ *   its tile table from the host and waits for the stream.  Under stream capture
+ *   it never does: a HIP graph keeps the type offsets of the captured call
+ *   (type_ptr is read during the call only).
  *   Rows written twice through `scatter` race; the caller avoids that.
  *   Arithmetic: fp32 inputs and outputs with fp32 accuracy.  For K, Nc in
  *   {64, 128} each product is formed from an exact split of both operands into

@@ -5,6 +5,7 @@
 #include <cstdio>
 #include <cstring>
 #include <mutex>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -218,6 +219,45 @@ size_t segment_gemm_need(int64_t M, int32_t T)
 size_t segment_gemm_least(int64_t M, int32_t T)
 {
     return pad256((size_t)segment_tiles_bound(M, T, kGemmTileRows) * sizeof(Tile));
+}
+
+// The segment GEMM's tiles are made on the device up to this many types, 512 types
+// per launch in a row of launches on one workgroup each; beyond, by the host in one
+// copy and a wait, except under capture, which can only take the launches.  us per
+// call, 64 x 64, launches / copy: 2048 types and 20 000 rows 25.5 / 33.0, 4096
+// 45.5 / 40.5, 8192 and 100 000 rows 91 / 62, 100 000 types and 200 000 rows
+// 1050 / 424.
+constexpr int32_t kTypesOnDevice = 3072;
+
+// whether s takes part in a stream capture (or cannot say)
+bool capturing(hipStream_t s)
+{
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cs) == hipSuccess) return cs != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
+
+// Writes the table by the host; false without enqueueing anything when host memory
+// runs out.
+bool upload_segment_tiles(const int64_t *type_ptr, int32_t ntypes, int rows, Tile *dst, int64_t *ntiles,
+                          hipStream_t s, hipError_t *err)
+{
+    std::vector<Tile> tiles;
+    try {
+        int64_t n = 0;
+        for (int32_t t = 0; t < ntypes; ++t) n += tile_count((int32_t)(type_ptr[t + 1] - type_ptr[t]), rows);
+        tiles.reserve((size_t)n);
+    } catch (const std::bad_alloc &) {
+        return false;
+    }
+    for (int32_t t = 0; t < ntypes; ++t)
+        for (int64_t r0 = type_ptr[t]; r0 < type_ptr[t + 1]; r0 += rows)
+            tiles.push_back(Tile{t, (int32_t)r0, (int32_t)std::min<int64_t>(rows, type_ptr[t + 1] - r0), 0});
+    *ntiles = (int64_t)tiles.size();
+    *err = hipMemcpyAsync(dst, tiles.data(), tiles.size() * sizeof(Tile), hipMemcpyHostToDevice, s);
+    if (*err == hipSuccess) *err = hipStreamSynchronize(s);   // tiles outlives its copy
+    return true;
 }
 
 }  // namespace
@@ -795,7 +835,12 @@ extern "C" rgnn_status rgnn_segment_gemm(const float *X, int64_t ldx, const int3
     int rows = tile_rows_for(M, want, kGemmTileRows);
     while (rows < kGemmTileRows && segment_tiles_bound(M, num_types, rows) * sizeof(Tile) > ws_bytes) rows += 64;
     int64_t ntiles = 0;
-    rgnn_status st = launch_segment_tiles(type_ptr, num_types, rows, dt, &ntiles, s);
+    rgnn_status st = RGNN_OK;
+    hipError_t e = hipSuccess;
+    if (num_types <= kTypesOnDevice || capturing(s) ||
+        !upload_segment_tiles(type_ptr, num_types, rows, dt, &ntiles, s, &e))
+        st = launch_segment_tiles(type_ptr, num_types, rows, dt, &ntiles, s);
+    if (e != hipSuccess) return hip_fail(e, "tile table upload");
     if (st != RGNN_OK) return st;
     GemmArgs ga;
     ga.split_bf16 = 1;

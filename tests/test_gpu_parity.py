@@ -1138,3 +1138,42 @@ def test_fused_long_segments(per_seg):
     for a, b in zip(run.rgcn_backward(), oracle.rgcn_backward(g, t["h"], t["W"], t["W0"], t["grad_out"])):
         assert row_err(a.reshape(-1, 128), b.reshape(-1, 128)) <= TOL
     run.close()
+
+
+@pytest.mark.parametrize("T", [3072, 3073, 9000])
+def test_segment_gemm_thousands_of_types(T):
+    """Type counts on both sides of the host-made tile table, with empty types and
+    some of several tiles: eagerly, and captured (where the table is made on the
+    device) and replayed with new inputs between eager calls."""
+    import torch
+    from paper_2301_06284_amd import rgnn
+    rng = np.random.default_rng(T)
+    counts = rng.choice([0, 1, 3, 65, 200], T, p=[.5, .3, .15, .04, .01])
+    type_ptr = np.concatenate([[0], np.cumsum(counts)]).astype(np.int64)
+    M = int(type_ptr[-1])
+    print(f"segment_gemm thousands of types T={T} M={M}", flush=True)
+    dev = torch.device("cuda:0")
+    W = torch.from_numpy(rng.standard_normal((T, 64, 64)).astype(np.float32)).to(dev)
+    X, Y = torch.empty(M, 64, device=dev), torch.empty(M, 64, device=dev)
+    ws = torch.empty(rgnn.segment_gemm_workspace_size(M, T), dtype=torch.uint8, device=dev)
+    seg = torch.from_numpy(np.repeat(np.arange(T), counts)).to(dev)
+
+    def check(call):
+        X.copy_(torch.from_numpy(rng.standard_normal((M, 64)).astype(np.float32)))
+        Y.fill_(float("nan"))
+        call()
+        torch.cuda.synchronize()
+        for lo in range(0, M, 4096):   # the rows' own weights, in double precision
+            x, w = X[lo:lo + 4096].double(), W[seg[lo:lo + 4096]].double()
+            ref = (x[:, :, None] * w).sum(1)
+            assert row_err(Y[lo:lo + 4096].cpu().numpy(), ref.cpu().numpy()) <= TOL
+
+    def call():
+        rgnn.segment_gemm(X, None, type_ptr, W, Y, None, ws, 64, 64)
+    check(call)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        call()
+    for _ in range(3):
+        check(g.replay)
+        check(call)
