@@ -309,10 +309,11 @@ rgnn_status build_host_index(int64_t N, int32_t T, int32_t R, int64_t E, const i
         int32_t slots = 0;
         int64_t v = 0;
         auto deg = [&](int64_t u) { return x.rowptr[u + 1] - x.rowptr[u]; };
-        // edges and destinations (sources) of a bundle: fewer on small graphs,
-        // so that the items still fill the chip
+        // edges and destinations (sources) of a bundle: fewer on small graphs, so
+        // that the items still fill the chip; destinations by the nodes too, of which
+        // a graph with far fewer edges than nodes has enough for its items
         const int64_t be = std::min<int64_t>(C, std::max<int64_t>(kMinBundleEdges, (E / kItemsWanted + 7) / 8 * 8));
-        const int64_t bd = be * kMaxDstPerItem / C;
+        const int64_t bd = std::min<int64_t>(kMaxDstPerItem, std::max<int64_t>(be * kMaxDstPerItem / C, N / kItemsWanted));
         while (v < N) {
             if (deg(v) > C) {
                 int32_t s = x.dst_vsegptr[v];

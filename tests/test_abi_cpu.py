@@ -190,3 +190,21 @@ def test_hgt_backward_folds_by_size(d, heads):
             assert sizes[1] - sizes[0] > 2 * N * d * 4
         else:
             assert abs(sizes[1] - sizes[0]) <= chunks
+
+
+@pytest.mark.parametrize("N,E", [(500000, 1000), (500000, 200000), (1000000, 40000), (3000, 50), (100000, 900000)])
+def test_work_items_of_sparse_graphs(N, E):
+    """Work items follow the edges and the nodes: a graph with far fewer edges than
+    nodes has full bundles of 32 destinations once those make 12 288 items, small
+    graphs finer ones."""
+    rgnn = _rgnn()
+    rng = np.random.default_rng(N + E)
+    src, dst = (rng.integers(0, N, E, dtype=np.int32) for _ in range(2))
+    g = rgnn.Graph.from_coo(N, 1, 2, src, dst, rng.integers(0, 2, E, dtype=np.int32), host_only=True)
+    items = g.info()["num_items"]
+    g.close()
+    per = 8 * max(1, -(-(E // 12288) // 8))      # edges of a bundle, at least 16 and at most 64
+    per = min(64, max(16, per))
+    nodes = min(32, max(per // 2, N // 12288))   # and destinations
+    assert items <= N / nodes + 2 * E / per + 1
+    assert items >= N / 32
