@@ -51,15 +51,15 @@ int tile_rows_for(int64_t total, int64_t want, int most)
 }
 
 // The rows of each relation (sorted by destination) cut where the destination
-// crosses a multiple of `span` node ids, at most tile_rows rows per tile; the
+// crosses a multiple of kDstRange node ids, at most tile_rows rows per tile; the
 // tiles of eight consecutive destination ranges are interleaved (range i of a
 // group at tile positions i, i + 8, ...; empty tiles fill the gaps), so that
 // the tiles of one range -- one per relation that enters it -- land on the same
 // XCD (workgroups are dealt to the eight XCDs in turn) at about the same time:
 // a destination row gathered by several relations' tiles is read from HBM once
 // and from that XCD's L2 after that.  Only for graphs that dst_ranges_pay accepts.
-void build_tiles_dst_ranges(const std::vector<int32_t> &rel_ptr, const std::vector<int32_t> &row_dst, int32_t span,
-                            int tile_rows, std::vector<Tile> &out)
+void build_tiles_dst_ranges(const std::vector<int32_t> &rel_ptr, const std::vector<int32_t> &row_dst, int tile_rows,
+                            std::vector<Tile> &out)
 {
     out.clear();
     const int R = (int)rel_ptr.size() - 1;
@@ -68,9 +68,9 @@ void build_tiles_dst_ranges(const std::vector<int32_t> &rel_ptr, const std::vect
     std::vector<Chunk> ch;
     for (int r = 0; r < R; ++r)
         for (int32_t i = rel_ptr[r]; i < rel_ptr[r + 1];) {
-            const int32_t rg = row_dst[i] / span;
+            const int32_t rg = row_dst[i] / kDstRange;
             int32_t j = i;
-            while (j < rel_ptr[r + 1] && row_dst[j] / span == rg && j - i < tile_rows) ++j;
+            while (j < rel_ptr[r + 1] && row_dst[j] / kDstRange == rg && j - i < tile_rows) ++j;
             ch.push_back(Chunk{rg, r, i, j - i});
             i = j;
         }
@@ -103,19 +103,19 @@ void build_tiles_dst_ranges(const std::vector<int32_t> &rel_ptr, const std::vect
 }
 
 // Whether the segments of each relation lie in runs of at least kDstRangeRows per
-// range of `span` destinations, weighted by rows (the run that a row is in).  Every
+// range of kDstRange destinations, weighted by rows (the run that a row is in).  Every
 // run is a tile of its own that stages a whole weight, and their number grows with
 // the relations, not with the rows: by destination range a graph of 300 000 nodes
 // and 535 relations has 216 000 tiles of 5 rows, by relation 2 500.
-bool dst_ranges_pay(const std::vector<int32_t> &rel_ptr, const std::vector<int32_t> &row_dst, int32_t span)
+bool dst_ranges_pay(const std::vector<int32_t> &rel_ptr, const std::vector<int32_t> &row_dst)
 {
     const int R = (int)rel_ptr.size() - 1;
     double sq = 0;
     for (int r = 0; r < R; ++r)
         for (int32_t i = rel_ptr[r]; i < rel_ptr[r + 1];) {
-            const int32_t rg = row_dst[i] / span;
+            const int32_t rg = row_dst[i] / kDstRange;
             int32_t j = i;
-            while (j < rel_ptr[r + 1] && row_dst[j] / span == rg) ++j;
+            while (j < rel_ptr[r + 1] && row_dst[j] / kDstRange == rg) ++j;
             sq += (double)(j - i) * (j - i);
             i = j;
         }
@@ -277,6 +277,8 @@ rgnn_status build_host_index(int64_t N, int32_t T, int32_t R, int64_t E, const i
                 sq += (int64_t)n * n;
             }
             g->fused_long = E > 0 && sq >= kFusedLongEdges * E;
+            // first in-edge position of a fused row: the rows lie one after another
+            auto first_edge = [&](int32_t row) { return row < g->V ? x.fused_rows[(size_t)row].e0 : (int32_t)E; };
             auto cut = [&](int max_rows, int max_edges, std::vector<Tile> &out) {
                 out.clear();
                 for (int32_t r = 0; r < R; ++r) {
@@ -286,8 +288,7 @@ rgnn_status build_host_index(int64_t N, int32_t T, int32_t R, int64_t E, const i
                         int32_t rows = 0, edges = 0;
                         while (rows < max_rows && r0 + rows < end) {
                             const int32_t nb = std::min<int32_t>(16, end - (r0 + rows));
-                            int32_t be = 0;
-                            for (int32_t j = 0; j < nb; ++j) be += x.fused_rows[r0 + rows + j].ne;
+                            const int32_t be = first_edge(r0 + rows + nb) - first_edge(r0 + rows);
                             if (rows > 0 && edges + be > max_edges) break;
                             rows += nb;
                             edges += be;
@@ -465,8 +466,8 @@ rgnn_status build_host_index(int64_t N, int32_t T, int32_t R, int64_t E, const i
             const int rows[2] = {tile_rows_for(total, kGemmTilesWanted, kGemmTileRows),
                                  tile_rows_for(total, kGemmTilesWantedWide, kGemmTileRows)};
             if (t == kRowsVsegsDst) {   // the narrow shapes of large graphs; else gemm_tiles() gives kRowsVsegs
-                if (rows[0] < kGemmTileRows || !dst_ranges_pay(x.rel_vsegptr, x.vsegdst_byrel, kGemmTileRows)) continue;
-                build_tiles_dst_ranges(x.rel_vsegptr, x.vsegdst_byrel, kGemmTileRows, kGemmTileRows, x.gemm_tiles[t][0]);
+                if (rows[0] < kGemmTileRows || !dst_ranges_pay(x.rel_vsegptr, x.vsegdst_byrel)) continue;
+                build_tiles_dst_ranges(x.rel_vsegptr, x.vsegdst_byrel, kGemmTileRows, x.gemm_tiles[t][0]);
             }
             for (int w = 0; w < (rows[1] != rows[0] ? 2 : 1) && t != kRowsVsegsDst; ++w)
                 build_tiles(*type_ptr[t], rows[w], x.gemm_tiles[t][w]);

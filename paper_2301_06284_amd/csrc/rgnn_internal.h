@@ -82,6 +82,7 @@ constexpr int64_t kMinBundleEdges = 16;
 // rows stay in L2 either way, by relation was never slower (mag-like 12 000 nodes
 // 148.9 / 142.4 us, 20 000 nodes and 100 relations 385 / 327).
 constexpr int kDstRangeRows = 192;
+constexpr int32_t kDstRange = 512;   // destinations per range
 
 struct Tile {          // one typed-GEMM tile: rows [row0, row0 + rows) of type `type`
     int32_t type, row0, rows, pad;

@@ -15,7 +15,7 @@
 //                      write its info and every exported index array to <out>
 //   errors             invalid inputs -> the documented status codes
 //   tiles              the tile count of one type at the ends of its range
-//   tables <in>        the typed-GEMM tile tables of the graph described by <in>:
+//   tables <in>        the typed-GEMM and fused tile tables of the graph described by <in>:
 //                      every row in one tile of its type, and the tile counts
 //   nomem <in>         fail the k-th allocation of a graph creation, for every
 //                      k until a creation runs without failure
@@ -259,6 +259,22 @@ static int mode_tables(const char *in)
         }
         const rgnn::TileTable u = G->gemm_tiles((rgnn::GemmRows)t);
         std::printf("%s %lld %lld %lld\n", name[t], (long long)ptr[t]->back(), (long long)u.n_narrow, (long long)u.n_wide);
+    }
+    // fused tiles: consecutive rows of one relation with their first in-edge, no more
+    // rows or (beyond the first 16-row block) edges than the kernels stage
+    for (int w = 0; w < 2; ++w) {
+        const auto &tt = w ? x.tiles_fused_wide : x.tiles_fused;
+        bool ok = covers(tt, x.rel_vsegptr) && (int64_t)tt.size() == (w ? G->n_tiles_fused_wide : G->n_tiles_fused);
+        for (const rgnn::Tile &t : tt) {
+            int64_t edges = 0, first = 0;
+            for (int32_t r = 0; ok && r < t.rows; ++r) {
+                edges += x.fused_rows[(size_t)t.row0 + r].ne;
+                if (r < 16) first = edges;
+            }
+            ok = ok && t.rows <= rgnn::kFusedTileRows && t.pad == x.fused_rows[(size_t)t.row0].e0 &&
+                 (edges <= (w ? rgnn::kFusedTileEdgesWide : rgnn::kFusedTileEdges) || edges == first);
+        }
+        if (!ok) { std::printf("FAIL fused table %d\n", w); rc = 1; }
     }
     std::printf("own_dst_ranges %d\n", (int)(G->n_gemm_tiles[rgnn::kRowsVsegsDst][0] > 0));
     rgnn_graph_destroy(G);

@@ -117,7 +117,7 @@ def test_tile_counts_under_sanitizers(exe):
     assert rc == 0 and "ok tile counts" in log, log
 
 
-@pytest.mark.parametrize("N,E,R,dst_ranges", [(0, 0, 3, False), (40, 0, 3, False), (200, 3000, 5, False),
+@pytest.mark.parametrize("N,E,R,dst_ranges", [(0, 0, 3, False), (40, 0, 3, False), (200, 3000, 5, False), (300, 90000, 3, False),
                                               (10000, 80000, 40, False), (60000, 300000, 300, False),
                                               (110000, 500000, 40, False), (110000, 800000, 7, True)])
 def test_gemm_tables_under_sanitizers(exe, tmp_path, N, E, R, dst_ranges):
