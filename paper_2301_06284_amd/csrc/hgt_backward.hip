@@ -626,14 +626,14 @@ size_t hgt_bwd_layout(const rgnn_graph *g, int D, int H, void *base, HgtBwdWs *w
     HgtBwdWs x{};
     const bool typed = fold_types(g, D, H);   // as hgt_backward_d
     x.KV = take(N * 2 * D); x.Q = take(typed && !forward_queries_in_kernel(g, D, H) ? 0 : N * D);
-    x.Wqp = take(R * D * D); x.QD = take(V * 2 * D);
+    x.Wqp = take(typed && !forward_queries_in_kernel(g, D, H) ? 0 : R * D * D); x.QD = take(V * 2 * D);
     x.agg = take(N * D); x.partial = take(slots * (2 * H + D)); x.saved = take(N * H * 2);
     x.dagg = take(typed ? 0 : N * D); x.Wmt = take(R * D * D);
     x.Sal = take(V * D); x.Bac = take(V * D);
     x.spart = take(slots * H);
     x.dQP = take(V * D); x.Tq = take(V * D);
     x.dKV = take(N * (typed ? 2 : 3) * D);   // dK | dV (| dQ) side by side per node
-    x.Wc = take((size_t)g->T * D * 3 * D);
+    x.Wc = take(D <= 64 ? (size_t)g->T * D * 3 * D : 0);
     x.chunks = take(nchunks * D * D); x.chunks2 = take(nchunks * D * D); x.OT = take(R * D * D); x.M2 = take(R * D * D);
     x.rec = take(N * H * 4);
     x.Wf = take(R * D * D); x.Wg = take(typed ? R * D * D : 0);
@@ -728,9 +728,10 @@ rgnn_status hgt_backward_d(const rgnn_graph *g, const float *h, const float *Wk,
         const unsigned nr = blocks_for((int64_t)g->R * D * D, 256);
         {
             LaunchScope ls("hgt_bwd_weights", s);
-            hipLaunchKernelGGL(hgt_bwd_weights_kernel, dim3(2 * nr + blocks_for((int64_t)g->T * D * 2 * D, 256)),
-                               dim3(256), 0, s, Wk, Wv, Wq, fold_a ? Wa : nullptr, Watt, Wmsg, mu, g->dev.rel_dsttype,
-                               att_scale, g->R, g->T, D, H, (int)nr, w.Wf, w.Wg, w.Wc);
+            const unsigned nc = D <= 64 ? blocks_for((int64_t)g->T * D * 2 * D, 256) : 0;   // Wc's only readers
+            hipLaunchKernelGGL(hgt_bwd_weights_kernel, dim3(2 * nr + nc), dim3(256), 0, s, Wk, Wv, Wq,
+                               fold_a ? Wa : nullptr, Watt, Wmsg, mu, g->dev.rel_dsttype, att_scale, g->R, g->T, D, H,
+                               (int)nr, w.Wf, w.Wg, w.Wc);
         }
         if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "hgt_bwd_weights launch");
     }
@@ -819,7 +820,8 @@ rgnn_status hgt_backward_d(const rgnn_graph *g, const float *h, const float *Wk,
         {
             LaunchScope ls("hgt_bwd_dqp", s);
             hipLaunchKernelGGL(hgt_bwd_dqp_kernel, dim3(blocks_for(g->V, GPB * kDqpRows)), dim3(256), 0, s,
-                               g->V, D, H, g->dev.vsegdst_byrel, g->dev.dst_vsegptr, g->dev.rowptr, w.Bac, reinterpret_cast<const float4 *>(w.rec), w.dQP);
+                               g->V, D, H, g->dev.vsegdst_byrel, g->dev.dst_vsegptr, g->dev.rowptr, w.Bac,
+                               reinterpret_cast<const float4 *>(w.rec), w.dQP);
         }
         if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "hgt_bwd_dqp launch");
         GemmArgs gt;

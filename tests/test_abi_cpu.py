@@ -183,7 +183,7 @@ def test_hgt_backward_folds_by_size(d, heads):
         sizes = []
         for T, ntype in ((1, np.zeros(N, np.int32)), (2, rng.integers(0, 2, N, dtype=np.int32))):
             g = rgnn.Graph.from_coo(N, T, R, ends[0], ends[1], rel, ntype, host_only=True)
-            sizes.append(rgnn.workspace_size(g, rgnn.LAYER_HGT_BACKWARD, d, d, heads) - T * d * 3 * d * 4)
+            sizes.append(rgnn.workspace_size(g, rgnn.LAYER_HGT_BACKWARD, d, d, heads) - (T * d * 3 * d * 4 if d <= 64 else 0))
             g.close()
         chunks = 2 * 2 * d * d * 4 * 32 + 4096   # at most one chunk more per node type, and padding
         if folded:
@@ -208,3 +208,23 @@ def test_work_items_of_sparse_graphs(N, E):
     nodes = min(32, max(per // 2, N // 12288))   # and destinations
     assert items <= N / nodes + 2 * E / per + 1
     assert items >= N / 32
+
+
+@pytest.mark.parametrize("d,heads,kept", [(32, 2, 1), (64, 4, 1), (128, 2, 0)])
+def test_hgt_backward_workspace_of_typed_relations(d, heads, kept):
+    """Folded weights need no query weights of their own, and the node weights side by
+    side ([T, d, 3 d]) only at d <= 64: the workspace grows with R and T by the
+    arrays that are used."""
+    rgnn = _rgnn()
+
+    def size(R, T):
+        N = 100
+        g = rgnn.Graph.from_coo(N, T, R, [0] * 4, [1] * 4, [0] * 4, np.zeros(N, np.int32), host_only=True)
+        n = rgnn.workspace_size(g, rgnn.LAYER_HGT_BACKWARD, d, d, heads)
+        g.close()
+        return n
+    mat = d * d * 4
+    heads_part = -(-(heads * (d // heads) ** 2) // 256) * 4   # shares of dmu per relation
+    per_rel = 5 * mat + heads_part                            # Wmt, OT, M2, Wf, Wg
+    assert abs(size(32, 1) - size(16, 1) - 16 * per_rel) <= 512
+    assert size(32, 65) - size(32, 1) == kept * 64 * 3 * mat
