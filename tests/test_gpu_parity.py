@@ -1177,3 +1177,108 @@ def test_segment_gemm_thousands_of_types(T):
     for _ in range(3):
         check(g.replay)
         check(call)
+
+
+@pytest.mark.parametrize("K,Nc", [(32, 32), (64, 64), (128, 128), (64, 128), (128, 64)])
+def test_segment_gemm_full_tiles(K, Nc):
+    """Tiles of 512 rows (the smallest workspace the call takes leaves room for no
+    others), every wave with several row blocks: gathered and scattered rows, types
+    that end inside a block, after one, in the next tile's first; rows over twelve
+    decades, each entry within a few fp32 roundoffs of the exact product."""
+    import torch
+    from paper_2301_06284_amd import rgnn
+    rng = np.random.default_rng(7 * K + Nc)
+    counts = np.array([511, 0, 512, 513, 1, 1025, 700, 495, 16, 3000])
+    type_ptr = np.concatenate([[0], np.cumsum(counts)]).astype(np.int64)
+    M, T = int(type_ptr[-1]), len(counts)
+    X = (rng.standard_normal((M + 50, K)) * 10.0 ** rng.uniform(-6, 6, (M + 50, 1))).astype(np.float32)
+    W = (rng.standard_normal((T, K, Nc)) * 10.0 ** rng.uniform(-3, 3, (T, 1, Nc))).astype(np.float32)
+    gather = rng.integers(0, M + 50, M).astype(np.int32)
+    scatter = rng.permutation(M + 9)[:M].astype(np.int32)
+    least = (((M + 511) // 512 + T) * 16 + 255) // 256 * 256
+    print(f"segment_gemm full tiles {K}x{Nc}", flush=True)
+    dev = torch.device("cuda:0")
+    Y = torch.full((M + 9, Nc), float("nan"), device=dev)
+    rgnn.segment_gemm(torch.from_numpy(X).to(dev), torch.from_numpy(gather).to(dev), type_ptr,
+                      torch.from_numpy(W).to(dev), Y, torch.from_numpy(scatter).to(dev),
+                      torch.empty(least, dtype=torch.uint8, device=dev), K, Nc)
+    torch.cuda.synchronize()
+    got = Y.cpu().numpy().astype(np.float64)
+    assert np.isnan(got[np.setdiff1d(np.arange(M + 9), scatter)]).all()
+    for t in range(T):
+        rows = np.arange(type_ptr[t], type_ptr[t + 1])
+        x, w = X[gather[rows]].astype(np.float64), W[t].astype(np.float64)
+        if len(rows):
+            err = np.abs(got[scatter[rows]] - x @ w) / (2.0 ** -24 * (np.abs(x) @ np.abs(w)))
+            assert err.max() <= 8.0
+
+
+def check_layers(g, d, heads, hgt_heads, seed):
+    """Forward and backward of every layer and plan at width d against the oracle.
+
+    RGAT's dh of a node without out-edges is a sum of softmax Jacobian terms that
+    nearly cancel when its relations' vectors point the same way.  The terms are of the
+    median row's size, so fp32 leaves about 2^-24 of that (measured: 4e-8): below
+    1e-3 of the median that alone can exceed 1e-4 of the row (2^-24 / 1e-4 = 6e-4),
+    and such rows are measured against the median row."""
+    t = workloads.tiny_tensors(seed, g, d, d, heads=max(hgt_heads))
+    isolated = (np.bincount(g["src"], minlength=g["N"]) + np.bincount(g["dst"], minlength=g["N"])) == 0
+    run = Runner(g, t)
+    ref = oracle.rgcn_forward(g, t["h"], t["W"], t["W0"], relu=True)
+    for plan in (1, 2):
+        assert row_err(run.rgcn(plan=plan, relu=True), ref) <= TOL
+    for a, b in zip(run.rgcn_backward(), oracle.rgcn_backward(g, t["h"], t["W"], t["W0"], t["grad_out"])):
+        assert row_err(a.reshape(-1, d), b.reshape(-1, d)) <= TOL
+    print("  rgcn", flush=True)
+    for plan, H, scope in ((1, heads, 0), (2, 1, 0), (2, 1, 1)):
+        ref = oracle.rgat_forward(g, t["h"], t["W"], t["w_src"], t["w_dst"], heads=H, scope=scope)
+        assert row_err(run.rgat(heads=H, plan=plan, scope=scope), ref) <= TOL
+    for H in {1, heads}:
+        got, ref = run.rgat_backward(heads=H), rgat_backward_ref(g, t, heads=H)
+        assert row_err(got[0], ref[0], structural_zero=isolated, cancel_floor=1e-3) <= TOL
+        for a, b in zip(got[1:], ref[1:]):
+            assert row_err(a.reshape(-1, d), b.reshape(-1, d), cancel_floor=1e-6) <= TOL
+    run.close()
+    print("  rgat", flush=True)
+    for H in hgt_heads:
+        t = workloads.tiny_tensors(seed, g, d, d, heads=H)
+        args = [t[k] for k in ("h", "Wk", "Wq", "Wv", "Wa", "Watt", "Wmsg", "mu")]
+        run = Runner(g, t)
+        assert row_err(run.hgt(H, 0.25), oracle.hgt_forward(g, *args, heads=H, att_scale=0.25)) <= TOL
+        ref = oracle.hgt_backward(g, *args, t["grad_out"], heads=H, att_scale=0.25)
+        for use_saved in (False, True):
+            check_hgt_grads(run.hgt_backward(H, 0.25, use_saved=use_saved), ref, H, d)
+        run.close()
+        print(f"  hgt {H}", flush=True)
+
+
+@pytest.mark.parametrize("kind", ["hub", "srchub", "typedhub"])
+@pytest.mark.parametrize("d", [32, 64, 128])
+def test_layers_with_several_blocks_per_wave(d, kind):
+    """Graphs large enough that a tile gives every wave several 16-row blocks (GEMM
+    tiles of 128 to 192 rows and fused ones of 128 to 192 for the narrow shapes, 320
+    to 512 and 256 rows at 128 x 128), with ragged ends and hubs: every layer, plan
+    and backward, HGT with narrow and wide heads."""
+    g = workloads.tiny_graph(101, N=20000, E=200000 if kind != "typedhub" else 400000, R=12, T=3, kind=kind)
+    print(f"several blocks per wave d={d} {kind}", flush=True)
+    check_layers(g, d, heads=d // 16, hgt_heads=sorted({1, d // 16}), seed=101)
+
+
+@pytest.mark.parametrize("d_in,d_out", [(64, 128), (128, 64)])
+@pytest.mark.parametrize("plan", [1, 2])
+def test_rgcn_dims_several_blocks(d_in, d_out, plan):
+    g = workloads.tiny_graph(103, N=20000, E=200000, R=12, T=1, kind="hub")
+    t = workloads.tiny_tensors(103, g, d_in, d_out)
+    print(f"rgcn dims, several blocks {d_in}->{d_out} plan={plan}", flush=True)
+    run = Runner(g, t)
+    for relu in (False, True):
+        ref = oracle.rgcn_forward(g, t["h"], t["W"], t["W0"], relu=relu)
+        assert row_err(run.rgcn(plan=plan, relu=relu), ref) <= TOL
+    run.close()
+
+
+def test_layers_of_a_sparse_graph():
+    """Far fewer edges than nodes: bundles of many destinations with few edges."""
+    g = workloads.tiny_graph(105, N=200000, E=3000, R=5, T=3, kind="random")
+    print("sparse graph", flush=True)
+    check_layers(g, 32, heads=2, hgt_heads=[1, 2], seed=105)
