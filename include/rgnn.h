@@ -29,10 +29,15 @@
  *     allocates no device memory inside the layer calls.  Two calls may run
  *     concurrently on different streams only with distinct workspaces.
  *   - On error nothing is enqueued and rgnn_last_error() describes the cause.
- *   - Arithmetic is fp32-accurate.  The forward layers' dense transforms form
- *     each fp32 product from exact three-piece bf16 splits on the bf16 matrix
- *     cores (see rgnn_segment_gemm), so their inputs (features, weights) must be
- *     finite with magnitude below 3.38e38.
+ *   - Arithmetic is fp32-accurate.  At widths of 64 and 128 the dense transforms
+ *     of the forward layers, of the RGCN and HGT backward and of the segment GEMM,
+ *     and every backward's outer products at 128, form each fp32 product from exact
+ *     three-piece bf16 splits on the bf16 matrix cores (see rgnn_segment_gemm), so
+ *     their inputs (features, weights, output gradients) must be finite with
+ *     magnitude below 3.38e38.  The aggregate-first transform, the RGAT backward's
+ *     transforms, HGT's combined K|V|Q products at d = 64 (relations with mixed
+ *     destination types) and the outer products at 32 and 64 run on the fp32 matrix
+ *     cores.
  */
 #ifndef RGNN_H
 #define RGNN_H
@@ -264,10 +269,8 @@ rgnn_status hgt_forward(const rgnn_graph_t *g, const float *h, const float *Wk, 
  * [N, heads, 2]; RGNN_SOFTMAX_PER_DST_REL with the forward's per-segment
  * saved [num_dst_segments, heads, 2].  d_in = d_out in {32, 64, 128}, d_out / heads
  * a multiple of 16.
- * Several heads run as one pass per head over the weights, attention vectors
- * and grad_out with the other heads' columns zeroed (each head's logits,
- * softmax and messages read only its own columns, so the per-head gradients
- * add up to the exact ones); the cost grows with the heads.  Workspace:
+ * Several heads run in one pass over the graph, on the messages h W_r, of which
+ * each head owns its columns.  Workspace:
  * rgnn_workspace_size(RGNN_LAYER_RGAT_BACKWARD, d_in, d_out, heads). */
 rgnn_status rgat_backward(const rgnn_graph_t *g, const float *h, const float *W,
                           const float *w_src, const float *w_dst, int32_t d_in, int32_t d_out,
@@ -303,8 +306,7 @@ rgnn_status rgcn_backward(const rgnn_graph_t *g, const float *h, const float *W,
  * NULL), grad_Watt, grad_Wmsg [R, heads, dk, dk] and grad_mu [R].  saved: the
  * forward's softmax statistics [N, heads, 2] from hgt_forward with the same
  * inputs, or NULL, in which case the forward traversal is recomputed inside
- * the call (with saved given, the aggregate that grad_Wa needs is rebuilt from
- * the backward's own per-segment sums instead).  d in {32, 64, 128},
+ * the call.  d in {32, 64, 128},
  * d / heads >= 16.  Workspace:
  * rgnn_workspace_size(RGNN_LAYER_HGT_BACKWARD, d, d, heads).  Results are
  * reproducible except the K|V gradient rows of sources with more than 64
@@ -333,8 +335,8 @@ rgnn_status hgt_backward(const rgnn_graph_t *g, const float *h, const float *Wk,
  *   {64, 128} each product is formed from an exact split of both operands into
  *   three bf16 pieces on the bf16 matrix cores (six piece products accumulated
  *   in fp32; the dropped ones are below 2^-23 |x||w|); X and W must then be
- *   finite with magnitude below 3.38e38.  The forward layers use the same
- *   products. */
+ *   finite with magnitude below 3.38e38.  The layers' transforms use the same
+ *   products (see the conventions above). */
 rgnn_status rgnn_segment_gemm(const float *X, int64_t ldx, const int32_t *gather,
                               const int64_t *type_ptr, int32_t num_types, const float *W,
                               int32_t K, int32_t Nc, float *Y, int64_t ldy,

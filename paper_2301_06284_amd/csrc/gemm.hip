@@ -1,11 +1,12 @@
-// gemm.hip -- typed / segment GEMM on fp32 MFMA:  Y[S[i]] = X[G[i]] x W[t(i)].
+// gemm.hip -- typed / segment GEMM on MFMA, fp32 in and out:  Y[S[i]] = X[G[i]] x W[t(i)].
 //
 // This is the GEMM template of the paper (Section "The GEMM Template and the
 // Traversal Template", Y[S] = X[G] x W[T] with gather list G, scatter list S
 // and a per-row type T), written for gfx950:
-//   * rows are pre-grouped by type; a host-built tile table gives every
-//     workgroup one tile of at most kGemmTileRows rows of a single type, so
-//     one launch covers all types (no per-type kernel loop);
+//   * rows are pre-grouped by type; a tile table (built with the graph; for the
+//     segment GEMM's entry on the device, or by the host for thousands of types)
+//     gives every workgroup one tile of at most kGemmTileRows rows of a single
+//     type, so one launch covers all types (no per-type kernel loop);
 //   * the tile's weight W[t] (K x Nc fp32) is staged once in LDS, transposed
 //     so that each lane fetches four k-values of one column with ds_read_b128;
 //   * each wave computes 16-row blocks with v_mfma_f32_16x16x4f32: the A rows
@@ -20,8 +21,9 @@
 //     selected at compile time, with its operand loads issued before the
 //     next block's prefetch.
 //
-// Split-bf16 products (the 64-deep shapes): the fp32 MFMA rate, not HBM,
-// bounds these GEMMs (16 flop per byte at d = 64, near the fp32 ridge).  Each
+// Split-bf16 products (K and Nc of 64 and 128, where the caller asks for them): the
+// fp32 MFMA rate, not HBM, would bound these GEMMs (16 flop per byte at d = 64, near
+// the fp32 ridge).  Each
 // fp32 operand x is split exactly into three bf16 pieces, x = x1 + x2 + x3
 // (x1 = RN_bf16(x), x2 = RN_bf16(x - x1), x3 = x - x1 - x2, which needs at
 // most 8 significant bits and so is exact in bf16), and the product is

@@ -248,9 +248,9 @@ __global__ __launch_bounds__(kBlock) void hgt_kernel(HK k)
 // beyond 160 KB of matrices, from L2) takes longer than the segment's gathers when
 // dk is large: on 200 000 nodes and 1.5M edges the traversal took 0.685 ms at d =
 // 64 with one head of 64 against 0.173 ms with four of 16, and 2.41 ms at d = 128
-// with one head (hgt_seg_values has the rule and both sides).  Each segment keeps an online softmax of its
-// own, (max, sum) per head and the value sum relative to that max; the
-// destination's softmax is finished when the transformed rows are summed.
+// with one head (hgt_seg_values has the rule and both sides).  Each segment keeps an
+// online softmax of its own, (max, sum) per head and the value sum relative to that
+// max; the destination's softmax is finished when the transformed rows are summed.
 // No destination boundaries, weights or queries in LDS: 256-thread workgroups at
 // the occupancy that the registers allow.
 struct HSegK {
@@ -346,8 +346,8 @@ __global__ __launch_bounds__(256) void hgt_seg_kernel(HSegK k)
     }
 }
 
-// out_t = sum_i exp(m_i - M) T_i / Z per head over t's segments i (+ residual), M = max m_i,
-// Z = sum s_i exp(m_i - M), (M, Z) to saved: a group of D / 4 lanes per
+// out_t = sum_i exp(m_i - M) T_i / Z per head over t's segments i (+ residual), with
+// M = max m_i and Z = sum s_i exp(m_i - M), (M, Z) to saved: a group of D / 4 lanes per
 // destination merges its segments' states online, four rows in flight.  Blocks [0,
 // nbig) take the destinations of big_vdst, the groups of a workgroup each a
 // strided share, the groups' states merged in group order.
@@ -531,7 +531,9 @@ hipError_t launch_hgt_shape(const HK &k, int64_t n_items, int R, hipStream_t s)
 // Whether Wmsg leaves the traversal for a GEMM over the segments (see "wide
 // heads"): always for dk >= 64, for dk = 32 at d = 32 and where the matrices do
 // not fit in LDS, never for dk = 16.  ms per forward, traversal -> GEMM, 200 000
-// nodes and 1.5M edges, typed graph of 7 relations / one type and 40 relations:
+// nodes and 1.5M edges, typed graph of 7 relations / one type and 40 relations (both
+// sides with the query GEMM's tiles by destination range; with 40 relations it takes
+// them by relation since, 0.02 ms less at d = 64 and 0.16 at d = 128):
 //   d = 64,  1 head of 64   0.80 -> 0.32 / 1.46 -> 0.69
 //   d = 128, 1 head of 128  2.72 -> 0.71,  2 heads of 64  1.30 -> 0.75
 //   d = 32,  1 head of 32   0.25 -> 0.16 / 0.47 -> 0.36

@@ -67,10 +67,11 @@ __device__ __forceinline__ void atomic_add4(float *p, float4 v)
 // than one item) keeps A and B of all but its last one in LDS until then, each
 // lane its own four features, and writes dQP itself; the others leave A in dQP's
 // place and B beside it for hgt_bwd_dqp_kernel.  Three segments cover the
-// destinations of graphs with a few relations per node type, and two held ones
-// are what LDS has room for at five waves per SIMD (31 KB per workgroup; a third
-// would cost one wave).  Writing A and B and combining all of them in a pass of
-// its own took 1.10 + 0.25 ms on the 950 000-node graph at d = 64, 4 heads.
+// destinations of graphs with a few relations per node type.  The registers (106 to
+// 112) allow four waves per SIMD; with two held segments the workgroup's LDS is 24
+// KB at d = 128, 31 KB at d = 64 (a third would be 39 KB and leave four) and 46 KB at
+// d = 32, where it leaves three.  Writing A and B and combining all of them in a pass
+// of its own took 1.10 + 0.25 ms on the 950 000-node graph at d = 64, 4 heads.
 constexpr int kHeldSegs = 3;
 __device__ __forceinline__ bool dqp_in_pass(int segs, int edges) { return segs <= kHeldSegs && edges <= kE; }
 
@@ -592,7 +593,10 @@ struct HgtBwdWs {
 };
 
 // the forward forms its segment queries from Q inside the traversal
-bool forward_queries_in_kernel(const rgnn_graph *g, int D, int H) { return D == 128 && hgt_fused_query_fits(g->R, D, H); }
+bool forward_queries_in_kernel(const rgnn_graph *g, int D, int H)
+{
+    return D == 128 && hgt_fused_query_fits(g->R, D, H);
+}
 // Whether the node-type weights are folded into the per-relation ones (typed
 // relations only).  The folded weights and the weight gradients that follow from
 // P1 and P2 are products of about R D^2 dk terms each on the vector units, against

@@ -52,18 +52,25 @@ constexpr int kPairChunkRows = 1024;
 // idle and each workgroup with a long serial chain (a 64-row step of an outer
 // product takes about 2.9 us, so one 2048-row chunk 92 us at any graph size).
 // A table is therefore cut into about this many pieces (multiples of 64 rows,
-// at least 64; bundles of at least kMinBundleEdges edges) until the pieces reach
-// those sizes.  Measured (us per call, largest pieces -> this rule): HGT
+// at least 64, and one partial tile per type more; bundles of at least
+// kMinBundleEdges edges, and of up to kMaxDstPerItem destinations once those make
+// kItemsWanted items) until the pieces reach those sizes.  Measured (us per call, largest pieces -> this rule): HGT
 // training step on 12 000 nodes 824 -> 217, RGCN forward on 2 000 nodes 38.6 ->
 // 17.7, RGCN backward at d = 32 on 131 000 nodes 266 -> 174; half or twice the
 // counts below are within 4 % on these and slower on larger graphs (twice the
 // outer chunks: HGT backward on 950 000 nodes 5.11 -> 5.21 ms; twice the GEMM
 // tiles: HGT forward at d = 128 on 172 000 nodes 1.21 -> 1.24 ms).
-// The 128-wide shapes of the typed GEMM and of the fused kernel stage 104 KB
-// and 68 KB of weights per workgroup and run one and two workgroups per CU: they
-// take tables of their own ("wide") with about one tile per CU.  On the tables of the narrow shapes they were slower than with the largest tiles
-// (RGCN forward at d = 128 on 48 000 nodes 103 -> 117 us, HGT on 254 000 nodes
-// 841 -> 870).
+// The 128 x 128 shapes of the typed GEMM and of the fused kernel stage 104 KB
+// and 68 KB of weights per workgroup: they take tables of their own ("wide") with
+// about 256 tiles, one per CU, which is all that the GEMM runs there (the fused
+// kernel runs two; twice the tiles were not measured for it).  On the tables of the
+// narrow shapes they were slower than with the largest tiles (RGCN forward at d = 128
+// on 48 000 nodes 103 -> 117 us, HGT on 254 000 nodes 841 -> 870).
+// The counts are a compromise: a grid that ends just past a full round of the chip
+// loses a few per cent (RGAT forward with 4 heads, d = 128, 50 000 nodes 145 -> 151
+// us, RGCN forward on 100 000 nodes and 300 relations 95 -> 100), at other sizes with
+// any other count (8192 items: that RGAT 140, but HGT on 85 000 nodes 221 -> 242;
+// 512 narrow tiles: that RGCN 95, but on 8 000 nodes 23.1 -> 23.9).
 constexpr int64_t kGemmTilesWanted = 768, kGemmTilesWantedWide = 256;
 constexpr int64_t kFusedTilesWanted = 1024, kFusedTilesWantedWide = 256;
 constexpr int64_t kOuterChunksWanted = 1024;
